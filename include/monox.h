@@ -284,6 +284,18 @@ MDX_API mdx_status mdx_set_profiling(mdx_ctx *ctx, int32_t every_n);
  *                        indices as 16-bit offsets from a per-slice base,
  *                        2 bytes per stored entry instead of 4; 0 reads the
  *                        32-bit indices.  Results are bitwise the same.
+ *   MDX_TUNE_ONCHIP_POLLS  single mesh: a solve whose matrix fits the
+ *                        registers and LDS of the device runs as one launch
+ *                        whose workgroups (at most one per CU) exchange their
+ *                        sums through memory; the value is how often a
+ *                        workgroup looks for the others' sums before the
+ *                        launch gives up and the step is solved by the
+ *                        streaming kernels, as all later ones until the next
+ *                        mdx_prepare (default 20000, about 20 ms); 0 always
+ *                        uses the streaming kernels.  MAX_GROUPS and
+ *                        SPMV_MAX_GROUPS other than their defaults and
+ *                        ITER_SCHEME 1 choose among the streaming kernels and
+ *                        so select them too, as does a profiled step.
  * MAX_GROUPS, SPMV_MAX_GROUPS and ITER_SCHEME take effect at the next
  * mdx_prepare / mdx_run;
  * the batched keys need a prepared batched context and act at once. */
@@ -297,7 +309,8 @@ enum {
     MDX_TUNE_NONTEMPORAL = 7,
     MDX_TUNE_COMPACT_COLUMNS = 8,
     MDX_TUNE_SPMV_MAX_GROUPS = 9,
-    MDX_TUNE_PERSISTENT = 10
+    MDX_TUNE_PERSISTENT = 10,
+    MDX_TUNE_ONCHIP_POLLS = 11
 };
 MDX_API mdx_status mdx_set_tuning(mdx_ctx *ctx, int32_t key, int64_t value);
 

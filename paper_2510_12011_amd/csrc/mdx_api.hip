@@ -454,6 +454,9 @@ mdx_status mdx_prepare(mdx_ctx *ctx, double dt, void *scratch, size_t scratch_by
                           hipMemcpyHostToDevice, st));
     HIPCHK(hipStreamSynchronize(st));
 
+    if (mdx_status e = build_onchip(ctx, st)) return e;
+    ctx->onchip_seen = 0;
+    ctx->onchip_off = false;
     ctx->tiling = make_tiling(ctx->npad, ctx->max_groups);
     ctx->tiling_spmv = make_tiling(ctx->npad, ctx->spmv_max_groups);
     release_graphs(ctx);
@@ -656,6 +659,11 @@ mdx_status mdx_set_tuning(mdx_ctx *ctx, int32_t key, int64_t value)
                         kPartialCap);
         ctx->spmv_max_groups = (int)value;
         if (ctx->npad > 0) ctx->tiling_spmv = make_tiling(ctx->npad, ctx->spmv_max_groups);
+        return MDX_OK;
+    case MDX_TUNE_ONCHIP_POLLS:
+        if (value < 0 || value > 1000000000)
+            return fail(ctx, MDX_ERR_INVALID_ARG, "onchip_polls must lie in [0, 10^9]");
+        ctx->onchip_polls = (int)value;
         return MDX_OK;
     case MDX_TUNE_ITER_SCHEME:
         if (value != 0 && value != 1) return fail(ctx, MDX_ERR_INVALID_ARG, "scheme is 0 or 1");

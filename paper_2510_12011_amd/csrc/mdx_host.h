@@ -52,6 +52,9 @@ struct Layout {
     size_t kdiag, kvp, feat, mlp_y, mlp_params;       // learned warm start
     size_t tile_real, grp, inst_grp, bsc, sptr_t, col_t, A32_t;   // batched form
     size_t pgrp, pinst_grp, pbar;   // batched form, persistent iteration
+    // single-launch solve: exchange slots, block maps, values, z
+    size_t words, oc_row, oc_col, oc_hptr, oc_hrow, oc_hat, oc_val64, oc_dinv64, oc_val32,
+        oc_dinv32, oc_away, oc_z;
     size_t csr_ptr, csr_col, csr_val, gv;
     size_t total;
     size_t x_xyz, x_tets, x_fibre, x_sig, x_vol, x_ek, x_cptr, x_contrib, x_total;
@@ -130,6 +133,16 @@ struct mdx_ctx {
     int nt_mode = -1;   // non-temporal matrix loads: -1 by stream size, 0 never, 1 always
     bool compact_cols = true;   // per-step kernels read col16 when it exists
 
+    // the solve in one launch (mdx_onchip.hip)
+    int onchip_polls = 20000;    // polls of an exchange before a launch gives up (0: not used)
+    OnchipPlan onchip;           // shape chosen with the mesh
+    OnchipMap onchip_map{};
+    bool onchip_ready = false;   // blocks built by the last prepare
+    int onchip_turn = 0;         // turn of the next exchange
+    uint32_t onchip_launch = 0;  // launches so far
+    uint32_t onchip_seen = 0;    // the last launch known to have given up
+    bool onchip_off = false;     // one gave up: streaming kernels until the next prepare
+
     // batched form: instances, each a contiguous row range starting on a
     // TILE boundary (a single-mesh context has one instance, rows [0, n))
     bool batched = false;
@@ -192,6 +205,7 @@ uint64_t hilbert_key(uint32_t x0, uint32_t x1, uint32_t x2, int bits);
 void hilbert_order(const std::vector<double> &xyz, int64_t p0, int64_t p1,
                    std::vector<int32_t> &out);
 void compact_columns(mdx_ctx *c);
+mdx_status build_onchip(mdx_ctx *c, hipStream_t st);
 SellView step_view(const mdx_ctx *c);
 int64_t sell_slot(const mdx_ctx *c, int64_t r, int32_t colv);
 void compute_layout(mdx_ctx *c);

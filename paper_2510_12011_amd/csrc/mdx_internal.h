@@ -60,6 +60,8 @@ struct alignas(256) Scalars {
     int32_t use_mlp;    // learned warm start: the MLP guess was chosen this step
     double beta;        // beta of the next iteration (0: restart with p = z)
     double alpha;       // alpha of the current iteration
+    uint32_t onchip_abort;   // number of the last single-launch solve that gave up (0: none)
+    int32_t onchip_turn;     // turn of the next exchange after the last single-launch solve
 };
 
 // Scalars as published to host memory (coherent pinned): the host spins on
@@ -192,6 +194,58 @@ void launch_replacement(hipStream_t s, const Tiling &t, SellView P, int max_iter
                         double *x, float *delta, double *r64, const double *dinv,
                         const float *dinv32, float *r32, float *z32, double *partial, Scalars *sc,
                         bool nt);
+
+// ---- the solve in one launch, matrix on chip (mdx_onchip.hip) ----------------
+constexpr int kOnchipGroups = 256;     // most workgroups (one per CU)
+constexpr int kOnchipThreads = 512;
+constexpr int kOnchipHaloPass = kOnchipThreads - SLICE;   // halo entries read at a time
+constexpr int kOnchipHalo = 7 * kOnchipHaloPass;          // most of a block (padded to passes)
+constexpr size_t kOnchipWords = 3 * NXCD * 2 * kOnchipGroups;   // exchange slots, all bits set before use
+// The rows cut into blocks, one per workgroup: block g's row i * 512 + t (pass
+// i, thread t) has block position (g * rows + i) * 512 + t.
+struct OnchipMap {
+    const int32_t *row;     // [position] row, -1 past the block's last
+    const uint2 *col;       // [pass][quad][thread] window positions of 4 entries: the
+                            //   block's own rows, then its halo
+    const int32_t *halo_ptr, *halo_row;   // halo: row and position of each entry
+    const uint32_t *halo_at;
+    double *val64, *dinv64;   // [pass][pair][thread][2], [position]
+    float *val32, *dinv32;    // [pass][quad][thread][4], [position]
+    float *r_away, *d_away;   // [position]: FP32 r and correction of the largest blocks
+};
+struct OnchipSolve {
+    OnchipMap map;
+    const double *z;                 // FP64 form: z0, r, x; FP32 form: r32, z32 and the
+    double *r, *x;                   //   FP64 residual, x and D^-1
+    const double *dinv;
+    const float *r32, *z32;
+    void *zb;                        // z by block position
+    const double *part;              // right-hand-side partials (part_groups > 0): the
+    int part_groups;                 //   launch forms the solve's start from them, else
+    int rel_mode;                    //   it is in the scalars
+    int max_iter, rr;
+    int polls;                       // of an exchange before the launch gives up
+    unsigned long long *words;       // kOnchipWords
+    int turn;                        // of the first exchange
+    unsigned launch;                 // number of this launch (not 0)
+    Scalars *sc;
+    Published *pub;
+    int32_t seq;
+};
+struct OnchipPlan {
+    int groups = 0;                  // 0: the matrix does not fit
+    int rows = 0, width = 0;
+    const void *shape[2] = {nullptr, nullptr};   // FP64, FP32 (null: does not fit)
+};
+// n rows, the longest of `width` entries
+OnchipPlan onchip_plan(int device, int64_t n, int width);
+void launch_onchip_values(hipStream_t s, const OnchipPlan &p, const OnchipMap &m,
+                          const int64_t *slice_ptr, const double *A, const double *dinv,
+                          const float *A32, const float *dinv32);
+// the whole solve: every exit publishes the scalars (seq); done = 0 and
+// onchip_abort = launch where it gave up (the caller forms the right-hand
+// side again and solves with the streaming kernels)
+void launch_onchip(hipStream_t s, const OnchipPlan &p, bool fp32, const OnchipSolve &a);
 
 // ---- learned warm start network (mdx_mlp.hip) ------------------------------
 int mlp_nparams();

@@ -5,6 +5,11 @@
 // a mesh or a batch of meshes.
 #include "mdx_host.h"
 
+#include <exception>
+#include <mutex>
+#include <system_error>
+#include <thread>
+
 namespace mdx {
 namespace host {
 
@@ -29,6 +34,213 @@ void compact_columns(mdx_ctx *c)
             off[e] = (uint16_t)(c->col_sell[e] - base[sl]);
     c->col16.swap(off);
     c->cbase.swap(base);
+}
+
+// Runs f(k) for k in [0, n) on a few host threads (setup only); an exception
+// (host memory) ends the call's other work and is passed on.
+template <class F>
+static void parallel_for(int n, F &&f)
+{
+    const int nt = (int)std::max(1u, std::min({8u, std::thread::hardware_concurrency(), (unsigned)n}));
+    std::atomic<int> next{0};
+    std::exception_ptr err;
+    std::mutex mu;
+    auto work = [&]() {
+        try {
+            for (int k; (k = next.fetch_add(1)) < n;) f(k);
+        } catch (...) {
+            std::lock_guard<std::mutex> g(mu);
+            err = std::current_exception();
+            next = n;
+        }
+    };
+    std::vector<std::thread> th;
+    try {
+        for (int i = 1; i < nt; ++i) th.emplace_back(work);
+    } catch (const std::system_error &) {   // no more threads: those there are do it
+    }
+    work();
+    for (std::thread &t : th) t.join();
+    if (err) std::rethrow_exception(err);
+}
+
+// Blocks of the single-launch solve: the rows cut into `groups` parts of equal
+// size by recursive coordinate bisection (each cut across the longest side of
+// the part's bounding box, in proportion to the parts on either side), each
+// part's rows ascending.  Compact parts have small halos: 4,904 rows of the
+// 1.26M-node shell share at most 2,646 with their neighbours, where a
+// contiguous range of the reverse Cuthill-McKee order would reach over its
+// whole band of 8,349 on either side.
+struct Bisection {
+    const mdx_ctx *c;
+    int32_t *rows;
+    std::vector<int64_t> end;   // of each part
+    double at(int32_t r, int ax) const { return c->xyz[3 * (int64_t)c->perm[r] + ax]; }
+    // splits part range [p, p + parts) over rows [lo, hi); returns the rows left of the cut
+    int64_t cut(int64_t lo, int64_t hi, int parts)
+    {
+        double mn[3], mx[3];
+        for (int k = 0; k < 3; ++k) {
+            mn[k] = std::numeric_limits<double>::infinity();
+            mx[k] = -mn[k];
+        }
+        for (int64_t i = lo; i < hi; ++i)
+            for (int k = 0; k < 3; ++k) {
+                const double v = at(rows[i], k);
+                mn[k] = std::min(mn[k], v);
+                mx[k] = std::max(mx[k], v);
+            }
+        int ax = 0;
+        for (int k = 1; k < 3; ++k)
+            if (mx[k] - mn[k] > mx[ax] - mn[ax]) ax = k;
+        const int64_t mid = lo + (hi - lo) * (parts / 2) / parts;
+        std::nth_element(rows + lo, rows + mid, rows + hi, [&](int32_t a, int32_t b) {
+            const double va = at(a, ax), vb = at(b, ax);
+            return va < vb || (va == vb && a < b);
+        });
+        return mid;
+    }
+    void run(int64_t lo, int64_t hi, int p, int parts)
+    {
+        if (parts == 1) {
+            std::sort(rows + lo, rows + hi);
+            end[p] = hi;
+            return;
+        }
+        const int64_t mid = cut(lo, hi, parts);
+        run(lo, mid, p, parts / 2);
+        run(mid, hi, p + parts / 2, parts - parts / 2);
+    }
+    void all(int64_t n, int parts)
+    {
+        end.assign(parts, 0);
+        struct Range { int64_t lo, hi; int p, parts; };
+        std::vector<Range> level{{0, n, 0, parts}};
+        for (int d = 0; d < 3; ++d) {   // the first cuts one after another, then in parallel
+            std::vector<Range> next(2 * level.size(), Range{0, 0, 0, 0});
+            parallel_for((int)level.size(), [&](int k) {
+                const Range r = level[k];
+                if (r.parts < 2) {
+                    next[2 * k] = r;
+                    return;
+                }
+                const int64_t mid = cut(r.lo, r.hi, r.parts);
+                next[2 * k] = {r.lo, mid, r.p, r.parts / 2};
+                next[2 * k + 1] = {mid, r.hi, r.p + r.parts / 2, r.parts - r.parts / 2};
+            });
+            level.swap(next);
+        }
+        parallel_for((int)level.size(), [&](int k) {
+            if (level[k].parts > 0) run(level[k].lo, level[k].hi, level[k].p, level[k].parts);
+        });
+    }
+};
+
+// Builds the blocks' maps and copies them to the device; leaves onchip_ready
+// false where a block's halo exceeds the window.
+mdx_status build_onchip(mdx_ctx *c, hipStream_t st)
+{
+    mdx_ctx *ctx = c;   // for HIPCHK
+    c->onchip_ready = false;
+    const OnchipPlan &o = c->onchip;
+    if (o.groups == 0) return MDX_OK;
+    const int OB = kOnchipThreads, own = o.rows * OB, quads = (o.width + 1) / 4;
+    std::vector<int32_t> rows(c->n);
+    for (int64_t i = 0; i < c->n; ++i) rows[i] = (int32_t)i;
+    Bisection cut{c, rows.data(), {}};
+    cut.all(c->n, o.groups);
+    const size_t pos = (size_t)o.groups * own;
+    std::vector<int32_t> at(c->n), row(pos, -1);
+    parallel_for(o.groups, [&](int g) {
+        const int64_t lo = g ? cut.end[g - 1] : 0;
+        for (int64_t i = lo; i < std::min(cut.end[g], lo + own); ++i) {   // equal parts fit
+            at[rows[i]] = (int32_t)((int64_t)g * own + (i - lo));
+            row[(size_t)g * own + (i - lo)] = rows[i];
+        }
+    });
+    for (int g = 0; g < o.groups; ++g)
+        if (cut.end[g] - (g ? cut.end[g - 1] : 0) > own) return MDX_OK;
+    std::vector<uint16_t> col((size_t)(o.width + 1) * pos, 0);
+    std::vector<std::vector<int32_t>> halos(o.groups);   // positions, ascending
+    std::atomic<bool> fits{true};
+    parallel_for(o.groups, [&](int g) {
+        const int32_t *br = &row[(size_t)g * own];
+        const int32_t p0 = (int32_t)((int64_t)g * own);
+        const int32_t nr = (int32_t)(cut.end[g] - (g ? cut.end[g - 1] : 0));
+        std::vector<int32_t> &halo = halos[g];
+        auto entries = [&](int32_t i, auto &&f) {   // f(entry, position of its column)
+            const int64_t b0 = c->slice_ptr[br[i] / SLICE] + br[i] % SLICE;
+            for (int j = 0; j < c->rowlen[br[i]]; ++j)
+                f(j, at[c->col_sell[b0 + (int64_t)j * SLICE]]);
+        };
+        for (int32_t i = 0; i < nr; ++i)
+            entries(i, [&](int, int32_t q) {
+                if (q < p0 || q >= p0 + own) halo.push_back(q);
+            });
+        std::sort(halo.begin(), halo.end());
+        halo.erase(std::unique(halo.begin(), halo.end()), halo.end());
+        if ((int)halo.size() > kOnchipHalo) {
+            fits = false;
+            return;
+        }
+        for (int32_t i = 0; i < nr; ++i)
+            entries(i, [&](int j, int32_t q) {
+                const int32_t w =
+                    q >= p0 && q < p0 + own
+                        ? q - p0
+                        : own + (int32_t)(std::lower_bound(halo.begin(), halo.end(), q) - halo.begin());
+                const size_t pass = (size_t)g * o.rows + i / OB;
+                col[((pass * quads + j / 4) * OB + i % OB) * 4 + j % 4] = (uint16_t)w;
+            });
+    });
+    if (!fits) return MDX_OK;   // streaming kernels
+    std::vector<int32_t> hptr(o.groups + 1, 0), hrow, hat;
+    for (int g = 0; g < o.groups; ++g) {
+        for (int32_t q : halos[g]) {
+            hrow.push_back(row[q]);
+            hat.push_back(q);
+        }
+        while (hat.size() % kOnchipHaloPass) {   // whole passes: the last entry again
+            hrow.push_back(hrow.back());
+            hat.push_back(hat.back());
+        }
+        hptr[g + 1] = (int32_t)hat.size();
+    }
+    const Layout &L = c->L;
+    HIPCHK(hipMemcpyAsync(c->dev<int32_t>(L.oc_row), row.data(), sizeof(int32_t) * row.size(),
+                          hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(c->dev<uint16_t>(L.oc_col), col.data(), sizeof(uint16_t) * col.size(),
+                          hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(c->dev<int32_t>(L.oc_hptr), hptr.data(), sizeof(int32_t) * hptr.size(),
+                          hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(c->dev<int32_t>(L.oc_hrow), hrow.data(), sizeof(int32_t) * hrow.size(),
+                          hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(c->dev<int32_t>(L.oc_hat), hat.data(), sizeof(int32_t) * hat.size(),
+                          hipMemcpyHostToDevice, st));
+    OnchipMap &m = c->onchip_map;
+    m.row = c->dev<int32_t>(L.oc_row);
+    m.col = c->dev<uint2>(L.oc_col);
+    m.halo_ptr = c->dev<int32_t>(L.oc_hptr);
+    m.halo_row = c->dev<int32_t>(L.oc_hrow);
+    m.halo_at = c->dev<uint32_t>(L.oc_hat);
+    m.val64 = c->dev<double>(L.oc_val64);
+    m.dinv64 = c->dev<double>(L.oc_dinv64);
+    m.val32 = c->dev<float>(L.oc_val32);
+    m.dinv32 = c->dev<float>(L.oc_dinv32);
+    m.r_away = c->dev<float>(L.oc_away);
+    m.d_away = m.r_away + pos;
+    launch_onchip_values(st, o, m, c->dev<int64_t>(L.slice_ptr), c->dev<double>(L.Av),
+                         c->dev<double>(L.dinv), c->dev<float>(L.A32), c->dev<float>(L.dinv32));
+    // no slot holds a value: all bits set
+    const uint64_t empty = ~(uint64_t)0;
+    double bits;
+    std::memcpy(&bits, &empty, sizeof bits);
+    launch_fill(st, (int64_t)kOnchipWords, bits, c->dev<double>(L.words));
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipStreamSynchronize(st));   // the host arrays end here
+    c->onchip_turn = 0;
+    c->onchip_ready = true;
+    return MDX_OK;
 }
 
 // the pattern as the per-step kernels read it
@@ -86,6 +298,22 @@ void compute_layout(mdx_ctx *c)
     L.stim_idx = take(sizeof(int32_t) * std::max<size_t>(nst, 1));
     L.partial = take(sizeof(double) * 3 * 3 * kPartialCap);
     L.scalars = take(sizeof(Scalars));
+    L.words = take(sizeof(uint64_t) * kOnchipWords);
+    {
+        const OnchipPlan &o = c->onchip;
+        const size_t pos = (size_t)o.groups * o.rows * kOnchipThreads, g = (size_t)o.groups;
+        L.oc_row = take(sizeof(int32_t) * pos);
+        L.oc_col = take(sizeof(uint16_t) * (o.width + 1) * pos);
+        L.oc_hptr = take(sizeof(int32_t) * (g + 1));
+        L.oc_hrow = take(sizeof(int32_t) * g * kOnchipHalo);
+        L.oc_hat = take(sizeof(int32_t) * g * kOnchipHalo);
+        L.oc_val64 = take(o.shape[0] ? sizeof(double) * (o.width + 1) * pos : 1);
+        L.oc_dinv64 = take(o.shape[0] ? sizeof(double) * pos : 1);
+        L.oc_val32 = take(o.shape[1] ? sizeof(float) * (o.width + 1) * pos : 1);
+        L.oc_dinv32 = take(o.shape[1] ? sizeof(float) * pos : 1);
+        L.oc_away = take(o.shape[1] ? 2 * sizeof(float) * pos : 1);
+        L.oc_z = take(sizeof(double) * pos);
+    }
     L.A32 = take(sizeof(float) * ns);
     L.dinv32 = take(sizeof(float) * np);
     L.r32 = take(sizeof(float) * np);
@@ -645,6 +873,14 @@ mdx_status set_mesh_impl(mdx_ctx *ctx, int32_t n_inst, const int64_t *node_ptr, 
     ctx->rowlen.swap(rowlen);
     compact_columns(ctx);
     ctx->batched = batched;
+    ctx->onchip = OnchipPlan{};
+    if (!batched && ctx->device >= 0) {
+        int width = 0;
+        for (int64_t sl = 0; sl < nslices; ++sl)
+            width = std::max(width, (int)((ctx->slice_ptr[sl + 1] - ctx->slice_ptr[sl]) / SLICE));
+        HIPCHK(hipSetDevice(ctx->device));
+        ctx->onchip = onchip_plan(ctx->device, n_nodes, width);
+    }
     ctx->n_inst = n_inst;
     ctx->inst_node_ptr.assign(node_ptr, node_ptr + n_inst + 1);
     ctx->inst_row0.swap(row0);

@@ -1,0 +1,814 @@
+// The PCG solve of one step in a single launch, with the matrix on chip.
+//
+// A solve reads the same matrix once per iteration.  On a mesh whose matrix
+// fits the register files (512 KB a CU, 128 MB in all) and the LDS, the
+// streaming kernels (mdx_solver.hip, mdx_mixed.hip) spend an iteration on
+// re-reading it and on four to five launches of 2-5 us each.  Here the rows
+// are cut into one compact block per CU (recursive coordinate bisection,
+// onchip_partition in mdx_layout.hip); a 512-thread workgroup loads its block's
+// values into registers and their 16-bit local columns into LDS once per solve
+// and keeps r, p, q, x (or the FP32 form's correction) in registers until the
+// end.  z of the block and of its halo (the neighbouring blocks' rows that its
+// columns name) lies in LDS, so a row's gathers are LDS reads; per iteration
+// only the halo and one or two FP64 sums per exchange cross workgroups.
+//
+// What bounds it: the two exchanges.  Of an iteration of the 442,401-node FP64
+// slab (17.2 a step; 256 workgroups of 4 rows a thread) the products take
+// 1.1 us, the update 0.7, the halo 0.9 and each exchange 3 (1.3 with 20
+// workgroups); an exchange alone measured 1.8 us at 256 workgroups, 3.0 with
+// one copy of the slots, 2.1-2.3 over two levels.  Time steps before -> after
+// (streaming kernels -> this): 9,261-node cube 283 -> 83 us, 58,176-node slab
+// 406 -> 143, 442,401-node slab 696 -> 292, FP32 iteration on 871,221 nodes
+// 464 -> 331, on the 1,255,450-node shell with the network 727 -> 684.
+// Gathering z through the caches instead of LDS took 4.3 us of the FP64 slab's
+// iteration and 14 of the shell's.
+//
+// Iteration k (Algorithm 1, A being linear as in the two-kernel schemes):
+//   q = A z_k + beta_k q, p = z_k + beta_k p; exchange p.q; alpha_k;
+//   x += alpha p, r -= alpha q, z = D^-1 r (to LDS and written through);
+//   exchange r.z and z.z; stopping test, beta_{k+1}; halo of z.
+// The FP32 form's residual replacement (mdx_mixed.hip) happens in the same
+// launch: the correction takes z's place in the window, r64 -= A delta in
+// FP64, x64 += delta, an exchange, the test on the true residual.
+//
+// Exchange: every workgroup writes its partial sums to its slots and polls all
+// workgroups' slots until none holds the empty word, then sums them in slot
+// order: all workgroups form the same bits and take the same branch, no
+// counter is contended, and a value and its arrival are one 8-byte access.
+// Slots are kept once per XCD (fewer pollers per line) and in three turns: on
+// leaving exchange e a workgroup empties its slots of exchange e - 1 (every
+// workgroup has left that one: it has written e), and they are empty before it
+// writes e + 1, so before any workgroup looks for e + 2 in them.  What crosses workgroups is stored and loaded with agent scope
+// (write-through past the XCD's L2, read past it) and complete (vmcnt) before
+// the slot is written, so no cache is flushed or invalidated.
+//
+// The wait needs every workgroup resident: at most one per CU is launched and
+// the host lets one such launch per device be in flight.  Polls are bounded:
+// where other work keeps a workgroup off the chip for long, the launch gives
+// up, marks its number in the scalars and changes nothing but scratch and x;
+// the host then forms the step's right-hand side again and solves it with the
+// streaming kernels.
+#include "mdx_device.h"
+#include "mdx_internal.h"
+
+#include <algorithm>
+
+namespace mdx {
+
+namespace {
+
+constexpr int OB = kOnchipThreads;  // threads of a workgroup
+constexpr int OW = OB / SLICE;      // its wavefronts
+constexpr int HT = kOnchipHaloPass, HR = kOnchipHalo / HT;   // halo entries of a pass, passes
+
+typedef unsigned long long u64;
+constexpr u64 kEmpty = ~0ull;       // slot without a value (a NaN no arithmetic gives)
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp0(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+// sum over the wavefront by data-parallel moves; the total is in lane 63
+__device__ __forceinline__ double wave_total63(double v)
+{
+    v += dpp0<0x111, 0xf>(v);   // row_shr:1, 2, 4, 8: lane 15 of each row of 16
+    v += dpp0<0x112, 0xf>(v);
+    v += dpp0<0x114, 0xf>(v);
+    v += dpp0<0x118, 0xf>(v);
+    v += dpp0<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+    v += dpp0<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+template <class T>
+__device__ __forceinline__ T ld_agent(const T *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ __forceinline__ void st_agent(T *p, T v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// this wavefront's stores have reached the agent's point of coherence
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+struct ExchangeLds {
+    double part[3][OW];
+    double tot[2];
+    int ok;
+};
+
+// Sum v over all threads of all G workgroups; false when the wait gave up.
+// turn: 0, 1, 2, 0, ... in successive exchanges.  during() runs once the
+// workgroup's sums are on their way: loads issued there are hidden by the wait
+// (issued before it they would hold up the sums: the store count that orders
+// them counts loads too).
+template <int NV, class F>
+__device__ __forceinline__ bool exchange(double (&v)[NV], ExchangeLds &l, const OnchipSolve &a,
+                                         int g, int G, int &turn, F &&during)
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    constexpr size_t TURN = NXCD * 2 * kOnchipGroups;   // slots of a turn: [XCD][value][workgroup]
+    u64 *const words = a.words;
+    u64 *buf = words + turn * TURN;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        const double s = wave_total63(v[k]);
+        if (lane == 63) l.part[k][w] = s;
+    }
+    stores_done();
+    __syncthreads();
+    if (w == 0) {
+        double s[NV];
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            s[k] = l.part[k][0];
+#pragma unroll
+            for (int i = 1; i < OW; ++i) s[k] += l.part[k][i];
+        }
+        if (lane < NXCD * NV) {
+            const double x = lane < NXCD ? s[0] : s[NV - 1];
+            u64 b = (u64)__double_as_longlong(x);
+            if (b == kEmpty) b = 0x7ff8000000000000ull;
+            st_agent(buf + (lane % NXCD * 2 + lane / NXCD) * kOnchipGroups + g, b);
+        }
+    }
+    during();
+    if (w == 0) {
+        buf += blockIdx.x % NXCD * (2 * kOnchipGroups);
+        constexpr int C = kOnchipGroups / SLICE;
+        double acc[NV];
+        int n = 0;
+        bool all;
+        do {
+            u64 s[C][NV];
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                if (c * SLICE < G) {
+                    const int slot = c * SLICE + lane;
+#pragma unroll
+                    for (int k = 0; k < NV; ++k)
+                        s[c][k] = slot < G ? ld_agent(buf + k * kOnchipGroups + slot) : 0ull;
+                }
+            all = true;
+#pragma unroll
+            for (int k = 0; k < NV; ++k) acc[k] = 0.0;
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                if (c * SLICE < G)
+#pragma unroll
+                    for (int k = 0; k < NV; ++k) {
+                        all = all && s[c][k] != kEmpty;
+                        acc[k] += __longlong_as_double((long long)s[c][k]);
+                    }
+            all = __all(all);
+        } while (!all && ++n < a.polls);
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            const double t = wave_total63(acc[k]);
+            if (lane == 63) l.tot[k] = t;
+        }
+        if (lane == 0) l.ok = all ? 1 : 0;
+        // empty the slots of the previous exchange, which every workgroup has
+        // left (it has written this one's): the next but one uses them again
+        const int prev = turn == 0 ? 2 : turn - 1;
+        if (lane < 2 * NXCD) st_agent(words + prev * TURN + lane * kOnchipGroups + g, kEmpty);
+    }
+    turn = turn == 2 ? 0 : turn + 1;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NV; ++k) v[k] = l.tot[k];
+    return l.ok != 0;
+}
+__device__ __forceinline__ void nothing() {}
+
+// the solve's start: either the right-hand-side pass's partials summed here
+// (every workgroup, in one fixed order) or the scalars a finalize kernel wrote
+struct Start {
+    double rho, z0, ref, floor_;
+    bool finite, done;
+};
+// (at most 4 partials a thread, loaded before the matrix so that their sum
+// does not wait for it)
+struct Partials {
+    double v[3];
+    __device__ __forceinline__ void load(const OnchipSolve &a)
+    {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) v[k] = 0.0;
+        double t[4][3];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int i = j * OB + (int)threadIdx.x;
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                t[j][k] = i < a.part_groups ? a.part[k * a.part_groups + i] : 0.0;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) v[k] += t[j][k];
+    }
+};
+__device__ __forceinline__ Start start_of(const OnchipSolve &a, Partials &q, ExchangeLds &l)
+{
+    Start s;
+    const Scalars *sc = a.sc;
+    if (a.part_groups == 0) {
+        s.rho = sc->rho[0];
+        s.z0 = sc->z0;
+        s.ref = sc->ref;
+        s.floor_ = sc->floor_;
+        s.finite = sc->nonfinite == 0;
+        s.done = sc->done != 0;
+        return s;
+    }
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    double v[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double t = wave_total63(q.v[k]);
+        if (lane == 63) l.part[k][w] = t;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        v[k] = l.part[k][0];
+#pragma unroll
+        for (int i = 1; i < OW; ++i) v[k] += l.part[k][i];
+    }
+    __syncthreads();
+    s.rho = v[0];
+    s.z0 = sqrt(v[1]);
+    const double db = sqrt(v[2]);
+    s.ref = a.rel_mode == 1 ? db : s.z0;
+    s.floor_ = 1e-15 * db;
+    s.finite = isfinite(s.z0) && isfinite(db) && isfinite(v[0]);
+    s.done = !s.finite || s.z0 <= s.floor_ || s.z0 < sc->atol;
+    return s;
+}
+
+// The outcome into the scalars and to the host (first workgroup).
+struct Outcome {
+    double rho, znorm;
+    int it, done, nonfinite, aborted;
+};
+__device__ void report(const OnchipSolve &a, const Start &s, const Outcome &o, int turn)
+{
+    if (o.aborted && threadIdx.x == 0) st_agent(&a.sc->onchip_abort, a.launch);
+    if (blockIdx.x != 0 || threadIdx.x >= SLICE) return;
+    Scalars *sc = a.sc;
+    if (threadIdx.x == 0) {
+        st_agent(&sc->rho[o.it & 1], o.rho);
+        st_agent(&sc->ref, s.ref);
+        st_agent(&sc->floor_, s.floor_);
+        st_agent(&sc->z0, s.z0);
+        st_agent(&sc->znorm, o.znorm);
+        st_agent(&sc->nonfinite, o.nonfinite);
+        st_agent(&sc->iters, o.done ? o.it : 0);
+        st_agent(&sc->replace, 0);
+        st_agent(&sc->beta, 0.0);
+        st_agent(&sc->it_next, o.it);
+        st_agent(&sc->onchip_turn, turn);
+        st_agent(&sc->done, o.aborted ? 0 : o.done);
+    }
+    stores_done();
+    publish_scalars(sc, a.pub, a.seq);
+}
+
+// This thread's rows: pass i holds row i * OB + thread of the block, if the
+// block has that many.  Local columns, four 16-bit window positions to an
+// 8-byte LDS word; the quads past LQ stay in registers.
+template <int W, int R, int LQ>
+struct Rows {
+    static constexpr int Q = (W + 3) / 4, NR = Q - LQ;
+    uint2 reg[NR > 0 ? R : 1][NR > 0 ? NR : 1];
+    __device__ __forceinline__ void load(const OnchipSolve &a, int g, uint2 (*lds)[OB])
+    {
+        const uint2 *c = a.map.col + (size_t)g * R * Q * OB + threadIdx.x;
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const uint2 v = c[(i * Q + q) * OB];
+                    if (q < LQ)
+                        lds[i * LQ + q][threadIdx.x] = v;
+                    else if constexpr (NR > 0)
+                        reg[i][q - LQ] = v;
+                }
+            }
+    }
+    __device__ __forceinline__ uint2 get(const uint2 (*lds)[OB], int i, int q, int t) const
+    {
+        if (q < LQ) return lds[i * LQ + q][t];
+        uint2 c = reg[NR > 0 ? i : 0][NR > 0 ? q - LQ : 0];
+        asm volatile("" : "+v"(c.x), "+v"(c.y));   // unpacked here, not once before the loop
+        return c;
+    }
+    // sum_j val_j x[col_j] in column order, accumulated in ACC; x in LDS
+    template <class ACC, class T>
+    __device__ __forceinline__ ACC product(const T (&val)[R][W], const uint2 (*lds)[OB], int i, int t,
+                                           const T *x) const
+    {
+        T xx[W];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const uint2 c = get(lds, i, q, t);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (4 * q + j < W) {
+                    const unsigned h = j < 2 ? c.x : c.y;
+                    xx[4 * q + j] = x[j & 1 ? h >> 16 : h & 0xffffu];
+                }
+        }
+        ACC s = 0;
+#pragma unroll
+        for (int j = 0; j < W; ++j) {
+            T v = val[i][j];
+            // converted here: kept converted across the iterations the values
+            // would take twice their registers
+            if constexpr (sizeof(ACC) != sizeof(T)) asm volatile("" : "+v"(v));
+            s += (ACC)v * (ACC)xx[j];
+        }
+        return s;
+    }
+};
+
+// Has row i's product formed here: the compiler would put the sums off and
+// hold every row's gathered values until then.
+__device__ __forceinline__ void formed(double &q) { asm volatile("" : "+v"(q)); }
+__device__ __forceinline__ void formed(float &q) { asm volatile("" : "+v"(q)); }
+
+// the values of the thread's rows, 16 bytes a load
+template <int W, int R>
+__device__ __forceinline__ void load_values(const double *__restrict__ A, double (&val)[R][W])
+{
+    constexpr int P = (W + 1) / 2;
+    const double2 *p = reinterpret_cast<const double2 *>(A) + threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+            const double2 v = p[(i * P + j) * OB];
+            val[i][2 * j] = v.x;
+            if (2 * j + 1 < W) val[i][2 * j + 1] = v.y;
+        }
+}
+template <int W, int R>
+__device__ __forceinline__ void load_values(const float *__restrict__ A, float (&val)[R][W])
+{
+    constexpr int P = (W + 3) / 4;
+    const float4 *p = reinterpret_cast<const float4 *>(A) + threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+            const float4 v = p[(i * P + j) * OB];
+            val[i][4 * j] = v.x;
+            if (4 * j + 1 < W) val[i][4 * j + 1] = v.y;
+            if (4 * j + 2 < W) val[i][4 * j + 2] = v.z;
+            if (4 * j + 3 < W) val[i][4 * j + 3] = v.w;
+        }
+}
+
+// Halo of the window, filled by all wavefronts but the first (which polls):
+// fetch() reads the entries' places (during an exchange, whose wait hides it),
+// fill() the entries themselves after it.  Lists are padded to whole passes.
+struct Halo {
+    unsigned at[HR];   // byte offsets (one register each beside the uniform base)
+    template <class T>
+    __device__ __forceinline__ void fetch(const unsigned *idx, int passes)
+    {
+        if (threadIdx.x < SLICE) return;
+        const unsigned h = threadIdx.x - SLICE;
+#pragma unroll
+        for (int k = 0; k < HR; ++k)
+            if (k < passes) at[k] = (idx + k * HT)[h] * (unsigned)sizeof(T);
+    }
+    template <class T>
+    __device__ __forceinline__ void fill(const T *zb, T *win, int passes) const
+    {
+        if (threadIdx.x >= SLICE) {
+            const unsigned h = threadIdx.x - SLICE;
+            T v[HR];
+#pragma unroll
+            for (int k = 0; k < HR; ++k)
+                if (k < passes)
+                    v[k] = ld_agent(reinterpret_cast<const T *>(reinterpret_cast<const char *>(zb) + at[k]));
+#pragma unroll
+            for (int k = 0; k < HR; ++k)
+                if (k < passes) win[k * HT + h] = v[k];
+        }
+        __syncthreads();
+    }
+};
+
+// ---- plain FP64 ------------------------------------------------------------
+template <int W, int R>
+__global__ __launch_bounds__(OB) void k_onchip(OnchipSolve a)
+{
+    constexpr int LQ = (W + 3) / 4, own = R * OB;
+    __shared__ ExchangeLds xl;
+    __shared__ uint2 lcol[R * LQ][OB];
+    __shared__ double win[own + kOnchipHalo];
+    __shared__ double ldv[R][OB];
+    const int G = gridDim.x, g = logical_group(G);
+    int t = threadIdx.x;
+    unsigned at0 = (unsigned)g * own + t;   // block position of pass i: at0 + i * OB
+    double *zb = static_cast<double *>(a.zb);
+    Partials parts;
+    parts.load(a);
+    const int h0 = a.map.halo_ptr[g], nh = (a.map.halo_ptr[g + 1] - h0) / HT;   // its passes
+    double val[R][W], r[R], p[R], q[R], x[R];
+    Rows<W, R, LQ> rows;
+    rows.load(a, g, lcol);
+    asm volatile("" ::: "memory");   // the columns' registers are free again
+    load_values<W, R>(a.map.val64 + (size_t)g * own * (W + 1), val);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int row = a.map.row[at0 + i * OB], at = max(row, 0);
+        const double ri = a.r[at], xi = a.x[at], zi = a.z[at];
+        r[i] = row < 0 ? 0.0 : ri;
+        x[i] = row < 0 ? 0.0 : xi;
+        p[i] = q[i] = 0.0;
+        win[i * OB + t] = row < 0 ? 0.0 : zi;
+        ldv[i][t] = a.map.dinv64[at0 + i * OB];
+    }
+    for (int h = t; h < nh * HT; h += OB) win[own + h] = a.z[a.map.halo_row[h0 + h]];
+    const Start st = start_of(a, parts, xl);
+    Outcome o{st.rho, st.z0, 0, 1, st.finite ? 0 : 2, 0};
+    int turn = a.turn;
+    if (st.done) {
+        report(a, st, o, turn);
+        return;
+    }
+    __syncthreads();
+    const StopTest test = {a.sc->atol, a.sc->rtol, st.ref, st.floor_};
+    double rho = st.rho, beta = 0.0;
+    int it = 0;
+    o.done = 0;
+    for (;;) {
+        // addresses and columns are formed anew in each iteration: kept across
+        // iterations they would take more registers than the vectors
+        asm volatile("" : "+v"(at0), "+v"(t));
+        double pq[1] = {0.0};
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            q[i] = rows.template product<double>(val, lcol, i, t, win) + beta * q[i];
+            formed(q[i]);
+            p[i] = win[i * OB + t] + beta * p[i];
+            pq[0] += p[i] * q[i];
+        }
+        if (!exchange<1>(pq, xl, a, g, G, turn, nothing)) {
+            o.aborted = 1;
+            break;
+        }
+        const double alpha = rho / pq[0];
+        double v[2] = {0.0, 0.0};
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            x[i] += alpha * p[i];
+            r[i] -= alpha * q[i];
+            const double z = ldv[i][t] * r[i];
+            win[i * OB + t] = z;
+            st_agent(zb + at0 + i * OB, z);
+            v[0] += r[i] * z;
+            v[1] += z * z;
+        }
+        Halo halo;
+        if (!exchange<2>(v, xl, a, g, G, turn, [&] { halo.fetch<double>(a.map.halo_at + h0, nh); })) {
+            o.aborted = 1;
+            break;
+        }
+        ++it;
+        const double zn = sqrt(v[1]);
+        o.znorm = zn;
+        if (!isfinite(zn)) {
+            o.nonfinite = 2;
+            o.done = 1;
+            break;
+        }
+        if (passes(test, zn)) {
+            o.done = 1;
+            break;
+        }
+        if (it >= a.max_iter) break;   // cap: the host reports no convergence
+        beta = v[0] / rho;
+        rho = v[0];
+        halo.fill(zb, win + own, nh);
+    }
+    o.it = it;
+    o.rho = rho;
+    if (!o.aborted)
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const int row = a.map.row[at0 + i * OB];
+            if (row >= 0) a.x[row] = x[i];
+        }
+    report(a, st, o, turn);
+}
+
+// ---- FP32 iteration with FP64 residual replacement ---------------------------
+// LQ: quads of columns in LDS (fewer than all where R rows' would not fit).
+// AWAY: r and the correction, which the product does not need, are kept in
+// memory by block position (they stay in the L2) and come back for the
+// update: with them the largest blocks do not fit.
+template <int W, int R, int LQ, bool AWAY>
+__global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
+{
+    constexpr int own = R * OB;
+    __shared__ ExchangeLds xl;
+    __shared__ uint2 lcol[R * LQ][OB];
+    __shared__ float win[own + kOnchipHalo];
+    __shared__ float ldv[AWAY ? 1 : R][OB];
+    const int G = gridDim.x, g = logical_group(G);
+    int t = threadIdx.x;
+    unsigned at0 = (unsigned)g * own + t;
+    float *zb = static_cast<float *>(a.zb);
+    Partials parts;
+    parts.load(a);
+    Start st;
+    if constexpr (AWAY) st = start_of(a, parts, xl);   // no registers to wait with
+    const int h0 = a.map.halo_ptr[g], nh = (a.map.halo_ptr[g + 1] - h0) / HT;   // its passes
+    float val[R][W], p[R], q[R], r[R], d[R];
+    Rows<W, R, LQ> rows;
+    rows.load(a, g, lcol);
+    asm volatile("" ::: "memory");   // the columns' registers are free again
+    if constexpr (!AWAY) load_values<W, R>(a.map.val32 + (size_t)g * own * (W + 1), val);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int row = a.map.row[at0 + i * OB], at = max(row, 0);
+        const float ri = a.r32[at], zi = a.z32[at];
+        r[i] = row < 0 ? 0.0f : ri;
+        p[i] = q[i] = d[i] = 0.0f;
+        win[i * OB + t] = row < 0 ? 0.0f : zi;
+        if constexpr (AWAY) {
+            a.map.r_away[at0 + i * OB] = r[i];
+            a.map.d_away[at0 + i * OB] = 0.0f;
+        } else {
+            ldv[i][t] = a.map.dinv32[at0 + i * OB];
+        }
+    }
+    for (int h = t; h < nh * HT; h += OB) win[own + h] = a.z32[a.map.halo_row[h0 + h]];
+    if constexpr (AWAY) {
+        asm volatile("" ::: "memory");
+        load_values<W, R>(a.map.val32 + (size_t)g * own * (W + 1), val);
+    } else {
+        st = start_of(a, parts, xl);
+    }
+    Outcome o{st.rho, st.z0, 0, 1, st.finite ? 0 : 2, 0};
+    int turn = a.turn;
+    if (st.done) {
+        report(a, st, o, turn);
+        return;
+    }
+    __syncthreads();
+    const StopTest test = {a.sc->atol, a.sc->rtol, st.ref, st.floor_};
+    double rho = st.rho, beta = 0.0;
+    int it = 0;
+    o.done = 0;
+    for (;;) {
+        asm volatile("" : "+v"(at0), "+v"(t));   // as in k_onchip
+        const float bf = (float)beta;
+        double pq[1] = {0.0};
+        float dv[R];
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            q[i] = rows.template product<float>(val, lcol, i, t, win) + bf * q[i];
+            formed(q[i]);
+            p[i] = win[i * OB + t] + bf * p[i];
+            pq[0] += (double)p[i] * (double)q[i];
+        }
+        if (!exchange<1>(pq, xl, a, g, G, turn, nothing)) {
+            o.aborted = 1;
+            break;
+        }
+        const float alpha = (float)(rho / pq[0]);
+        double v[2] = {0.0, 0.0};
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+            if constexpr (AWAY) {
+                dv[i] = a.map.dinv32[at0 + i * OB];
+                r[i] = a.map.r_away[at0 + i * OB];
+                d[i] = a.map.d_away[at0 + i * OB];
+            }
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            d[i] += alpha * p[i];
+            r[i] -= alpha * q[i];
+            if constexpr (AWAY) {
+                a.map.d_away[at0 + i * OB] = d[i];
+                a.map.r_away[at0 + i * OB] = r[i];
+            }
+            const float z = (AWAY ? dv[i] : ldv[AWAY ? 0 : i][t]) * r[i];
+            win[i * OB + t] = z;
+            st_agent(zb + at0 + i * OB, z);
+            v[0] += (double)r[i] * (double)z;
+            v[1] += (double)z * (double)z;
+        }
+        Halo halo;
+        if (!exchange<2>(v, xl, a, g, G, turn, [&] { halo.fetch<float>(a.map.halo_at + h0, nh); })) {
+            o.aborted = 1;
+            break;
+        }
+        ++it;
+        double zn = sqrt(v[1]);
+        o.znorm = zn;
+        if (!isfinite(zn)) {
+            o.nonfinite = 2;
+            o.done = 1;
+            break;
+        }
+        const bool pass = passes(test, zn);
+        if (!pass && !(a.rr > 0 && it % a.rr == 0) && it < a.max_iter) {
+            beta = v[0] / rho;
+            rho = v[0];
+            halo.fill(zb, win + own, nh);
+            continue;
+        }
+        // ---- replacement: r64 -= A delta, x64 += delta, the test on r64 ----
+        // (zb is overwritten: no workgroup reads z from it at this exchange)
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const float di = AWAY ? a.map.d_away[at0 + i * OB] : d[i];
+            win[i * OB + t] = di;
+            st_agent(zb + at0 + i * OB, di);
+        }
+        double none[1] = {0.0};
+        if (!exchange<1>(none, xl, a, g, G, turn, nothing)) {
+            o.aborted = 1;
+            break;
+        }
+        halo.fill(zb, win + own, nh);
+        v[0] = v[1] = 0.0;
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const int row = a.map.row[at0 + i * OB];
+            double ad = rows.template product<double>(val, lcol, i, t, win);
+            formed(ad);
+            float ri = 0.0f;
+            if (row >= 0) {
+                const double r64 = a.r[row] - ad;
+                a.r[row] = r64;
+                a.x[row] += (double)win[i * OB + t];
+                ri = (float)r64;
+                const double zi = a.dinv[row] * r64;
+                v[1] += zi * zi;
+            }
+            v[0] += (double)ri * (double)(a.map.dinv32[at0 + i * OB] * ri);
+            if constexpr (AWAY) {
+                a.map.r_away[at0 + i * OB] = ri;
+                a.map.d_away[at0 + i * OB] = 0.0f;
+            } else {
+                r[i] = ri;
+                d[i] = 0.0f;
+            }
+        }
+        if (!exchange<2>(v, xl, a, g, G, turn, nothing)) {
+            o.aborted = 1;
+            break;
+        }
+        zn = sqrt(v[1]);
+        o.znorm = zn;
+        if (!isfinite(zn)) {
+            o.nonfinite = 2;
+            o.done = 1;
+            break;
+        }
+        if (passes(test, zn)) {
+            o.done = 1;
+            break;
+        }
+        if (it >= a.max_iter) break;
+        // restart (p = z) where the recursive residual had passed, the
+        // recurrence kept after a periodic replacement
+        beta = pass ? 0.0 : v[0] / rho;
+        rho = v[0];
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const float ri = AWAY ? a.map.r_away[at0 + i * OB] : r[i];
+            const float z = a.map.dinv32[at0 + i * OB] * ri;
+            win[i * OB + t] = z;
+            st_agent(zb + at0 + i * OB, z);
+        }
+        if (!exchange<1>(none, xl, a, g, G, turn, nothing)) {
+            o.aborted = 1;
+            break;
+        }
+        halo.fill(zb, win + own, nh);
+    }
+    o.it = it;
+    o.rho = rho;
+    report(a, st, o, turn);
+}
+
+// values and diagonals of the blocks' rows from the sliced layout
+template <class T, class V>
+__global__ __launch_bounds__(256) void k_onchip_values(int64_t n, int rows, int width, OnchipMap m,
+                                                       const int64_t *__restrict__ slice_ptr,
+                                                       const V *__restrict__ A,
+                                                       const V *__restrict__ dinv,
+                                                       T *__restrict__ val, T *__restrict__ dv)
+{
+    const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;   // block position
+    if (at >= n) return;
+    const int64_t pass = at / OB;   // g * rows + i
+    const int t = (int)(at % OB);
+    constexpr int L = 16 / sizeof(T);   // entries of a 16-byte load
+    const int row = m.row[at];
+    int w = 0;
+    int64_t b0 = 0;
+    if (row >= 0) {
+        const int64_t sl = row / SLICE;
+        b0 = slice_ptr[sl] + row % SLICE;
+        w = (int)((slice_ptr[sl + 1] - slice_ptr[sl]) / SLICE);
+    }
+    for (int j = 0; j <= width; ++j)
+        val[(pass * ((width + 1) / L) + j / L) * (OB * L) + t * L + j % L] =
+            j < w ? (T)A[b0 + (int64_t)j * SLICE] : T(0);
+    dv[at] = row >= 0 ? (T)dinv[row] : T(0);
+}
+
+struct OnchipShape {
+    int width, rows;   // entries of a row, rows per thread
+    void (*k)(OnchipSolve);
+};
+#define MDX_OC(w, r) {w, r, k_onchip<w, r>}
+const OnchipShape kShapes64[] = {
+    MDX_OC(7, 1),  MDX_OC(7, 2),  MDX_OC(7, 3),  MDX_OC(7, 4),  MDX_OC(7, 6),  MDX_OC(15, 1),
+    MDX_OC(15, 2), MDX_OC(15, 3), MDX_OC(15, 4), MDX_OC(31, 1), MDX_OC(31, 2),
+};
+#undef MDX_OC
+#define MDX_OC(w, r) {w, r, k_onchip32<w, r, (w + 3) / 4, false>}
+const OnchipShape kShapes32[] = {
+    MDX_OC(7, 1),  MDX_OC(7, 2),  MDX_OC(7, 3),  MDX_OC(7, 4),  MDX_OC(7, 6),  MDX_OC(7, 7),
+    MDX_OC(7, 8),  MDX_OC(7, 10), MDX_OC(7, 12), MDX_OC(15, 1), MDX_OC(15, 2), MDX_OC(15, 3),
+    MDX_OC(15, 4), MDX_OC(15, 6), MDX_OC(15, 7), {15, 8, k_onchip32<15, 8, 3, true>},
+    {15, 10, k_onchip32<15, 10, 3, true>}, MDX_OC(31, 1), MDX_OC(31, 2), MDX_OC(31, 3), MDX_OC(31, 4),
+};
+#undef MDX_OC
+constexpr int kRows[] = {1, 2, 3, 4, 6, 7, 8, 10, 12};
+
+template <int N>
+const OnchipShape *pick(const OnchipShape (&s)[N], int width, int rows)
+{
+    for (const OnchipShape &c : s)
+        if (width == c.width && rows == c.rows) return &c;
+    return nullptr;
+}
+
+}  // namespace
+
+OnchipPlan onchip_plan(int device, int64_t n, int width)
+{
+    OnchipPlan p;
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
+        return p;
+    const int64_t cap = std::min(cus, kOnchipGroups);
+    if (cap < 1 || n < 1) return p;
+    p.width = width <= 7 ? 7 : width <= 15 ? 15 : 31;
+    if (width > 31) return p;
+    const int64_t need = (n + cap * OB - 1) / (cap * OB);
+    for (int r : kRows)
+        if (r >= need) {
+            p.rows = r;
+            break;
+        }
+    if (p.rows == 0) return p;
+    const OnchipShape *s[2] = {pick(kShapes64, p.width, p.rows), pick(kShapes32, p.width, p.rows)};
+    for (int i = 0; i < 2; ++i) {
+        int resident = 0;
+        if (s[i] && hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, s[i]->k, OB, 0) == hipSuccess &&
+            resident >= 1)
+            p.shape[i] = s[i];
+    }
+    if (p.shape[0] || p.shape[1]) p.groups = (int)std::min(cap, (n + OB - 1) / OB);
+    return p;
+}
+
+void launch_onchip_values(hipStream_t s, const OnchipPlan &p, const OnchipMap &m,
+                          const int64_t *slice_ptr, const double *A, const double *dinv,
+                          const float *A32, const float *dinv32)
+{
+    const int64_t n = (int64_t)p.groups * p.rows * OB;
+    const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+    if (p.shape[0])
+        hipLaunchKernelGGL((k_onchip_values<double, double>), grid, block, 0, s, n, p.rows, p.width, m,
+                           slice_ptr, A, dinv, m.val64, m.dinv64);
+    if (p.shape[1])
+        hipLaunchKernelGGL((k_onchip_values<float, float>), grid, block, 0, s, n, p.rows, p.width, m,
+                           slice_ptr, A32, dinv32, m.val32, m.dinv32);
+}
+
+void launch_onchip(hipStream_t s, const OnchipPlan &p, bool fp32, const OnchipSolve &a)
+{
+    const OnchipShape *sh = static_cast<const OnchipShape *>(p.shape[fp32 ? 1 : 0]);
+    hipLaunchKernelGGL(sh->k, dim3(p.groups), dim3(OB), 0, s, a);
+}
+
+}  // namespace mdx

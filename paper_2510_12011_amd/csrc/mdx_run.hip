@@ -10,6 +10,20 @@
 // instruction.
 #include "mdx_host.h"
 
+#include <mutex>
+
+namespace {
+
+// One single-launch solve per device at a time: two whose workgroups share the
+// CUs would each wait for workgroups that the other keeps off the chip.
+std::mutex &onchip_mutex(int device)
+{
+    static std::mutex m[64];
+    return m[device & 63];
+}
+
+}  // namespace
+
 extern "C" {
 
 mdx_status mdx_run(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double *v_out)
@@ -78,6 +92,37 @@ mdx_status mdx_run(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double *v_o
             launch_ionic_step(st, ctx->ionic_kind, ctx->ionic_params.data(), ctx->n, ctx->npad,
                               ctx->dt, ctx->cm, Vk, u, istim_k, s, 0, nullptr, guard, times);
     };
+    // The solve as one launch where the matrix fits on chip.  The launch-shape
+    // tunings and the two-kernel scheme choose among the streaming kernels and
+    // so select them; so does a step whose SpMV launches are timed.
+    const bool onchip_run = ctx->onchip_ready && ctx->onchip.shape[mixed ? 1 : 0] &&
+                            ctx->onchip_polls > 0 && ctx->iter_scheme == 0 &&
+                            ctx->max_groups == kMaxGroups && ctx->spmv_max_groups == kPartialCap;
+    OnchipSolve os{};
+    os.map = ctx->onchip_map;
+    os.z = pbuf[1];
+    os.r = r;
+    os.dinv = dinv;
+    os.r32 = r32;
+    os.z32 = z32;
+    os.zb = ctx->dev<double>(L.oc_z);
+    os.part = part0;
+    os.part_groups = learned ? 0 : T.groups;
+    os.rel_mode = sp.rel_mode;
+    os.max_iter = max_iter;
+    os.rr = ctx->opts.rr_interval;
+    os.polls = ctx->onchip_polls;
+    os.words = ctx->dev<unsigned long long>(L.words);
+    os.sc = sc;
+    os.pub = ctx->pub_dev;
+    // a launch that gave up after it had been taken for done (its first
+    // workgroup saw every sum that another did not)
+    auto late_abort = [&]() -> mdx_status {
+        if (ctx->sc_host->onchip_abort == ctx->onchip_seen) return MDX_OK;
+        ctx->onchip_seen = ctx->sc_host->onchip_abort;
+        ctx->onchip_off = true;
+        return fail(ctx, MDX_ERR_DEVICE, "a single-launch solve was interrupted");
+    };
     bool ionic_queued = false;   // this step's ionic update was queued by the previous step
 
     for (int64_t j = 0; j < n_steps; ++j) {
@@ -93,47 +138,52 @@ mdx_status mdx_run(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double *v_o
         ionic_queued = false;
 
         // ---- right-hand side, warm start, initial residual ----
-        // (the three-kernel FP64 iteration starts from p0 = z0, written by
-        // the pass that forms r0)
-        double *p0_fp64 = mixed ? nullptr : ctx->iter_scheme == 0 ? pbuf[0] : pbuf[1];
+        bool onchip = onchip_run && !ctx->onchip_off && !ctx->profiling;
         // the learned warm start and the recorder need the neighbour feature
         // (K V^{n-1})_i / K_ii, kept up to date by the right-hand-side pass
         const bool want_kvp = learned || ctx->rec_X;
         if (want_kvp && !ctx->kvp_valid) launch_kv_feature(st, T, P, Kv, kdiag, Vprev, kvp);
+        if (ctx->rec_X)   // training-data recorder: raw features
+            launch_features(st, ctx->n, ctx->n, V, Vprev, s, kvp, ctx->cm, ctx->mlp_norm, nullptr,
+                            ctx->rec_X);
         if (learned) {
             // the network forms its features from the state (padding rows
-            // keep y = 0); the recorder also takes the raw features and y
-            if (ctx->rec_X)
-                launch_features(st, ctx->n, ctx->n, V, Vprev, s, kvp, ctx->cm, ctx->mlp_norm,
-                                nullptr, ctx->rec_X);
+            // keep y = 0); the recorder also takes y
             launch_mlp_forward_state(st, mlp_params, ctx->n, V, Vprev, s, kvp, ctx->cm,
                                      ctx->mlp_norm, mlp_y);
             if (ctx->rec_y)
                 HIPCHK(hipMemcpyAsync(ctx->rec_y, mlp_y, sizeof(float) * ctx->n,
                                       hipMemcpyDeviceToDevice, st));
-            launch_rhs_learned(st, T, P, Mv, Kv, kdiag, dinv, dinv32, sp,
-                               ctx->mlp_norm.out_scale, V, Vprev, s, mlp_y, X, r, p0_fp64,
-                               mixed ? r32 : nullptr, z32, delta, kvp, part_pq, nt_rhs);
-            launch_init_finalize_ws(st, T, part_pq, sp.rel_mode, sc);
-            // where the extrapolation's residual was the smaller, its start
-            // vectors (the scalars are already its own, from the same pass):
-            // one pass on a small grid, which returns at once, and cheaply,
-            // when the network's guess is taken
-            StepParams ex = sp;
-            ex.warm_start = MDX_WS_EXTRAP;
-            const Tiling TF = make_tiling(ctx->npad, 256);
-            const int32_t *lost = &sc->use_mlp;
-            double *part_unused = part0 + 3 * kPartialCap;   // no reader
-            if (mixed)
-                launch_rhs_init_mixed(st, TF, P, Mv, Kv, dinv, dinv32, ex, V, Vprev, s, X, r, r32,
-                                      z32, delta, part_unused, kdiag, nullptr, nt_rhs, lost);
-            else
-                launch_rhs_init(st, TF, P, Mv, Kv, dinv, ex, V, Vprev, s, X, r, part_unused,
-                                kdiag, nullptr, p0_fp64, nt_rhs, lost);
-        } else {
-            if (ctx->rec_X)   // training-data recorder: raw features
-                launch_features(st, ctx->n, ctx->n, V, Vprev, s, kvp, ctx->cm, ctx->mlp_norm,
-                                nullptr, ctx->rec_X);
+        }
+        // b, x0, r0 and the start of the iteration (the three-kernel FP64
+        // iteration starts from p0 = z0 in the direction's buffer, the
+        // two-kernel form and the single launch from z0, both written by the
+        // pass that forms r0)
+        auto queue_rhs = [&]() {
+            double *p0_fp64 = mixed ? nullptr : ctx->iter_scheme == 0 && !onchip ? pbuf[0] : pbuf[1];
+            if (learned) {
+                launch_rhs_learned(st, T, P, Mv, Kv, kdiag, dinv, dinv32, sp,
+                                   ctx->mlp_norm.out_scale, V, Vprev, s, mlp_y, X, r, p0_fp64,
+                                   mixed ? r32 : nullptr, z32, delta, kvp, part_pq, nt_rhs);
+                launch_init_finalize_ws(st, T, part_pq, sp.rel_mode, sc);
+                // where the extrapolation's residual was the smaller, its start
+                // vectors (the scalars are already its own, from the same pass):
+                // one pass on a small grid, which returns at once, and cheaply,
+                // when the network's guess is taken
+                StepParams ex = sp;
+                ex.warm_start = MDX_WS_EXTRAP;
+                const Tiling TF = make_tiling(ctx->npad, 256);
+                const int32_t *lost = &sc->use_mlp;
+                double *part_unused = part0 + 3 * kPartialCap;   // no reader
+                if (mixed)
+                    launch_rhs_init_mixed(st, TF, P, Mv, Kv, dinv, dinv32, ex, V, Vprev, s, X, r,
+                                          r32, z32, delta, part_unused, kdiag, nullptr, nt_rhs,
+                                          lost);
+                else
+                    launch_rhs_init(st, TF, P, Mv, Kv, dinv, ex, V, Vprev, s, X, r, part_unused,
+                                    kdiag, nullptr, p0_fp64, nt_rhs, lost);
+                return;
+            }
             float *kvp_out = want_kvp ? kvp : nullptr;
             if (mixed)
                 launch_rhs_init_mixed(st, T, P, Mv, Kv, dinv, dinv32, sp, V, Vprev, s, X, r, r32,
@@ -141,8 +191,9 @@ mdx_status mdx_run(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double *v_o
             else
                 launch_rhs_init(st, T, P, Mv, Kv, dinv, sp, V, Vprev, s, X, r, part0, kdiag,
                                 kvp_out, p0_fp64, nt_rhs);
-            launch_init_finalize(st, T, part0, sp.rel_mode, sc);
-        }
+            if (!onchip) launch_init_finalize(st, T, part0, sp.rel_mode, sc);
+        };
+        queue_rhs();
         ctx->kvp_valid = want_kvp;
 
         // ---- PCG ----
@@ -160,7 +211,7 @@ mdx_status mdx_run(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double *v_o
         auto end_chunk = [&]() -> mdx_status {
             const bool carry = j + 1 < n_steps;
             if (!carry) launch_epilogue(st, ctx->n, t1, V, X, lat, lrt, sc, &sc->done);
-            launch_publish(st, sc, ctx->pub_dev, ++ctx->pub_seq);
+            if (!onchip) launch_publish(st, sc, ctx->pub_dev, ++ctx->pub_seq);
             if (carry) {
                 bool any_next = false;
                 if (mdx_status e = update_stimulus(ctx, st, k + 1, any_next)) return e;
@@ -175,7 +226,28 @@ mdx_status mdx_run(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double *v_o
                 std::chrono::duration<double>(std::chrono::steady_clock::now() - w0).count();
             return MDX_OK;
         };
-        if (mixed) {
+        if (onchip) {
+            std::lock_guard<std::mutex> one(onchip_mutex(ctx->device));
+            os.x = X;
+            os.turn = ctx->onchip_turn;
+            if (++ctx->onchip_launch == 0) ctx->onchip_launch = 1;
+            os.launch = ctx->onchip_launch;
+            os.seq = ++ctx->pub_seq;   // the launch publishes the scalars itself
+            launch_onchip(st, ctx->onchip, mixed, os);
+            if (mdx_status e = end_chunk()) return e;
+            ctx->onchip_turn = ctx->sc_host->onchip_turn;
+            if (ctx->sc_host->onchip_abort == os.launch) {
+                ctx->onchip_seen = os.launch;
+                ctx->onchip_off = true;
+                onchip = false;
+                queue_rhs();
+            } else {
+                if (mdx_status e = late_abort()) return e;
+                done = ctx->sc_host->done != 0;
+            }
+        }
+        if (onchip) {
+        } else if (mixed) {
             // a chunk of iterations (each ends with its stopping test), then
             // the (conditional) residual replacement
             const int rr = ctx->opts.rr_interval;
@@ -286,6 +358,7 @@ mdx_status mdx_run(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double *v_o
     HIPCHK(hipStreamSynchronize(st));
     ctx->stats.step_loop_seconds +=
         std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();
+    if (mdx_status e = late_abort()) return e;
     if (ctx->sc_host->nonfinite || ctx->sc_host->nonfinite_v)
         return fail(ctx, MDX_ERR_NONFINITE, "non-finite V after step %lld", (long long)ctx->step);
     return result;

@@ -362,19 +362,10 @@ __global__ __launch_bounds__(256) void k_epilogue(int64_t n, double t1, const do
     if (!update_times(i, t1, Vold[i], Vnew[i], lat, lrt)) sc->nonfinite = 1;
 }
 
-// One wavefront: the scalars (whole 4-byte words) into host-visible memory,
-// a system-scope fence, then the sequence number the host waits for.
 __global__ __launch_bounds__(64) void k_publish(const Scalars *__restrict__ sc, Published *pub,
                                                 int32_t seq)
 {
-    static_assert(sizeof(Scalars) % 4 == 0, "whole words");
-    constexpr int words = (int)(sizeof(Scalars) / 4);
-    const int32_t *src = reinterpret_cast<const int32_t *>(sc);
-    int32_t *dst = reinterpret_cast<int32_t *>(&pub->s);
-    for (int w = threadIdx.x; w < words; w += 64) dst[w] = src[w];
-    __threadfence_system();
-    __syncthreads();
-    if (threadIdx.x == 0) pub->seq = seq;
+    publish_scalars(sc, pub, seq);
 }
 
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
