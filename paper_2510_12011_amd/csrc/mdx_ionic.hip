@@ -16,6 +16,7 @@
 //    (Am. J. Physiol. Heart Circ. Physiol. 291:H1088), 18 states + V;
 //  * Courtemanche-Ramirez-Nattel 1998 human atrial model (Am. J. Physiol.
 //    275:H301), 20 states + V.
+#include "mdx_cellmath.h"
 #include "mdx_device.h"
 #include "mdx_internal.h"
 
@@ -32,12 +33,6 @@ struct IonicParams {
     double v[16];
 };
 
-// exponential in the gate precision
-__device__ __forceinline__ double ex(double x) { return exp(x); }
-__device__ __forceinline__ float ex(float x) { return expf(x); }
-__device__ __forceinline__ double sqr_root(double x) { return sqrt(x); }
-__device__ __forceinline__ float sqr_root(float x) { return sqrtf(x); }
-
 // Rush-Larsen step y <- y_inf + (y - y_inf) exp(-dt/tau).  In FP32 it is
 // evaluated as y + (y_inf - y) (1 - exp(-dt/tau)) with expm1: exp(-dt/tau)
 // is within 1e-4 of 1, and rounding it to FP32 would misstate the decay
@@ -51,10 +46,6 @@ __device__ __forceinline__ float rush_larsen(float y, float y_inf, float tau, fl
     return y - (y_inf - y) * expm1f(-dt / tau);
 }
 // the same step given the rate 1/tau
-__device__ __forceinline__ double rush_larsen_rate(double y, double y_inf, double rate, double dt)
-{
-    return y_inf - (y_inf - y) * exp(-dt * rate);
-}
 __device__ __forceinline__ float rush_larsen_rate(float y, float y_inf, float rate, float dt)
 {
     return y - (y_inf - y) * expm1f(-dt * rate);
@@ -104,27 +95,38 @@ __constant__ double TT_U0[TT_NS] = {136.89,   8.604,    0.000126, 3.64,   0.0003
                                     0.00621,  0.4712,   0.0095,   0.00172, 0.7444, 0.7045,
                                     3.373e-5, 0.7888,   0.9755,   0.9953, 0.999998, 2.42e-8};
 
+__device__ __forceinline__ double sq(double x) { return x * x; }
+
 // factors of the currents that depend on V only
 struct VOnly {
     double ical_drive;   // 2F * w/expm1(w) with w = 2(V-15)F/RT
-    double ical_ew;      // exp(w)
-    double nak_den;      // 1 + 0.1245 e^{-0.1 VF/RT} + 0.0353 e^{-VF/RT}
-    double ncx_up, ncx_down, ncx_sat;   // e^{g VF/RT}, e^{(g-1) VF/RT}, 1 + ksat e^{(g-1)VF/RT}
-    double ipk;          // 1 / (1 + exp((25 - V)/5.98))
+    double ical_ew;      // exp(w) / 4
+    double nak;          // pNaK K_o/(K_o + K_mK) / (1 + 0.1245 e^{-0.1 VF/RT} + 0.0353 e^{-VF/RT})
+    double ncx_up, ncx_down;   // iNaCa = ncx_up Nai^3 - ncx_down Cai
+    double ipk;          // gpK / (1 + exp((25 - V)/5.98))
 };
 
-__device__ __forceinline__ VOnly v_only(double V)
+__device__ __forceinline__ VOnly v_only(const cell::Coef &C, const IonicParams &P, double V)
 {
+    using namespace cell;
     VOnly o;
-    double w = (V - 15.0) * (2.0 / RTONF);
-    o.ical_ew = exp(w);
-    o.ical_drive = 2.0 * Far * (w == 0.0 ? 1.0 : w / expm1(w));
-    double phi = V * (1.0 / RTONF);
-    o.nak_den = 1.0 + 0.1245 * exp(-0.1 * phi) + 0.0353 * exp(-phi);
-    o.ncx_up = exp(NCX_GAMMA * phi);
-    o.ncx_down = exp((NCX_GAMMA - 1.0) * phi);
-    o.ncx_sat = 1.0 + K_SAT * o.ncx_down;
-    o.ipk = 1.0 / (1.0 + exp((25.0 - V) * (1.0 / 5.98)));
+    V = clip(V, 1.5e4);   // every exponential below stays in range
+    const double phi = V * (1.0 / RTONF);
+    const double e1 = exp_(C, -phi), up = exp_(C, NCX_GAMMA * phi), down = up * e1;
+    constexpr double nao3 = NA_O * NA_O * NA_O;
+    constexpr double ncx_den = (KM_NAI * KM_NAI * KM_NAI + nao3) * (KM_CA + CA_O);
+    // the pump's and the exchanger's denominators, and 1 + exp((25 - V)/5.98)
+    const double rn = rcp(1.0 + 0.1245 * exp_(C, -0.1 * phi) + 0.0353 * e1);
+    const double rx = rcp(ncx_den * (1.0 + K_SAT * down));
+    o.nak = P.v[10] * (K_O / (K_O + KM_K)) * rn;
+    o.ncx_up = P.v[11] * CA_O * (rx * up);
+    o.ncx_down = P.v[11] * (nao3 * NCX_ALPHA) * (rx * down);
+    const double w = clip((V - 15.0) * (2.0 / RTONF), 700.0);
+    double ew, em1;
+    exp_expm1(C, w, ew, em1);
+    o.ical_drive = w == 0.0 ? 2.0 * Far : 2.0 * Far * (w * rcp(em1));
+    o.ical_ew = 0.25 * ew;
+    o.ipk = P.v[9] * rcp(1.0 + exp_(C, (25.0 - clip(V, 2400.0)) * (1.0 / 5.98)));
     return o;
 }
 
@@ -149,52 +151,53 @@ struct Currents {
 
 // currents at V and the concentration-type states c[0..5] (Ki Nai Cai CaSR
 // CaSS Rbar) and gates summarised by gp
-__device__ __forceinline__ Currents tt_currents(const IonicParams &P, double V, const VOnly &vo,
-                                                const double *c, const GateProducts &gp)
+__device__ __forceinline__ Currents tt_currents(const cell::Coef &C, const IonicParams &P, double V,
+                                                const VOnly &vo, const double *c,
+                                                const GateProducts &gp)
 {
+    using namespace cell;
     const double gNa = P.v[0], gK1 = P.v[1], gto = P.v[2], gKr = P.v[3], gKs = P.v[4];
-    const double gCaL = P.v[5], gbNa = P.v[6], gbCa = P.v[7], gpCa = P.v[8], gpK = P.v[9];
-    const double pNaK = P.v[10], kNaCa = P.v[11];
+    const double gCaL = P.v[5], gbNa = P.v[6], gbCa = P.v[7], gpCa = P.v[8];
     const double ki = c[KI], nai = c[NAI], cai = c[CAI];
-    const double e_k = RTONF * log(K_O / ki);
-    const double e_na = RTONF * log(NA_O / nai);
-    const double e_ks = RTONF * log((K_O + P_KNA * NA_O) / (ki + P_KNA * nai));
-    const double e_ca = 0.5 * RTONF * log(CA_O / cai);
+    const double e_k = RTONF * log_ratio(C, 1.6863989535702286, 7.914947588915769e-17, ki);
+    const double e_na = RTONF * log_ratio(C, 4.941642422609304, 4.344622201918654e-16, nai);
+    const double e_ks = RTONF * log_ratio(C, 2.2617630984737906, -9.075191670702233e-17, ki + P_KNA * nai);
+    const double e_ca = 0.5 * RTONF * log_ratio(C, 0.6931471805599453, 2.3190468138462996e-17, cai);
     const double ko_scale = sqrt(K_O / 5.4);
     Currents cu;
     // inward rectifier: steady-state rectification a/(a+b) with
-    // a = 0.1/(1+e1), b = q/(1+e2), formed as 0.1(1+e2) / (0.1(1+e2) + q(1+e1))
-    const double a_k1 = 0.1 * (1.0 + exp(-0.5 * (V - e_k)));
-    const double b_k1 = (3.0 * exp(0.0002 * (V - e_k + 100.0)) + exp(0.1 * (V - e_k - 10.0)))
-                      * (1.0 + exp(0.06 * (V - e_k - 200.0)));
-    cu.iK1 = gK1 * ko_scale * (a_k1 / (a_k1 + b_k1)) * (V - e_k);
+    // a = 0.1/(1+e1), b = q/(1+e2) and y = V - E_K: e1 = e^{0.06 y - 12},
+    // e2 = e^{-0.5 y} = 1/T^5 with T = e^{0.1 y}; both denominators and T^5
+    // cleared: 0.1 (1 + T^5) / (0.1 (1 + T^5) + T^5 q (1 + e1)).  Beyond
+    // +-1000 mV the factor has saturated.
+    const double y = clip(V - e_k, 1000.0);
+    const double T = exp_(C, 0.1 * y), T2 = T * T, T5 = T2 * T2 * T;
+    const double a_k1 = __builtin_fma(0.1, T5, 0.1);
+    const double b_k1 = T5 * (3.0 * exp_(C, 0.0002 * (y + 100.0)) + 0.36787944117144233 * T)
+                      * __builtin_fma(6.14421235332821e-06, exp_(C, 0.06 * y), 1.0);
+    cu.iK1 = gK1 * ko_scale * (a_k1 * rcp(a_k1 + b_k1)) * (V - e_k);
     cu.ito = gto * gp.to * (V - e_k);
     cu.iKr = gKr * ko_scale * gp.kr * (V - e_k);
     cu.iKs = gKs * gp.ks * (V - e_ks);
     cu.iNa = gNa * gp.na * (V - e_na);
     cu.ibNa = gbNa * (V - e_na);
-    cu.iCaL = gCaL * gp.cal * vo.ical_drive * (0.25 * c[CASS] * vo.ical_ew - CA_O);
+    cu.iCaL = gCaL * gp.cal * vo.ical_drive * (c[CASS] * vo.ical_ew - CA_O);
     cu.ibCa = gbCa * (V - e_ca);
-    cu.iNaK = pNaK * (K_O / (K_O + KM_K)) * nai / ((nai + KM_NA) * vo.nak_den);
-    constexpr double nao3 = NA_O * NA_O * NA_O;
-    constexpr double ncx_den = (KM_NAI * KM_NAI * KM_NAI + nao3) * (KM_CA + CA_O);
-    cu.iNaCa = kNaCa * (vo.ncx_up * nai * nai * nai * CA_O - vo.ncx_down * nao3 * cai * NCX_ALPHA)
-             / (ncx_den * vo.ncx_sat);
-    cu.ipCa = gpCa * cai / (K_PCA + cai);
-    cu.ipK = gpK * vo.ipk * (V - e_k);
+    cu.iNaK = vo.nak * (nai * rcp(nai + KM_NA));
+    cu.iNaCa = vo.ncx_up * (nai * nai * nai) - vo.ncx_down * cai;
+    cu.ipCa = gpCa * (cai * rcp(K_PCA + cai));
+    cu.ipK = vo.ipk * (V - e_k);
     return cu;
 }
 
-__device__ __forceinline__ double sq(double x) { return x * x; }
-
-// Gating variables of the model advanced by Rush-Larsen at V^k, in precision
-// T, streamed one at a time: gate s (xr1 xr2 xs m h j d f f2 fCass s r) is
+// Gating variables of the model advanced by Rush-Larsen at V^k in FP32,
+// streamed one at a time: gate s (xr1 xr2 xs m h j d f f2 fCass s r) is
 // read from g[s * ld], advanced and written back at once.  po and pn receive
 // the gate products before and after the step; cass is CaSS^k.
-template <typename T>
-__device__ __forceinline__ void tt_gates(T V, T dt, T cass, T *__restrict__ g, int64_t ld,
-                                         GateProducts &po, GateProducts &pn)
+__device__ __forceinline__ void tt_gates32(float V, float dt, float cass, float *__restrict__ g,
+                                           int64_t ld, GateProducts &po, GateProducts &pn)
 {
+    using T = float;
     const T one = T(1);
     auto sqt = [](T x) { return x * x; };
     // advance gate s towards y_inf with time constant tau; old value to y0
@@ -216,22 +219,22 @@ __device__ __forceinline__ void tt_gates(T V, T dt, T cass, T *__restrict__ g, i
 
     // rapid delayed rectifier xr1, xr2
     {
-        T inf = one / (one + ex((T(-26.0) - V) * T(1.0 / 7.0)));
+        T inf = one / (one + expf((T(-26.0) - V) * T(1.0 / 7.0)));
         // 450/(1+a) * 6/(1+b) with one division
-        T tau = T(450.0 * 6.0) / ((one + ex((T(-45.0) - V) * T(1.0 / 10.0))) * (one + ex((V + T(30.0)) * T(1.0 / 11.5))));
+        T tau = T(450.0 * 6.0) / ((one + expf((T(-45.0) - V) * T(1.0 / 10.0))) * (one + expf((V + T(30.0)) * T(1.0 / 11.5))));
         n0 = adv(0, inf, tau, o0);
     }
     {
-        T inf = one / (one + ex((V + T(88.0)) * T(1.0 / 24.0)));
-        T tau = T(3.0 * 1.12) / ((one + ex((T(-60.0) - V) * T(1.0 / 20.0))) * (one + ex((V - T(60.0)) * T(1.0 / 20.0))));
+        T inf = one / (one + expf((V + T(88.0)) * T(1.0 / 24.0)));
+        T tau = T(3.0 * 1.12) / ((one + expf((T(-60.0) - V) * T(1.0 / 20.0))) * (one + expf((V - T(60.0)) * T(1.0 / 20.0))));
         n1 = adv(1, inf, tau, o1);
     }
     po.kr = o0 * o1;
     pn.kr = n0 * n1;
     // slow delayed rectifier xs
     {
-        T inf = one / (one + ex((T(-5.0) - V) * T(1.0 / 14.0)));
-        T tau = T(1400.0) / (sqr_root(one + ex((T(5.0) - V) * T(1.0 / 6.0))) * (one + ex((V - T(35.0)) * T(1.0 / 15.0))))
+        T inf = one / (one + expf((T(-5.0) - V) * T(1.0 / 14.0)));
+        T tau = T(1400.0) / (sqrtf(one + expf((T(5.0) - V) * T(1.0 / 6.0))) * (one + expf((V - T(35.0)) * T(1.0 / 15.0))))
               + T(80.0);
         n0 = adv(2, inf, tau, o0);
     }
@@ -239,25 +242,25 @@ __device__ __forceinline__ void tt_gates(T V, T dt, T cass, T *__restrict__ g, i
     pn.ks = n0 * n0;
     // fast sodium m, h, j
     {
-        T inf = one / sqt(one + ex((T(-56.86) - V) * T(1.0 / 9.03)));
-        T tau = (one / (one + ex((T(-60.0) - V) * T(1.0 / 5.0))))
-              * (T(0.1) / (one + ex((V + T(35.0)) * T(1.0 / 5.0))) + T(0.1) / (one + ex((V - T(50.0)) * T(1.0 / 200.0))));
+        T inf = one / sqt(one + expf((T(-56.86) - V) * T(1.0 / 9.03)));
+        T tau = (one / (one + expf((T(-60.0) - V) * T(1.0 / 5.0))))
+              * (T(0.1) / (one + expf((V + T(35.0)) * T(1.0 / 5.0))) + T(0.1) / (one + expf((V - T(50.0)) * T(1.0 / 200.0))));
         n0 = adv(3, inf, tau, o0);
     }
     {
-        T h_inf = one / sqt(one + ex((V + T(71.55)) * T(1.0 / 7.43)));
+        T h_inf = one / sqt(one + expf((V + T(71.55)) * T(1.0 / 7.43)));
         T alpha_h, beta_h, alpha_j, beta_j;
         if (V < T(-40.0)) {
-            alpha_h = T(0.057) * ex(-(V + T(80.0)) * T(1.0 / 6.8));
-            beta_h = T(2.7) * ex(T(0.079) * V) + T(3.1e5) * ex(T(0.3485) * V);
-            alpha_j = (T(-25428.0) * ex(T(0.2444) * V) - T(6.948e-6) * ex(T(-0.04391) * V)) * (V + T(37.78))
-                    / (one + ex(T(0.311) * (V + T(79.23))));
-            beta_j = T(0.02424) * ex(T(-0.01052) * V) / (one + ex(T(-0.1378) * (V + T(40.14))));
+            alpha_h = T(0.057) * expf(-(V + T(80.0)) * T(1.0 / 6.8));
+            beta_h = T(2.7) * expf(T(0.079) * V) + T(3.1e5) * expf(T(0.3485) * V);
+            alpha_j = (T(-25428.0) * expf(T(0.2444) * V) - T(6.948e-6) * expf(T(-0.04391) * V)) * (V + T(37.78))
+                    / (one + expf(T(0.311) * (V + T(79.23))));
+            beta_j = T(0.02424) * expf(T(-0.01052) * V) / (one + expf(T(-0.1378) * (V + T(40.14))));
         } else {
             alpha_h = T(0.0);
-            beta_h = T(0.77 / 0.13) / (one + ex(-(V + T(10.66)) * T(1.0 / 11.1)));
+            beta_h = T(0.77 / 0.13) / (one + expf(-(V + T(10.66)) * T(1.0 / 11.1)));
             alpha_j = T(0.0);
-            beta_j = T(0.6) * ex(T(0.057) * V) / (one + ex(T(-0.1) * (V + T(32.0))));
+            beta_j = T(0.6) * expf(T(0.057) * V) / (one + expf(T(-0.1) * (V + T(32.0))));
         }
         n1 = adv_rate(4, h_inf, alpha_h + beta_h, o1);
         n2 = adv_rate(5, h_inf, alpha_j + beta_j, o2);
@@ -266,23 +269,23 @@ __device__ __forceinline__ void tt_gates(T V, T dt, T cass, T *__restrict__ g, i
     pn.na = n0 * n0 * n0 * n1 * n2;
     // L-type calcium d, f, f2, fCass
     {
-        T inf = one / (one + ex((T(-8.0) - V) * T(1.0 / 7.5)));
-        T tau = (T(1.4) / (one + ex((T(-35.0) - V) * T(1.0 / 13.0))) + T(0.25)) * (T(1.4) / (one + ex((V + T(5.0)) * T(1.0 / 5.0))))
-              + one / (one + ex((T(50.0) - V) * T(1.0 / 20.0)));
+        T inf = one / (one + expf((T(-8.0) - V) * T(1.0 / 7.5)));
+        T tau = (T(1.4) / (one + expf((T(-35.0) - V) * T(1.0 / 13.0))) + T(0.25)) * (T(1.4) / (one + expf((V + T(5.0)) * T(1.0 / 5.0))))
+              + one / (one + expf((T(50.0) - V) * T(1.0 / 20.0)));
         n0 = adv(6, inf, tau, o0);
     }
     {
-        T inf = one / (one + ex((V + T(20.0)) * T(1.0 / 7.0)));
-        T tau = T(1102.5) * ex(-sqt(V + T(27.0)) * T(1.0 / 225.0)) + T(200.0) / (one + ex((T(13.0) - V) * T(1.0 / 10.0)))
-              + T(180.0) / (one + ex((V + T(30.0)) * T(1.0 / 10.0))) + T(20.0);
+        T inf = one / (one + expf((V + T(20.0)) * T(1.0 / 7.0)));
+        T tau = T(1102.5) * expf(-sqt(V + T(27.0)) * T(1.0 / 225.0)) + T(200.0) / (one + expf((T(13.0) - V) * T(1.0 / 10.0)))
+              + T(180.0) / (one + expf((V + T(30.0)) * T(1.0 / 10.0))) + T(20.0);
         n1 = adv(7, inf, tau, o1);
     }
     po.cal = o0 * o1;
     pn.cal = n0 * n1;
     {
-        T inf = T(0.67) / (one + ex((V + T(35.0)) * T(1.0 / 7.0))) + T(0.33);
-        T tau = T(562.0) * ex(-sqt(V + T(27.0)) * T(1.0 / 240.0)) + T(31.0) / (one + ex((T(25.0) - V) * T(1.0 / 10.0)))
-              + T(80.0) / (one + ex((V + T(30.0)) * T(1.0 / 10.0)));
+        T inf = T(0.67) / (one + expf((V + T(35.0)) * T(1.0 / 7.0))) + T(0.33);
+        T tau = T(562.0) * expf(-sqt(V + T(27.0)) * T(1.0 / 240.0)) + T(31.0) / (one + expf((T(25.0) - V) * T(1.0 / 10.0)))
+              + T(80.0) / (one + expf((V + T(30.0)) * T(1.0 / 10.0)));
         n0 = adv(8, inf, tau, o0);
     }
     {
@@ -295,15 +298,144 @@ __device__ __forceinline__ void tt_gates(T V, T dt, T cass, T *__restrict__ g, i
     pn.cal = pn.cal * n0 * n1;
     // transient outward s (endocardial), r
     {
-        T inf = one / (one + ex((V + T(28.0)) * T(1.0 / 5.0)));
-        T tau = T(1000.0) * ex(-sqt(V + T(67.0)) * T(1.0 / 1000.0)) + T(8.0);
+        T inf = one / (one + expf((V + T(28.0)) * T(1.0 / 5.0)));
+        T tau = T(1000.0) * expf(-sqt(V + T(67.0)) * T(1.0 / 1000.0)) + T(8.0);
         n0 = adv(10, inf, tau, o0);
     }
     {
-        T inf = one / (one + ex((T(20.0) - V) * T(1.0 / 6.0)));
-        T tau = T(9.5) * ex(-sqt(V + T(40.0)) * T(1.0 / 1800.0)) + T(0.8);
+        T inf = one / (one + expf((T(20.0) - V) * T(1.0 / 6.0)));
+        T tau = T(9.5) * expf(-sqt(V + T(40.0)) * T(1.0 / 1800.0)) + T(0.8);
         n1 = adv(11, inf, tau, o1);
     }
+    po.to = o1 * o0;
+    pn.to = n1 * n0;
+}
+
+// The same gates in FP64 with fewer operations: the sigmoids' exponentials
+// share a few bases (e^{V/20} gives those of V/10, e^{V/14} those of V/7,
+// e^{V/15} those of V/7.5, reciprocals their inverses) and every time constant
+// enters as its rate with the denominators cleared.  V is held within
+// +-2400 mV, beyond which every gate has saturated, so that no product of two
+// denominators overflows.  The m gate keeps exponentials of its own: its
+// steep time constant makes the current feel the rounding of e^{V/5}'s larger
+// argument.
+__device__ __forceinline__ void tt_gates64(const cell::Coef &C, double V, double dt, double cass,
+                                           double *__restrict__ g, int64_t ld, GateProducts &po,
+                                           GateProducts &pn)
+{
+    using namespace cell;
+    const double ndt = -dt;
+    // gates are loaded three ahead of their use
+    double gy[12];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) gy[k] = g[k * ld];
+    // advance gate s towards inf at the rate 1/tau; old value to y0
+    auto adv = [&](int s, double inf, double rate, double &y0) -> double {
+        y0 = gy[s];
+        if (s + 3 < 12) gy[s + 3] = g[(s + 3) * ld];
+        const double y1 = inf - (inf - y0) * exp_neg(C, ndt * rate);
+        g[s * ld] = y1;
+        return y1;
+    };
+    const double v = clip(V, 2400.0);
+    const double E20 = exp_(C, v * (1.0 / 20.0)), E14 = exp_(C, v * (1.0 / 14.0));
+    const double E15 = exp_(C, v * (1.0 / 15.0));
+    const double I20 = rcp(E20), I14 = rcp(E14), I15 = rcp(E15);
+    const double E10 = E20 * E20, I10 = I20 * I20;
+    const double E5 = exp_(C, v * (1.0 / 5.0));
+    const double E7 = E14 * E14, I7 = I14 * I14;
+    const double I6 = exp_(C, v * (-1.0 / 6.0));
+    auto one = [](double c, double E) { return __builtin_fma(c, E, 1.0); };   // 1 + c E
+    double o0, o1, o2, n0, n1, n2, ra, rb;
+
+    // rapid delayed rectifier xr1, xr2
+    ra = rcp(one(0.0243728440732796, I7));
+    rb = rcp(1.0 + exp_(C, (v + 88.0) * (1.0 / 24.0)));
+    n0 = adv(0, ra, one(0.011108996538242306, I10) * (1.0 + exp_(C, (v + 30.0) * (1.0 / 11.5)))
+                        * (1.0 / 2700.0), o0);
+    n1 = adv(1, rb, one(0.049787068367863944, I20) * one(0.049787068367863944, E20)
+                        * (1.0 / (3.0 * 1.12)), o1);
+    po.kr = o0 * o1;
+    pn.kr = n0 * n1;
+    // slow delayed rectifier xs
+    {
+        const double f = sqrt(one(2.300975890892825, I6)) * one(0.09697196786440507, E15);
+        ra = rcp(one(0.6996725373751304, I14));
+        rb = rcp(__builtin_fma(80.0, f, 1400.0));
+        n0 = adv(2, ra, f * rb, o0);
+    }
+    po.ks = o0 * o0;
+    pn.ks = n0 * n0;
+    // fast sodium m, h, j
+    {
+        const double q = 1.0 + exp_(C, (-56.86 - v) * (1.0 / 9.03));
+        const double e1 = exp_(C, (-60.0 - v) * (1.0 / 5.0));
+        const double e2 = exp_(C, (v + 35.0) * (1.0 / 5.0)), e3 = exp_(C, (v - 50.0) * (1.0 / 200.0));
+        ra = rcp(q * q);
+        rb = rcp(2.0 + e2 + e3);
+        n0 = adv(3, ra, 10.0 * (1.0 + e1) * (1.0 + e2) * (1.0 + e3) * rb, o0);
+    }
+    {
+        const double q = 1.0 + exp_(C, (v + 71.55) * (1.0 / 7.43)), q2 = q * q;
+        double rate_h, rate_j;
+        if (v < -40.0) {
+            const double da = 1.0 + exp_(C, 0.311 * (v + 79.23)), db = 1.0 + exp_(C, -0.1378 * (v + 40.14));
+            rate_h = 0.057 * exp_(C, (v + 80.0) * (-1.0 / 6.8))
+                   + (2.7 * exp_(C, 0.079 * v) + 3.1e5 * exp_(C, 0.3485 * v));
+            rate_j = (-25428.0 * exp_(C, 0.2444 * v) - 6.948e-6 * exp_(C, -0.04391 * v)) * (v + 37.78)
+                         * rcp(da)
+                   + 0.02424 * exp_(C, -0.01052 * v) * rcp(db);
+        } else {
+            const double dh = 1.0 + exp_(C, (v + 10.66) * (-1.0 / 11.1)), dj = one(0.04076220397836622, I10);
+            rate_h = (0.77 / 0.13) * rcp(dh);
+            rate_j = 0.6 * exp_(C, 0.057 * v) * rcp(dj);
+        }
+        n1 = adv(4, rcp(q2), rate_h, o1);
+        n2 = adv(5, rcp(q2), rate_j, o2);
+    }
+    po.na = o0 * o0 * o0 * o1 * o2;
+    pn.na = n0 * n0 * n0 * n1 * n2;
+    // L-type calcium d, f, f2, fCass
+    {
+        const double p = 1.0 + exp_(C, (-35.0 - v) * (1.0 / 13.0)), q = one(2.718281828459045, E5);
+        const double t = one(12.182493960703473, I20), pq = p * q;
+        ra = rcp(one(0.34415378686541237, I15 * I15));
+        rb = rcp(1.4 * __builtin_fma(0.25, p, 1.4) * t + pq);
+        n0 = adv(6, ra, pq * t * rb, o0);
+    }
+    const double b = one(20.085536923187668, E10), x27 = sq(v + 27.0);
+    {
+        const double a = one(3.669296667619244, I10), ab = a * b;
+        const double den = __builtin_fma(1102.5, exp_(C, x27 * (-1.0 / 225.0)), 20.0) * ab
+                         + (200.0 * b + 180.0 * a);
+        ra = rcp(one(17.41170806332765, E7));
+        rb = rcp(den);
+        n1 = adv(7, ra, ab * rb, o1);
+    }
+    po.cal = o0 * o1;
+    pn.cal = n0 * n1;
+    {
+        const double a = one(12.182493960703473, I10), ab = a * b;
+        const double den = 562.0 * exp_(C, x27 * (-1.0 / 240.0)) * ab + (31.0 * b + 80.0 * a);
+        ra = rcp(one(148.4131591025766, E7));
+        rb = rcp(den);
+        n0 = adv(8, __builtin_fma(0.67, ra, 0.33), ab * rb, o0);
+    }
+    {
+        const double f = 1.0 + sq(cass * (1.0 / 0.05));
+        ra = rcp(f);
+        rb = rcp(__builtin_fma(2.0, f, 80.0));
+        n1 = adv(9, __builtin_fma(0.6, ra, 0.4), f * rb, o1);
+    }
+    po.cal = po.cal * o0 * o1;
+    pn.cal = pn.cal * n0 * n1;
+    // transient outward s (endocardial), r
+    ra = rcp(one(270.42640742615265, E5));
+    rb = rcp(__builtin_fma(1000.0, exp_(C, sq(v + 67.0) * (-1.0 / 1000.0)), 8.0));
+    n0 = adv(10, ra, rb, o0);
+    ra = rcp(one(28.031624894526136, I6));
+    rb = rcp(__builtin_fma(9.5, exp_(C, sq(v + 40.0) * (-1.0 / 1800.0)), 0.8));
+    n1 = adv(11, ra, rb, o1);
     po.to = o1 * o0;
     pn.to = n1 * n0;
 }
@@ -316,31 +448,39 @@ template <typename G>
 __device__ double tt_point(const IonicParams &P, double dt, double V, double *c,
                            G *__restrict__ g, int64_t ld)
 {
-    const VOnly vo = v_only(V);
+    const cell::Coef C = cell::make_coef();
     const double cai = c[CAI], casr = c[CASR], cass = c[CASS], rbar = c[RBAR];
 
     // ---- gating variables at V^k (their products at u^k and u^{k+1}) ----
     GateProducts po, pn;
-    tt_gates<G>((G)V, (G)dt, (G)cass, g, ld, po, pn);
+    if constexpr (sizeof(G) == sizeof(double))
+        tt_gates64(C, V, dt, cass, g, ld, po, pn);
+    else
+        tt_gates32((float)V, (float)dt, (float)cass, g, ld, po, pn);
+    const VOnly vo = v_only(C, P, V);
 
     // ---- calcium subsystem and ion concentrations: rates at (V^k, u^k) ----
-    const Currents cur = tt_currents(P, V, vo, c, po);
-    double kcasr = MAX_SR - (MAX_SR - MIN_SR) / (1.0 + sq(EC_SR / casr));
-    double k1 = K1_PRIME / kcasr;
-    double k2 = K2_PRIME * kcasr;
-    double open_ = k1 * cass * cass * rbar / (K3 + k1 * cass * cass);
-    double i_rel = V_REL * open_ * (casr - cass);
-    double i_up = VMAX_UP / (1.0 + sq(K_UP) / sq(cai));
+    // (quotients with their denominators cleared)
+    const Currents cur = tt_currents(C, P, V, vo, c, po);
+    const double casr2 = casr * casr, cai2 = cai * cai;
+    const double xc = sq(cai + KBUF_C), xsr = sq(casr + KBUF_SR), xss = sq(cass + KBUF_SS);
+    const double r_sr = cell::rcp(casr2 + EC_SR * EC_SR);
+    const double r_up = cell::rcp(cai2 + K_UP * K_UP);
+    const double r_c = cell::rcp(xc + BUF_C * KBUF_C);
+    const double r_bsr = cell::rcp(xsr + BUF_SR * KBUF_SR);
+    const double kcasr = MAX_SR - (MAX_SR - MIN_SR) * (casr2 * r_sr);
+    const double k1c2 = K1_PRIME * cass * cass;
+    const double r_ss = cell::rcp(xss + BUF_SS * KBUF_SS);
+    const double r_open = cell::rcp(K3 * kcasr + k1c2);
+    double i_rel = V_REL * (k1c2 * rbar * r_open) * (casr - cass);
+    double i_up = VMAX_UP * (cai2 * r_up);
     double i_leak = V_LEAK * (casr - cai);
     double i_xfer = V_XFER * (cass - cai);
-    double buf_c = 1.0 / (1.0 + BUF_C * KBUF_C / sq(cai + KBUF_C));
-    double buf_sr = 1.0 / (1.0 + BUF_SR * KBUF_SR / sq(casr + KBUF_SR));
-    double buf_ss = 1.0 / (1.0 + BUF_SS * KBUF_SS / sq(cass + KBUF_SS));
-    double d_rbar = -k2 * cass * rbar + K4 * (1.0 - rbar);
-    double d_cai = buf_c * ((i_leak - i_up) * (VOLSR / VOLC) + i_xfer
+    double d_rbar = -(K2_PRIME * kcasr) * cass * rbar + K4 * (1.0 - rbar);
+    double d_cai = (xc * r_c) * ((i_leak - i_up) * (VOLSR / VOLC) + i_xfer
                             - (cur.ibCa + cur.ipCa - 2.0 * cur.iNaCa) * (CAPAC / (2.0 * VOLC * Far)));
-    double d_casr = buf_sr * (i_up - i_rel - i_leak);
-    double d_cass = buf_ss * (-cur.iCaL * (CAPAC / (2.0 * VOLSS * Far)) + i_rel * (VOLSR / VOLSS)
+    double d_casr = (xsr * r_bsr) * (i_up - i_rel - i_leak);
+    double d_cass = (xss * r_ss) * (-cur.iCaL * (CAPAC / (2.0 * VOLSS * Far)) + i_rel * (VOLSR / VOLSS)
                               - i_xfer * (VOLC / VOLSS));
     double d_nai = -(cur.iNa + cur.ibNa + 3.0 * cur.iNaK + 3.0 * cur.iNaCa) * (CAPAC / (VOLC * Far));
     double d_ki = -(cur.iK1 + cur.ito + cur.iKr + cur.iKs - 2.0 * cur.iNaK + cur.ipK) * (CAPAC / (VOLC * Far));
@@ -354,14 +494,14 @@ __device__ double tt_point(const IonicParams &P, double dt, double V, double *c,
     c[RBAR] = rbar + dt * d_rbar;
 
     // ---- I_ion(V^k, u^{k+1}) ----
-    return tt_currents(P, V, vo, c, pn).total();
+    return tt_currents(C, P, V, vo, c, pn).total();
 }
 
 // ---------------------------------------------------------------------------
 // Courtemanche-Ramirez-Nattel 1998 human atrial cell (Am. J. Physiol. 275:
-// H301), 20 states + V, held in registers for the step:
-//   y[0..4]  Na_i K_i Ca_i Ca_up Ca_rel (mM; forward Euler)
-//   y[5..19] m h j oa oi ua ui xr xs d f fCa u v w (Rush-Larsen)
+// H301), 20 states + V:
+//   Na_i K_i Ca_i Ca_up Ca_rel (mM; forward Euler)
+//   m h j oa oi ua ui xr xs d f fCa u v w (Rush-Larsen)
 // params: gNa gK1 gto gKr gKs gCaL gbNa gbCa (nS/pF), INaK_max INaCa_max
 // IpCa_max (pA/pF), Iup_max (mM/ms), and a scale of gKur(V).
 // Currents are per unit capacitance; the membrane capacitance (100 pF) turns
@@ -391,19 +531,25 @@ __device__ const double CRN_U0[CRN_NS] = {11.17,  139.0,  1.013e-4, 1.488,    1.
                                           4.966e-3, 0.9986, 3.296e-5, 1.869e-2, 1.367e-4,
                                           0.9996, 0.7755, 0.0,      1.0,      0.9992};
 
-// x / (1 - e^{-x/s}), whose limit at x = 0 is s
-__device__ __forceinline__ double rise_ratio(double x, double s)
+// x / (1 - e^{-x/s}), whose limit at x = 0 is s; e receives e^{-x/s}
+__device__ __forceinline__ double rise_ratio(const cell::Coef &C, double x, double s, double &e)
 {
-    const double t = x / s;
-    return t != 0.0 ? x / -expm1(-t) : s;
+    double em1;
+    cell::exp_expm1(C, -x * (1.0 / s), e, em1);
+    return x != 0.0 ? cell::div(x, -em1) : s;
 }
 // x / (e^{x/s} - 1), whose limit at x = 0 is s
-__device__ __forceinline__ double fall_ratio(double x, double s)
+__device__ __forceinline__ double fall_ratio(const cell::Coef &C, double x, double s)
 {
-    const double t = x / s;
-    return t != 0.0 ? x / expm1(t) : s;
+    double e, em1;
+    cell::exp_expm1(C, x * (1.0 / s), e, em1);
+    return x != 0.0 ? cell::div(x, em1) : s;
 }
-__device__ __forceinline__ double logistic(double x) { return 1.0 / (1.0 + exp(-x)); }
+// 1 / (1 + e^{-x}), |x| < 700
+__device__ __forceinline__ double logistic(const cell::Coef &C, double x)
+{
+    return cell::rcp(1.0 + cell::exp_(C, -x));
+}
 
 struct CrnCurrents {
     double iNa, iK1, ito, iKur, iKr, iKs, iCaL, iNaK, iNaCa, ibNa, ibCa, ipCa;
@@ -413,49 +559,139 @@ struct CrnCurrents {
     }
 };
 
-__device__ __forceinline__ CrnCurrents crn_currents(const IonicParams &P, double V, const double *y)
+// products of the gates that enter the currents
+struct CrnGates {
+    double na;    // m^3 h j
+    double to;    // oa^3 oi
+    double kur;   // ua^3 ui
+    double kr;    // xr
+    double ks;    // xs
+    double cal;   // d f fCa
+};
+
+// currents at V, concentrations y[0..2] and gates summarised by gp
+__device__ __forceinline__ CrnCurrents crn_currents(const cell::Coef &C, const IonicParams &P, double V,
+                                                    const double *y, const CrnGates &gp)
 {
     using namespace crn;
+    using namespace cell;
     const double na = y[0], k = y[1], ca = y[2];
-    const double e_na = RT_F * log(NA_OUT / na), e_k = RT_F * log(K_OUT / k);
-    const double e_ca = 0.5 * RT_F * log(CA_OUT / ca);
-    const double u = V * (1.0 / RT_F);
+    const double e_na = RT_F * log_ratio(C, 4.941642422609304, 4.344622201918654e-16, na), e_k = RT_F * log_ratio(C, 1.6863989535702286, 7.914947588915769e-17, k);
+    const double e_ca = 0.5 * RT_F * log_ratio(C, 0.5877866649021191, -5.2182156685858313e-17, ca);
+    const double v = clip(V, 9e3), u = v * (1.0 / RT_F);   // every exponential stays in range
     CrnCurrents c;
-    const double m = y[5];
-    c.iNa = P.v[0] * (m * m * m) * y[6] * y[7] * (V - e_na);
-    c.iK1 = P.v[1] * (V - e_k) * logistic(-0.07 * (V + 80.0));
-    const double oa = y[8];
-    c.ito = P.v[2] * (oa * oa * oa) * y[9] * (V - e_k);
-    const double ua = y[10];
-    const double g_kur = P.v[12] * (0.005 + 0.05 * logistic((V - 15.0) * (1.0 / 13.0)));
-    c.iKur = g_kur * (ua * ua * ua) * y[11] * (V - e_k);
-    c.iKr = P.v[3] * y[12] * (V - e_k) * logistic(-(V + 15.0) * (1.0 / 22.4));
-    c.iKs = P.v[4] * y[13] * y[13] * (V - e_k);
-    c.iCaL = P.v[5] * y[14] * y[15] * y[16] * (V - 65.0);
-    const double pump_v = 1.0 / (1.0 + 0.1245 * exp(-0.1 * u) + 0.0365 * nak_sigma() * exp(-u));
-    const double pump_na = 1.0 / (1.0 + (NAK_KM_NA / na) * sqrt(NAK_KM_NA / na));
+    c.iNa = P.v[0] * gp.na * (V - e_na);
+    c.iK1 = P.v[1] * (V - e_k) * logistic(C, -0.07 * (v + 80.0));
+    c.ito = P.v[2] * gp.to * (V - e_k);
+    const double g_kur = P.v[12] * (0.005 + 0.05 * logistic(C, (v - 15.0) * (1.0 / 13.0)));
+    c.iKur = g_kur * gp.kur * (V - e_k);
+    c.iKr = P.v[3] * gp.kr * (V - e_k) * logistic(C, (v + 15.0) * (-1.0 / 22.4));
+    c.iKs = P.v[4] * (gp.ks * gp.ks) * (V - e_k);
+    c.iCaL = P.v[5] * gp.cal * (V - 65.0);
+    const double pump_v = rcp(1.0 + 0.1245 * exp_(C, -0.1 * u) + 0.0365 * nak_sigma() * exp_(C, -u));
+    const double na_ratio = NAK_KM_NA * rcp(na);
+    const double pump_na = rcp(1.0 + na_ratio * sqrt(na_ratio));
     c.iNaK = P.v[8] * pump_v * pump_na * (K_OUT / (K_OUT + NAK_KM_K));
-    const double e_in = exp(NACA_GAMMA * u), e_out = exp((NACA_GAMMA - 1.0) * u);
+    const double e_in = exp_(C, NACA_GAMMA * u), e_out = exp_(C, (NACA_GAMMA - 1.0) * u);
     const double km3 = NACA_KM_NA * NACA_KM_NA * NACA_KM_NA, nao3 = NA_OUT * NA_OUT * NA_OUT;
-    c.iNaCa = P.v[9] * (e_in * (na * na * na) * CA_OUT - e_out * nao3 * ca)
-            / ((km3 + nao3) * (NACA_KM_CA + CA_OUT) * (1.0 + NACA_SAT * e_out));
+    c.iNaCa = div(P.v[9] * (e_in * (na * na * na) * CA_OUT - e_out * nao3 * ca),
+                  (km3 + nao3) * (NACA_KM_CA + CA_OUT) * (1.0 + NACA_SAT * e_out));
     c.ibNa = P.v[6] * (V - e_na);
     c.ibCa = P.v[7] * (V - e_ca);
-    c.ipCa = P.v[10] * ca / (0.0005 + ca);
+    c.ipCa = P.v[10] * (ca * rcp(0.0005 + ca));
     return c;
 }
 
-// One step at one node: fluxes and rates at (V^k, u^k), then u^{k+1};
-// returns I_ion(V^k, u^{k+1}) / Cm (mV/ms).
-__device__ double crn_point(const IonicParams &P, double dt, double V, double *y)
+// One step at one node: concentrations y[0..4] (Na_i K_i Ca_i Ca_up Ca_rel)
+// by forward Euler, gates g[s * ld] (m h j oa oi ua ui xr xs d f fCa u v w) by
+// Rush-Larsen, streamed one at a time: the currents need six products of them.
+// Fluxes and rates at (V^k, u^k); returns I_ion(V^k, u^{k+1}) / Cm (mV/ms).
+__device__ double crn_point(const IonicParams &P, double dt, double V, double *y,
+                            double *__restrict__ g, int64_t ld)
 {
     using namespace crn;
-    const CrnCurrents c = crn_currents(P, V, y);
+    using namespace cell;
+    const Coef C = make_coef();
+    // ---- gates: Rush-Larsen with the rate 1/tau at V^k, which is held within
+    // +-3000 mV: every gate has saturated there and no exponential overflows ----
+    const double v = clip(V, 3000.0), ndt = -dt;
+    // gates are loaded three ahead of their use
+    double gy[15];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) gy[k] = g[k * ld];
+    // advance gate s towards inf at the given rate; old value to y0
+    auto adv = [&](int s, double inf, double rate, double &y0) -> double {
+        y0 = gy[s];
+        if (s + 3 < 15) gy[s + 3] = g[(s + 3) * ld];
+        const double y1 = inf - (inf - y0) * exp_neg(C, ndt * rate);
+        g[s * ld] = y1;
+        return y1;
+    };
+    CrnGates po, pn;
+    double e, o0, o1, o2, n0, n1, n2;
+    {   // fast sodium m, h, j from their opening and closing rates
+        const double am = 0.32 * rise_ratio(C, v + 47.13, 10.0, e), bm = 0.08 * exp_(C, v * (-1.0 / 11.0));
+        n0 = adv(0, div(am, am + bm), am + bm, o0);
+        double ah = 0.0, bh, aj = 0.0, bj;
+        if (v < -40.0) {
+            ah = 0.135 * exp_(C, (v + 80.0) * (-1.0 / 6.8));
+            bh = 3.56 * exp_(C, 0.079 * v) + 3.1e5 * exp_(C, 0.35 * v);
+            aj = (-127140.0 * exp_(C, 0.2444 * v) - 3.474e-5 * exp_(C, -0.04391 * v)) * (v + 37.78)
+               * logistic(C, -0.311 * (v + 79.23));
+            bj = 0.1212 * exp_(C, -0.01052 * v) * logistic(C, 0.1378 * (v + 40.14));
+        } else {
+            bh = (1.0 / 0.13) * logistic(C, (v + 10.66) * (1.0 / 11.1));
+            bj = 0.3 * exp_(C, -2.535e-7 * v) * logistic(C, 0.1 * (v + 32.0));
+        }
+        n1 = adv(1, div(ah, ah + bh), ah + bh, o1);
+        n2 = adv(2, div(aj, aj + bj), aj + bj, o2);
+        po.na = o0 * o0 * o0 * o1 * o2;
+        pn.na = n0 * n0 * n0 * n1 * n2;
+    }
+    {   // transient (oa, oi) and ultrarapid (ua, ui) potassium, Q10 = 3
+        const double a_a = 0.65 * rcp(exp_(C, (v + 10.0) * (-1.0 / 8.5)) + exp_(C, (v - 30.0) * (-1.0 / 59.0)));
+        const double b_a = 0.65 * rcp(2.5 + exp_(C, (v + 82.0) * (1.0 / 17.0)));
+        const double r_a = (a_a + b_a) * Q10;
+        n0 = adv(3, logistic(C, (v + 20.47) * (1.0 / 17.54)), r_a, o0);
+        const double a_oi = rcp(18.53 + exp_(C, (v + 113.7) * (1.0 / 10.95)));
+        const double b_oi = rcp(35.56 + exp_(C, (v + 1.26) * (-1.0 / 7.44)));
+        n1 = adv(4, logistic(C, (v + 43.1) * (-1.0 / 5.3)), (a_oi + b_oi) * Q10, o1);
+        po.to = o0 * o0 * o0 * o1;
+        pn.to = n0 * n0 * n0 * n1;
+        n0 = adv(5, logistic(C, (v + 30.3) * (1.0 / 9.6)), r_a, o0);
+        const double a_ui = rcp(21.0 + exp_(C, (v - 185.0) * (-1.0 / 28.0)));
+        const double b_ui = exp_(C, (v - 158.0) * (1.0 / 16.0));
+        n1 = adv(6, logistic(C, (v - 99.45) * (-1.0 / 27.48)), (a_ui + b_ui) * Q10, o1);
+        po.kur = o0 * o0 * o0 * o1;
+        pn.kur = n0 * n0 * n0 * n1;
+    }
+    {   // rapid and slow delayed rectifiers
+        const double a_r = 0.0003 * rise_ratio(C, v + 14.1, 5.0, e);
+        const double b_r = 7.3898e-5 * fall_ratio(C, v - 3.3328, 5.1237);
+        pn.kr = adv(7, logistic(C, (v + 14.1) * (1.0 / 6.5)), a_r + b_r, po.kr);
+        const double a_s = 4e-5 * rise_ratio(C, v - 19.9, 17.0, e);
+        const double b_s = 3.5e-5 * fall_ratio(C, v - 19.9, 9.0);
+        pn.ks = adv(8, sqrt(logistic(C, (v - 19.9) * (1.0 / 12.7))), 2.0 * (a_s + b_s), po.ks);
+    }
+    {   // L-type calcium d, f, fCa
+        const double x = v + 10.0;
+        // 1/tau_d = 0.035 x (1 + e^{-x/6.24}) / (1 - e^{-x/6.24})
+        const double r_x = rise_ratio(C, x, 6.24, e), r_d = 0.035 * r_x * (1.0 + e);
+        n0 = adv(9, logistic(C, x * (1.0 / 8.0)), r_d, o0);
+        const double r_f = (0.0197 * exp_(C, -(0.0337 * 0.0337) * x * x) + 0.02) * (1.0 / 9.0);
+        n1 = adv(10, logistic(C, (v + 28.0) * (-1.0 / 6.9)), r_f, o1);
+        n2 = adv(11, rcp(1.0 + y[2] * (1.0 / 0.00035)), 0.5, o2);
+        po.cal = o0 * o1 * o2;
+        pn.cal = n0 * n1 * n2;
+    }
+
+    // ---- currents and fluxes at (V^k, u^k) ----
+    const CrnCurrents c = crn_currents(C, P, V, y, po);
     const double ca = y[2], ca_up = y[3], ca_rel = y[4];
-    const double uu = y[17];
-    const double j_rel = REL_RATE * (uu * uu) * y[18] * y[19] * (ca_rel - ca);
+    const double uu = gy[12];
+    const double j_rel = REL_RATE * (uu * uu) * gy[13] * gy[14] * (ca_rel - ca);
     const double j_tr = (ca_up - ca_rel) * (1.0 / TR_TAU);
-    const double j_up = P.v[11] / (1.0 + UP_KM / ca);
+    const double j_up = P.v[11] * (ca * rcp(ca + UP_KM));
     const double j_leak = P.v[11] * ca_up * (1.0 / UP_CA_MAX);
     // current (pA/pF) to concentration rate in the myoplasm (mM/ms)
     constexpr double to_conc = CAP / (FARADAY * VOL_I);
@@ -463,72 +699,26 @@ __device__ double crn_point(const IonicParams &P, double dt, double V, double *y
     const double d_k = to_conc * (2.0 * c.iNaK - (c.iK1 + c.ito + c.iKur + c.iKr + c.iKs));
     const double free_ca = 0.5 * to_conc * (2.0 * c.iNaCa - c.ipCa - c.iCaL - c.ibCa)
                          + (VOL_UP * (j_leak - j_up) + VOL_REL * j_rel) * (1.0 / VOL_I);
-    const double b_cmdn = CMDN_TOT * CMDN_KM / ((ca + CMDN_KM) * (ca + CMDN_KM));
-    const double b_trpn = TRPN_TOT * TRPN_KM / ((ca + TRPN_KM) * (ca + TRPN_KM));
-    const double d_ca = free_ca / (1.0 + b_trpn + b_cmdn);
+    // free_ca / (1 + buffering by troponin and calmodulin), denominators cleared
+    const double x_cmdn = sq(ca + CMDN_KM), x_trpn = sq(ca + TRPN_KM), x_both = x_cmdn * x_trpn;
+    const double d_ca = free_ca * x_both
+                      * rcp(x_both + (TRPN_TOT * TRPN_KM) * x_cmdn + (CMDN_TOT * CMDN_KM) * x_trpn);
     const double d_up = j_up - j_leak - j_tr * (VOL_REL / VOL_UP);
-    const double d_rel = (j_tr - j_rel) / (1.0 + CSQN_TOT * CSQN_KM / ((ca_rel + CSQN_KM) * (ca_rel + CSQN_KM)));
+    const double x_csqn = sq(ca_rel + CSQN_KM);
+    const double d_rel = (j_tr - j_rel) * x_csqn * rcp(x_csqn + CSQN_TOT * CSQN_KM);
 
     // release trigger: SR release plus the Ca entry of I_CaL and I_NaCa (pA)
     const double fn = 1e-12 * VOL_REL * j_rel - (5e-13 / FARADAY) * CAP * (0.5 * c.iCaL - 0.2 * c.iNaCa);
-    const double on_u = logistic((fn - 3.4175e-13) * (1.0 / 13.67e-16));
+    const double on_u = logistic(C, clip((fn - 3.4175e-13) * (1.0 / 13.67e-16), 700.0));
 
-    // ---- gates: Rush-Larsen with the rate 1/tau at V^k ----
-    {   // fast sodium m, h, j from their opening and closing rates
-        const double am = 0.32 * rise_ratio(V + 47.13, 10.0), bm = 0.08 * exp(-V * (1.0 / 11.0));
-        y[5] = rush_larsen_rate(y[5], am / (am + bm), am + bm, dt);
-        double ah = 0.0, bh, aj = 0.0, bj;
-        if (V < -40.0) {
-            ah = 0.135 * exp(-(V + 80.0) * (1.0 / 6.8));
-            bh = 3.56 * exp(0.079 * V) + 3.1e5 * exp(0.35 * V);
-            aj = (-127140.0 * exp(0.2444 * V) - 3.474e-5 * exp(-0.04391 * V)) * (V + 37.78)
-               * logistic(-0.311 * (V + 79.23));
-            bj = 0.1212 * exp(-0.01052 * V) * logistic(0.1378 * (V + 40.14));
-        } else {
-            bh = (1.0 / 0.13) * logistic((V + 10.66) * (1.0 / 11.1));
-            bj = 0.3 * exp(-2.535e-7 * V) * logistic(0.1 * (V + 32.0));
-        }
-        y[6] = rush_larsen_rate(y[6], ah / (ah + bh), ah + bh, dt);
-        y[7] = rush_larsen_rate(y[7], aj / (aj + bj), aj + bj, dt);
-    }
-    {   // transient (oa, oi) and ultrarapid (ua, ui) potassium, Q10 = 3
-        const double a_a = 0.65 / (exp(-(V + 10.0) * (1.0 / 8.5)) + exp(-(V - 30.0) * (1.0 / 59.0)));
-        const double b_a = 0.65 / (2.5 + exp((V + 82.0) * (1.0 / 17.0)));
-        const double r_a = (a_a + b_a) * Q10;
-        y[8] = rush_larsen_rate(y[8], logistic((V + 20.47) * (1.0 / 17.54)), r_a, dt);
-        y[10] = rush_larsen_rate(y[10], logistic((V + 30.3) * (1.0 / 9.6)), r_a, dt);
-        const double a_oi = 1.0 / (18.53 + exp((V + 113.7) * (1.0 / 10.95)));
-        const double b_oi = 1.0 / (35.56 + exp(-(V + 1.26) * (1.0 / 7.44)));
-        y[9] = rush_larsen_rate(y[9], logistic(-(V + 43.1) * (1.0 / 5.3)), (a_oi + b_oi) * Q10, dt);
-        const double a_ui = 1.0 / (21.0 + exp(-(V - 185.0) * (1.0 / 28.0)));
-        const double b_ui = exp((V - 158.0) * (1.0 / 16.0));
-        y[11] = rush_larsen_rate(y[11], logistic(-(V - 99.45) * (1.0 / 27.48)), (a_ui + b_ui) * Q10, dt);
-    }
-    {   // rapid and slow delayed rectifiers
-        const double a_r = 0.0003 * rise_ratio(V + 14.1, 5.0);
-        const double b_r = 7.3898e-5 * fall_ratio(V - 3.3328, 5.1237);
-        y[12] = rush_larsen_rate(y[12], logistic((V + 14.1) * (1.0 / 6.5)), a_r + b_r, dt);
-        const double a_s = 4e-5 * rise_ratio(V - 19.9, 17.0);
-        const double b_s = 3.5e-5 * fall_ratio(V - 19.9, 9.0);
-        y[13] = rush_larsen_rate(y[13], sqrt(logistic((V - 19.9) * (1.0 / 12.7))), 2.0 * (a_s + b_s), dt);
-    }
-    {   // L-type calcium d, f, fCa
-        const double x = V + 10.0;
-        // 1/tau_d = 0.035 x (1 + e^{-x/6.24}) / (1 - e^{-x/6.24})
-        const double r_d = 0.035 * rise_ratio(x, 6.24) * (1.0 + exp(-x * (1.0 / 6.24)));
-        y[14] = rush_larsen_rate(y[14], logistic(x * (1.0 / 8.0)), r_d, dt);
-        const double r_f = (0.0197 * exp(-(0.0337 * 0.0337) * x * x) + 0.02) * (1.0 / 9.0);
-        y[15] = rush_larsen_rate(y[15], logistic(-(V + 28.0) * (1.0 / 6.9)), r_f, dt);
-        y[16] = rush_larsen_rate(y[16], 1.0 / (1.0 + ca * (1.0 / 0.00035)), 0.5, dt);
-    }
     {   // SR release gates u, v (trigger fn) and w (voltage)
-        y[17] = rush_larsen_rate(y[17], on_u, 1.0 / 8.0, dt);
-        const double v_inf = 1.0 - logistic((fn - 6.835e-14) * (1.0 / 13.67e-16));
-        y[18] = rush_larsen_rate(y[18], v_inf, 1.0 / (1.91 + 2.09 * on_u), dt);
-        const double xw = V - 7.9;
+        adv(12, on_u, 1.0 / 8.0, o0);
+        const double v_inf = 1.0 - logistic(C, clip((fn - 6.835e-14) * (1.0 / 13.67e-16), 700.0));
+        adv(13, v_inf, rcp(1.91 + 2.09 * on_u), o0);
+        const double xw = v - 7.9;
         // 1/tau_w = x (1 + 0.3 e^{-x/5}) / (6 (1 - e^{-x/5}))
-        const double r_w = rise_ratio(xw, 5.0) * (1.0 + 0.3 * exp(-xw * (1.0 / 5.0))) * (1.0 / 6.0);
-        y[19] = rush_larsen_rate(y[19], 1.0 - logistic((V - 40.0) * (1.0 / 17.0)), r_w, dt);
+        const double r_x = rise_ratio(C, xw, 5.0, e), r_w = r_x * (1.0 + 0.3 * e) * (1.0 / 6.0);
+        adv(14, 1.0 - logistic(C, (v - 40.0) * (1.0 / 17.0)), r_w, o0);
     }
     // ---- forward Euler for the concentrations ----
     y[0] += dt * d_na;
@@ -536,7 +726,7 @@ __device__ double crn_point(const IonicParams &P, double dt, double V, double *y
     y[2] = ca + dt * d_ca;
     y[3] = ca_up + dt * d_up;
     y[4] = ca_rel + dt * d_rel;
-    return crn_currents(P, V, y).total();
+    return crn_currents(C, P, V, y, pn).total();
 }
 
 // Row i holds a cell: i < n, or, with the per-tile count of real rows of the
@@ -548,10 +738,15 @@ __device__ __forceinline__ bool real_row(int64_t i, int64_t n, const int32_t *ti
 }
 
 // ---------------------------------------------------------------------------
-// The ten Tusscher-Panfilov update is latency bound (a chain of FP64
-// exponentials per node); streaming the gates through tt_gates keeps it at
-// ~123 registers, four wavefronts per SIMD with no spills.  A tighter bound
-// spills more than it gains.
+// The ten Tusscher-Panfilov and Courtemanche-Ramirez-Nattel updates were bound
+// by instruction issue: ~4,000 vector instructions a wavefront, half of them
+// the library's exponentials, logarithms and divisions.  With the functions of cell:: and shared
+// exponentials it is ~1,700, and the state traffic (18 or 20 rows read and
+// written) bounds the large sizes: at 1,255,450 cells 180 -> 117 us and
+// 178 -> 123 us (392 and 432 MB: 82 and 90 us at the copy rate), at 300,007
+// 58 -> 41 and 55 -> 42 us.  Gates are streamed, loaded three ahead of their
+// use: 108 and 117 registers, four wavefronts per SIMD with no spills (with
+// the CRN states held in registers it was 179 and two wavefronts, 134 us).
 template <int KIND>
 __global__ __launch_bounds__(256) void k_ionic_step(IonicParams P, int64_t n, int64_t ld, double dt,
                                                     double cm, const double *__restrict__ V,
@@ -585,12 +780,12 @@ __global__ __launch_bounds__(256) void k_ionic_step(IonicParams P, int64_t n, in
 #pragma unroll
         for (int s = 0; s < 6; ++s) u[s * ld + i] = c[s];
     } else if constexpr (KIND == MDX_KIND_CRN) {
-        double y[CRN_NS];
+        double c[5];
 #pragma unroll
-        for (int s = 0; s < CRN_NS; ++s) y[s] = u[s * ld + i];
-        iion = crn_point(P, dt, v, y);
+        for (int s = 0; s < 5; ++s) c[s] = u[s * ld + i];
+        iion = crn_point(P, dt, v, c, u + 5 * ld + i, ld);
 #pragma unroll
-        for (int s = 0; s < CRN_NS; ++s) u[s * ld + i] = y[s];
+        for (int s = 0; s < 5; ++s) u[s * ld + i] = c[s];
     }
     if (raw)
         out[i] = iion;
