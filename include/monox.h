@@ -443,7 +443,7 @@ MDX_API mdx_status mdx_mlp_grad(mdx_ctx *ctx, const float *params, int64_t n, co
  * the library runs on until the process ends; its address is resolved per
  * device at mdx_create.  Any n in [1, 2^31 - 1] fits (each workgroup takes
  * ceil(n / 8192) tiles of 32 samples); a larger n is rejected with
- * MDX_ERR_INVALID_ARG.  For n <= 8192 the samples are partitioned as in
+ * MDX_ERR_INVALID_ARG.  For n < 65505 the samples are partitioned as in
  * mdx_mlp_grad and the results are bitwise the same; above, they differ by
  * the FP32 summation order of the partials.  Allocates nothing and calls no
  * allocating routine.  All calls on one device share its array (each call

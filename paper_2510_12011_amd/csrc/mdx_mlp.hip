@@ -1,6 +1,6 @@
 // Per-node MLP of the learned warm start: 4 -> 64 -> 64 -> 64 -> 1, ReLU,
-// BF16 weights and activations, FP32 accumulation, on the 32x32x8 BF16 MFMA
-// of gfx950.  Forward (inference), gradient of the mean-squared error
+// BF16 weights and activations, FP32 accumulation, on the BF16 MFMA of
+// gfx950.  Forward (inference), gradient of the mean-squared error
 // (training) and Adam.
 //
 // Parameter vector (FP32 master copy, 8,705 values):
@@ -11,13 +11,12 @@
 // accumulators) plus FP32 bias; h2 = bf16(relu(z2)); h3 = relu(z3) in FP32;
 // y = sum bf16(W4) h3 + b4 in FP32.
 //
-// One wavefront handles a tile of 32 nodes.  Hidden layers are computed as
-// transposed products Z^T = W H^T (M = output unit, N = node, K = input
-// unit).  With v_mfma_f32_32x32x8_bf16 the accumulator element held in
-// register v of lane l is Z^T[8(v/4) + 4(l/32) + v%4][l%32]; the B operand
-// of the next layer's K-step s in lane l is H^T[8s + 4(l/32) + i][l%32],
-// i = 0..3.  These coincide (s = v/4 within a 32-row output tile), so each
-// layer's output feeds the next MFMA from registers with no data exchange.
+// Inference gives a wavefront tiles of 32 nodes.  Hidden layers are computed
+// as transposed products Z^T = W H^T (M = output unit, N = node, K = input
+// unit).  With the 32x32 MFMAs the accumulator element held in register v of
+// lane l is Z^T[8(v/4) + 4(l/32) + v%4][l%32], which the next layer's B operand
+// takes from registers with no data exchange (the weights' columns are read in
+// that order).
 #include "mdx_device.h"
 #include "mdx_internal.h"
 
@@ -48,121 +47,9 @@ __device__ __forceinline__ unsigned short f2bf(float f)
 __device__ __forceinline__ float bf2f(unsigned short h) { return __uint_as_float((unsigned)h << 16); }
 __device__ __forceinline__ float round_bf(float f) { return bf2f(f2bf(f)); }
 
-__device__ __forceinline__ f32x16 mfma(bf16x4 a, bf16x4 b, f32x16 c)
-{
-    return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, b, c, 0, 0, 0);
-}
-
-// weights staged in LDS once per workgroup
-struct MlpLds {
-    float w1[NH][4];       // BF16-rounded
-    float b1[NH];
-    unsigned short w2[NH * WSTRIDE];
-    float b2[NH];
-    unsigned short w3[NH * WSTRIDE];
-    float b3[NH];
-    float w4[NH];          // BF16-rounded
-    float b4;
-};
-
-__device__ void load_weights(const float *__restrict__ P, MlpLds &w)
-{
-    for (int i = threadIdx.x; i < NH * 4; i += blockDim.x) w.w1[i / 4][i % 4] = round_bf(P[OFF_W1 + i]);
-    for (int i = threadIdx.x; i < NH * NH; i += blockDim.x) {
-        const int o = i / NH, k = i % NH;
-        w.w2[o * WSTRIDE + k] = f2bf(P[OFF_W2 + i]);
-        w.w3[o * WSTRIDE + k] = f2bf(P[OFF_W3 + i]);
-    }
-    for (int i = threadIdx.x; i < NH; i += blockDim.x) {
-        w.b1[i] = P[OFF_B1 + i];
-        w.b2[i] = P[OFF_B2 + i];
-        w.b3[i] = P[OFF_B3 + i];
-        w.w4[i] = round_bf(P[OFF_W4 + i]);
-    }
-    if (threadIdx.x == 0) w.b4 = P[OFF_B4];
-}
-
-// A fragment of W (rows = output units): lane holds W[32 ot + l%32][8 ks + 4 half + 0..3]
-__device__ __forceinline__ bf16x4 frag_w(const unsigned short *w, int ot, int ks, int lane)
-{
-    const int o = 32 * ot + (lane & 31), k = 8 * ks + 4 * (lane >> 5);
-    return *reinterpret_cast<const bf16x4 *>(w + o * WSTRIDE + k);
-}
-
-// A fragment of W^T (rows = input units): lane holds W[8 s + 4 half + i][32 kt + l%32]
-__device__ __forceinline__ bf16x4 frag_wt(const unsigned short *w, int kt, int s, int lane)
-{
-    const int k = 32 * kt + (lane & 31), o = 8 * s + 4 * (lane >> 5);
-    bf16x4 a;
-    a[0] = (short)w[(o + 0) * WSTRIDE + k];
-    a[1] = (short)w[(o + 1) * WSTRIDE + k];
-    a[2] = (short)w[(o + 2) * WSTRIDE + k];
-    a[3] = (short)w[(o + 3) * WSTRIDE + k];
-    return a;
-}
-
-// unit index held in accumulator register v of output tile ot by this lane
-__device__ __forceinline__ int unit_of(int ot, int v, int half) { return 32 * ot + 8 * (v / 4) + 4 * half + (v % 4); }
-
-struct Tile {
-    bf16x4 h1[8];      // B fragments: h1 for units 8t + 4 half + i
-    bf16x4 h2[8];      // B fragments: h2 for units 8t + 4 half + i
-    float z1[32];      // layer-1 pre-activations (same units as h1, t*4 + i)
-    float z2[32];      // layer-2 pre-activations, index 16 ot + v
-    float z3[32];      // layer-3 pre-activations, index 16 ot + v
-    float y;
-};
-
-__device__ __forceinline__ void forward_tile(const MlpLds &w, float4 x, Tile &T, bool keep)
-{
-    const int lane = threadIdx.x & 63, half = lane >> 5;
-    // layer 1 (VALU)
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int o = 8 * t + 4 * half + i;
-            float z = w.b1[o] + w.w1[o][0] * x.x + w.w1[o][1] * x.y + w.w1[o][2] * x.z + w.w1[o][3] * x.w;
-            if (keep) T.z1[4 * t + i] = z;
-            T.h1[t][i] = (short)f2bf(fmaxf(z, 0.0f));
-        }
-    }
-    // layer 2 (MFMA)
-#pragma unroll
-    for (int ot = 0; ot < 2; ++ot) {
-        f32x16 acc = {0};
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) acc = mfma(frag_w(w.w2, ot, ks, lane), T.h1[ks], acc);
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const float z = acc[v] + w.b2[unit_of(ot, v, half)];
-            if (keep) T.z2[16 * ot + v] = z;
-            T.h2[4 * ot + v / 4][v % 4] = (short)f2bf(fmaxf(z, 0.0f));
-        }
-    }
-    // layer 3 (MFMA) and output layer (VALU)
-    float s = 0.0f;
-#pragma unroll
-    for (int ot = 0; ot < 2; ++ot) {
-        f32x16 acc = {0};
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) acc = mfma(frag_w(w.w3, ot, ks, lane), T.h2[ks], acc);
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int o = unit_of(ot, v, half);
-            const float z = acc[v] + w.b3[o];
-            T.z3[16 * ot + v] = z;
-            s += w.w4[o] * fmaxf(z, 0.0f);
-        }
-    }
-    s += __shfl_xor(s, 32, 64);
-    T.y = s + w.b4;
-}
-
 // ---------------------------------------------------------------------------
-// Inference (the warm start of every time step).  Same function as
-// forward_tile with every layer on v_mfma_f32_32x32x16_bf16 (K = 16, twice
-// the K of the training kernels' instruction per issue):
+// Inference (the warm start of every time step), every layer on
+// v_mfma_f32_32x32x16_bf16:
 //   layer 1: the FP32 features enter as a BF16 pair hi + lo (x = hi + lo to
 //            about 2^-17 relative): B rows 0..3 hi, 4..7 lo, 8..15 zero and
 //            A columns W1, W1, 0, so one MFMA gives BF16(W1) x in FP32;
@@ -462,192 +349,299 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 }
 
 // ---------------------------------------------------------------------------
-// Training: gradient of L = (1/n) sum_i (y_i - t_i)^2.  One wavefront per
-// workgroup; each workgroup accumulates its samples' gradient into its own
-// slice of `partial` (NPARAM values + its loss sum), reduced afterwards in a
+// Training: gradient of L = (1/n) sum_i (y_i - t_i)^2.  Each workgroup
+// accumulates its samples' gradient in registers and writes it to its own
+// slice of `partials` (NPARAM values + its loss sum), reduced afterwards in a
 // fixed order by k_mlp_reduce -- no atomics, deterministic.
-// Weight gradients dW = dZ H^T are MFMA products over the tile's 32 nodes:
-// activations and deltas are staged in LDS as [unit][node] BF16 so that the
-// A fragments (lane = output unit) and B fragments (lane = input unit) are
-// 8-byte reads.  An extra row of ones in each staged input gives the bias
-// gradients as one more column of the same products.
+//
+// At the training batch of 8,192 samples a workgroup has one tile of 32 nodes,
+// so what counts is the length of the chain: weights in, three layers forward,
+// two back, four gradient products.  Four wavefronts share the tile, each
+// computing 16 of the 64 units of every layer (16x16x32 MFMA: lane l holds
+// row or column l % 16 and k = 8 (l / 16) .. + 7 of the operands, and rows
+// 4 (l / 16) .. + 3 of column l % 16 of the result).  A layer's output goes to
+// LDS twice: node by node for the next layer's B operand, and unit by unit for
+// the weight gradients dW = dZ H^T, products over the tile's nodes, which run
+// under the latency of the next layer back.  Bias gradients are the same
+// products with a column of ones.  On 8,192 samples with one wavefront a tile,
+// 32x32x8 MFMAs and partials read, added to and written per product it was
+// 98 us; 12 us now.
 // ---------------------------------------------------------------------------
-constexpr int SSTRIDE = 36;   // staged row stride (bf16): 32 nodes + pad
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-struct TrainLds {
-    MlpLds w;
-    unsigned short xs[32 * SSTRIDE];    // rows 0..3 features, 4 ones, rest 0
-    unsigned short h1s[96 * SSTRIDE];   // rows 0..63 h1, 64 ones, rest 0
-    unsigned short h2s[96 * SSTRIDE];
-    unsigned short h3s[96 * SSTRIDE];
-    unsigned short d1s[64 * SSTRIDE];   // dz1 [unit][node]
-    unsigned short d2s[64 * SSTRIDE];
-    unsigned short d3s[64 * SSTRIDE];
-    unsigned short dys[32 * SSTRIDE];   // row 0: dL/dy, rest 0
+constexpr int TW = 72;   // LDS row strides (bf16), 16-byte rows: a weight's or a node's 64 units,
+constexpr int TN = 40;   // a unit's 32 nodes
+
+struct alignas(16) TrainLds {
+    unsigned short w2[NH * TW], w3[NH * TW];     // [output][input]
+    unsigned short w2t[NH * TW], w3t[NH * TW];   // [input][output]
+    unsigned short by_node[2][32 * TW];          // the layer in hand [node][unit]
+    unsigned short h1[NH * TN], h2[NH * TN], h3[NH * TN];   // activations [unit][node]
+    unsigned short d1[NH * TN], d2[NH * TN], d3[NH * TN];   // dL/dz [unit][node]
+    unsigned short x[4 * TN], dy[TN];
+    float w1[NH][4];                             // BF16-rounded
+    float b1[NH], b2[NH], b3[NH], w4[NH];        // w4 BF16-rounded
+    float ysum[4][32];                           // a wavefront's part of y
+    float b4;
 };
+static_assert(2 * sizeof(TrainLds) <= 160 * 1024, "two workgroups a compute unit");
 
-__device__ __forceinline__ bf16x4 frag_rows(const unsigned short *s, int row, int ks, int lane)
+__device__ __forceinline__ f32x4 mfma32(s16x8 a, s16x8 b, f32x4 c)
 {
-    return *reinterpret_cast<const bf16x4 *>(s + row * SSTRIDE + 8 * ks + 4 * (lane >> 5));
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8n, a),
+                                                   __builtin_bit_cast(bf16x8n, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ s16x8 frag(const unsigned short *s, int stride, int row, int k)
+{
+    return *reinterpret_cast<const s16x8 *>(s + row * stride + k);
 }
 
-// acc[v] -> partial for output tile (mt, nt) of dW = D S^T where D rows are
-// output units m and S rows are inputs n; map(m, n) gives the parameter
-// index or -1.
-template <class Map>
-__device__ __forceinline__ void product_to_partial(const unsigned short *D, int mt,
-                                                   const unsigned short *S, int nt, float *part,
-                                                   Map map)
-{
-    const int lane = threadIdx.x & 63, half = lane >> 5;
-    f32x16 acc = {0};
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-        acc = mfma(frag_rows(D, 32 * mt + (lane & 31), ks, lane),
-                   frag_rows(S, 32 * nt + (lane & 31), ks, lane), acc);
-    const int n = 32 * nt + (lane & 31);
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int m = 32 * mt + 8 * (v / 4) + 4 * half + (v % 4);
-        const int idx = map(m, n);
-        if (idx >= 0) part[idx] += acc[v];
-    }
-}
-
-__global__ __launch_bounds__(64) void k_mlp_grad(const float *__restrict__ P, int64_t n,
-                                                 const float *__restrict__ X,
-                                                 const float *__restrict__ Tgt,
-                                                 int tiles_per_group, float *__restrict__ partials)
+__global__ __launch_bounds__(256, 2) void k_mlp_grad(const float *__restrict__ P, int64_t n,
+                                                     const float *__restrict__ X,
+                                                     const float *__restrict__ Tgt,
+                                                     int tiles_per_group,
+                                                     float *__restrict__ partials)
 {
     __shared__ TrainLds L;
-    load_weights(P, L.w);
-    const int lane = threadIdx.x;
-    const int half = lane >> 5;
-    const int j = lane & 31;
-    // constant rows: ones and zero padding
-    for (int i = lane; i < 32 * SSTRIDE; i += 64) {
-        const int row = i / SSTRIDE;
-        L.xs[i] = row == 4 ? (unsigned short)0x3f80 : 0;
-        L.dys[i] = 0;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r = lane & 15, q = lane >> 4;
+    const int64_t t0 = (int64_t)blockIdx.x * tiles_per_group;
+    const int64_t t1 = min(t0 + tiles_per_group, (n + 31) / 32);
+
+    // the lane's two nodes of a tile
+    float4 x[2];
+    float tg[2];
+    bool valid[2];
+    auto fetch = [&](int64_t tile) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int64_t node = tile * 32 + 16 * b + r;
+            valid[b] = node < n;
+            x[b] = make_float4(0.f, 0.f, 0.f, 0.f);
+            tg[b] = 0.0f;
+            if (valid[b]) {
+                x[b] = reinterpret_cast<const float4 *>(X)[node];
+                tg[b] = Tgt[node];
+            }
+        }
+    };
+    fetch(t0);
+    {   // weights into LDS, every load issued before the first conversion
+        constexpr int R = NH * NH / 256;
+        float a2[R], a3[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            a2[j] = P[OFF_W2 + tid + 256 * j];
+            a3[j] = P[OFF_W3 + tid + 256 * j];
+        }
+        const float a1 = P[OFF_W1 + tid];
+        float bb[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (tid < NH) {
+            bb[0] = P[OFF_B1 + tid];
+            bb[1] = P[OFF_B2 + tid];
+            bb[2] = P[OFF_B3 + tid];
+            bb[3] = P[OFF_W4 + tid];
+        }
+        if (tid == 0) L.b4 = P[OFF_B4];
+        const int k = tid & 63;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int o = wave + 4 * j;
+            const unsigned short c2 = f2bf(a2[j]), c3 = f2bf(a3[j]);
+            L.w2[o * TW + k] = c2;
+            L.w3[o * TW + k] = c3;
+            L.w2t[k * TW + o] = c2;
+            L.w3t[k * TW + o] = c3;
+        }
+        L.w1[tid / 4][tid % 4] = round_bf(a1);
+        if (tid < NH) {
+            L.b1[tid] = bb[0];
+            L.b2[tid] = bb[1];
+            L.b3[tid] = bb[2];
+            L.w4[tid] = round_bf(bb[3]);
+        }
     }
-    for (int i = lane; i < 96 * SSTRIDE; i += 64) {
-        const int row = i / SSTRIDE;
-        const unsigned short v = row == 64 ? (unsigned short)0x3f80 : 0;
-        L.h1s[i] = v;
-        L.h2s[i] = v;
-        L.h3s[i] = v;
-    }
-    float *part = partials + (int64_t)blockIdx.x * (NPARAM + 1);
-    for (int i = lane; i < NPARAM + 1; i += 64) part[i] = 0.0f;
     __syncthreads();
 
-    const double inv_n = 1.0 / (double)n;
+    const int u0 = 16 * wave + 4 * q;   // the lane's units u0 .. u0 + 3 of every layer
+    const s16x8 none = {0, 0, 0, 0, 0, 0, 0, 0};
+    const short bf_one = 0x3f80;
+    const s16x8 ones = {bf_one, bf_one, bf_one, bf_one, bf_one, bf_one, bf_one, bf_one};
+    const s16x8 bias_col = r == 0 ? ones : none;
+    f32x4 gw3[4] = {}, gw2[4] = {}, gb3 = {}, gb2 = {}, gw1 = {}, gw4 = {}, gb4 = {};
     float loss = 0.0f;
-    Tile T;
-    const int64_t t0 = (int64_t)blockIdx.x * tiles_per_group;
-    const int64_t n_tiles = (n + 31) / 32;
-    for (int64_t tile = t0; tile < min(t0 + tiles_per_group, n_tiles); ++tile) {
-        const int64_t node = tile * 32 + j;
-        const bool valid = node < n;
-        float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-        float tg = 0.0f;
-        if (valid) {
-            x = reinterpret_cast<const float4 *>(X)[node];
-            tg = Tgt[node];
-        }
-        forward_tile(L.w, x, T, true);
-        const float r = valid ? T.y - tg : 0.0f;
-        if (half == 0) loss += r * r;
-        const float dy = (float)(2.0 * inv_n) * r;
+    const float scale = (float)(2.0 * (1.0 / (double)n));
 
-        // output layer: dz3 = dy W4 (z3 > 0); stage h3 and dz3
-        bf16x4 d3f[8];
+    // a layer's values at the lane's units of node 16 b + r
+    auto put = [&](unsigned short *by_node, unsigned short *by_unit, int b, const float (&v)[4]) {
+        const int j = 16 * b + r;
+        const bf16x4 h = pack_bf16x4(v[0], v[1], v[2], v[3]);
+        if (by_node) *reinterpret_cast<bf16x4 *>(by_node + j * TW + u0) = h;
 #pragma unroll
-        for (int ot = 0; ot < 2; ++ot)
+        for (int i = 0; i < 4; ++i) by_unit[(u0 + i) * TN + j] = (unsigned short)h[i];
+    };
+    // 16 rows of w (this wavefront's) times the layer in hand, at 16 b .. + 15
+    auto layer = [&](const unsigned short *w, const unsigned short *by_node, f32x4 (&acc)[2]) {
+        acc[0] = acc[1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int o = unit_of(ot, v, half);
-                const float z = T.z3[16 * ot + v];
-                const float dz = z > 0.0f ? dy * L.w.w4[o] : 0.0f;
-                d3f[4 * ot + v / 4][v % 4] = (short)f2bf(dz);
-                L.d3s[o * SSTRIDE + j] = f2bf(dz);
-                L.h3s[o * SSTRIDE + j] = f2bf(fmaxf(z, 0.0f));
-            }
-        if (half == 0) L.dys[j] = f2bf(dy);
-        // dh2 = W3^T dz3 -> dz2 = dh2 (z2 > 0); stage h2 and dz2
-        bf16x4 d2f[8];
+        for (int s = 0; s < 2; ++s) {
+            const s16x8 a = frag(w, TW, 16 * wave + r, 32 * s + 8 * q);
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
-            f32x16 acc = {0};
-#pragma unroll
-            for (int s = 0; s < 8; ++s) acc = mfma(frag_wt(L.w.w3, kt, s, lane), d3f[s], acc);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int k = unit_of(kt, v, half);
-                const float z = T.z2[16 * kt + v];
-                const float dz = z > 0.0f ? acc[v] : 0.0f;
-                d2f[4 * kt + v / 4][v % 4] = (short)f2bf(dz);
-                L.d2s[k * SSTRIDE + j] = f2bf(dz);
-                L.h2s[k * SSTRIDE + j] = (unsigned short)T.h2[4 * kt + v / 4][v % 4];
-            }
+            for (int b = 0; b < 2; ++b)
+                acc[b] = mfma32(a, frag(by_node, TW, 16 * b + r, 32 * s + 8 * q), acc[b]);
         }
-        // dh1 = W2^T dz2 -> dz1 = dh1 (z1 > 0); stage h1, dz1, x
+    };
+    // rows 16 wave .. + 15 of D S^T and of D's row sums
+    auto product = [&](const unsigned short *D, const unsigned short *S, f32x4 (&gw)[4], f32x4 &gb) {
+        const s16x8 a = frag(D, TN, 16 * wave + r, 8 * q);
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
-            f32x16 acc = {0};
+        for (int c = 0; c < 4; ++c) gw[c] = mfma32(a, frag(S, TN, 16 * c + r, 8 * q), gw[c]);
+        gb = mfma32(a, bias_col, gb);
+    };
+
+    for (int64_t tile = t0; tile < t1; ++tile) {
+        float z1[2][4], z2[2][4], z3[2][4], v[4];
+        f32x4 acc[2];
+        // layer 1 (FP32)
 #pragma unroll
-            for (int s = 0; s < 8; ++s) acc = mfma(frag_wt(L.w.w2, kt, s, lane), d2f[s], acc);
+        for (int b = 0; b < 2; ++b) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int k = unit_of(kt, v, half);   // = 8 t + 4 half + i, t = 4 kt + v / 4
-                const int t = 4 * kt + v / 4, i = v % 4;
-                const float z = T.z1[4 * t + i];
-                L.d1s[k * SSTRIDE + j] = f2bf(z > 0.0f ? acc[v] : 0.0f);
-                L.h1s[k * SSTRIDE + j] = (unsigned short)T.h1[t][i];
+            for (int i = 0; i < 4; ++i) {
+                const float4 w = *reinterpret_cast<const float4 *>(L.w1[u0 + i]);
+                z1[b][i] = L.b1[u0 + i] + w.x * x[b].x + w.y * x[b].y + w.z * x[b].z + w.w * x[b].w;
+                v[i] = fmaxf(z1[b][i], 0.0f);
             }
-        }
-        if (half == 0) {
-            L.xs[0 * SSTRIDE + j] = f2bf(x.x);
-            L.xs[1 * SSTRIDE + j] = f2bf(x.y);
-            L.xs[2 * SSTRIDE + j] = f2bf(x.z);
-            L.xs[3 * SSTRIDE + j] = f2bf(x.w);
+            put(L.by_node[0], L.h1, b, v);
+            if (wave == b && q == 0) {
+                const bf16x4 f = pack_bf16x4(x[b].x, x[b].y, x[b].z, x[b].w);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) L.x[i * TN + 16 * b + r] = (unsigned short)f[i];
+            }
         }
         __syncthreads();
-        // weight and bias gradients: MFMA over the tile's 32 nodes
+        layer(L.w2, L.by_node[0], acc);
 #pragma unroll
-        for (int nt = 0; nt < 3; ++nt) {
-            product_to_partial(L.dys, 0, L.h3s, nt, part, [](int m, int c) {
-                return m == 0 ? (c < NH ? OFF_W4 + c : c == NH ? OFF_B4 : -1) : -1;
-            });
+        for (int b = 0; b < 2; ++b) {
 #pragma unroll
-            for (int mt = 0; mt < 2; ++mt) {
-                product_to_partial(L.d3s, mt, L.h2s, nt, part, [](int m, int c) {
-                    return c < NH ? OFF_W3 + m * NH + c : c == NH ? OFF_B3 + m : -1;
-                });
-                product_to_partial(L.d2s, mt, L.h1s, nt, part, [](int m, int c) {
-                    return c < NH ? OFF_W2 + m * NH + c : c == NH ? OFF_B2 + m : -1;
-                });
+            for (int i = 0; i < 4; ++i) {
+                z2[b][i] = acc[b][i] + L.b2[u0 + i];
+                v[i] = fmaxf(z2[b][i], 0.0f);
             }
+            put(L.by_node[1], L.h2, b, v);
+        }
+        __syncthreads();
+        // layer 3 and the output unit
+        layer(L.w3, L.by_node[1], acc);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            float s = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                z3[b][i] = acc[b][i] + L.b3[u0 + i];
+                v[i] = fmaxf(z3[b][i], 0.0f);
+                s += L.w4[u0 + i] * v[i];
+            }
+            put(nullptr, L.h3, b, v);
+            s += __shfl_xor(s, 16, 64);
+            s += __shfl_xor(s, 32, 64);
+            if (q == 0) L.ysum[wave][16 * b + r] = s;
+        }
+        __syncthreads();
+        // dz3 = dy W4 (z3 > 0)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int j = 16 * b + r;
+            const float y = ((L.ysum[0][j] + L.ysum[1][j]) + (L.ysum[2][j] + L.ysum[3][j])) + L.b4;
+            const float res = valid[b] ? y - tg[b] : 0.0f;
+            const float dy = scale * res;
+            if (wave == 0 && q == 0) {
+                loss += res * res;
+                L.dy[j] = f2bf(dy);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = z3[b][i] > 0.0f ? dy * L.w4[u0 + i] : 0.0f;
+            put(L.by_node[0], L.d3, b, v);
+        }
+        if (tile + 1 < t1) fetch(tile + 1);
+        __syncthreads();
+        // dz2 = W3^T dz3 (z2 > 0); the gradients of layer 3 and the output unit
+        layer(L.w3t, L.by_node[0], acc);
+        product(L.d3, L.h2, gw3, gb3);
+        {
+            const s16x8 a = r == 0 ? *reinterpret_cast<const s16x8 *>(L.dy + 8 * q) : none;
+            gw4 = mfma32(a, frag(L.h3, TN, 16 * wave + r, 8 * q), gw4);
+            gb4 = mfma32(a, bias_col, gb4);
         }
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-            product_to_partial(L.d1s, mt, L.xs, 0, part, [](int m, int c) {
-                return c < 4 ? OFF_W1 + m * 4 + c : c == 4 ? OFF_B1 + m : -1;
-            });
+        for (int b = 0; b < 2; ++b) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = z2[b][i] > 0.0f ? acc[b][i] : 0.0f;
+            put(L.by_node[1], L.d2, b, v);
+        }
         __syncthreads();
+        // dz1 = W2^T dz2 (z1 > 0)
+        layer(L.w2t, L.by_node[1], acc);
+        product(L.d2, L.h1, gw2, gb2);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = z1[b][i] > 0.0f ? acc[b][i] : 0.0f;
+            put(nullptr, L.d1, b, v);
+        }
+        __syncthreads();
+        {
+            const s16x8 f = r < 4 ? *reinterpret_cast<const s16x8 *>(L.x + r * TN + 8 * q)
+                                  : r == 4 ? ones : none;
+            gw1 = mfma32(frag(L.d1, TN, 16 * wave + r, 8 * q), f, gw1);
+        }
+        if (tile + 1 < t1) __syncthreads();   // before this tile's h1 and x are overwritten
     }
-    loss = wave_sum((double)loss);
-    if (lane == 0) part[NPARAM] = loss;
+
+    float *part = partials + (int64_t)blockIdx.x * (NPARAM + 1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int m = u0 + i;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            part[OFF_W2 + m * NH + 16 * c + r] = gw2[c][i];
+            part[OFF_W3 + m * NH + 16 * c + r] = gw3[c][i];
+        }
+        if (r < 4) part[OFF_W1 + m * 4 + r] = gw1[i];
+        if (r == 4) part[OFF_B1 + m] = gw1[i];
+        if (r == 0) {
+            part[OFF_B2 + m] = gb2[i];
+            part[OFF_B3 + m] = gb3[i];
+        }
+    }
+    if (q == 0) part[OFF_W4 + 16 * wave + r] = gw4[0];
+    if (wave == 0) {
+        loss = wave_sum((double)loss);
+        if (lane == 0) {
+            part[OFF_B4] = gb4[0];
+            part[NPARAM] = loss;
+        }
+    }
 }
 
+// 32 parameters a workgroup, the groups' rows in eight slices: one thread a
+// parameter walked 256 rows one after the other (60 us; 4.5 us now).
 __global__ __launch_bounds__(256) void k_mlp_reduce(int groups, const float *__restrict__ partials,
                                                     int64_t n, float *__restrict__ grad,
                                                     float *__restrict__ loss)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > NPARAM) return;
+    __shared__ float part[8][32];
+    const int c = threadIdx.x & 31, slice = threadIdx.x >> 5;
+    const int p = blockIdx.x * 32 + c;
     float s = 0.0f;
-    for (int g = 0; g < groups; ++g) s += partials[(int64_t)g * (NPARAM + 1) + p];
+    if (p <= NPARAM) {
+        const float *row = partials + p;
+#pragma unroll 16
+        for (int g = slice; g < groups; g += 8) s += row[(int64_t)g * (NPARAM + 1)];
+    }
+    part[slice][c] = s;
+    __syncthreads();
+    if (slice || p > NPARAM) return;
+    s = ((part[0][c] + part[1][c]) + (part[2][c] + part[3][c]))
+      + ((part[4][c] + part[5][c]) + (part[6][c] + part[7][c]));
     if (p < NPARAM)
         grad[p] = s;
     else if (loss)
@@ -734,14 +728,23 @@ void launch_mlp_forward_state(hipStream_t s, const float *P, int64_t n, const do
     hipLaunchKernelGGL(k_mlp_forward<true>, dim3(blocks), dim3(256), 0, s, P, n, in, y);
 }
 
+// Workgroups of a gradient: one a compute unit, two from eight tiles of 32
+// samples each on.  More rows of partials, 35 KB each, cost more to write and
+// sum than the second workgroup gains (gradient and reduction, 256 and 512
+// workgroups: 16,384 samples 18 and 24 us, 65,536 33 and 33, 262,144 92 and
+// 69; with 1,024 it is 78).
+constexpr int kGradLaunch = 256;
+constexpr int64_t kGradLaunchTwice = 2048;   // tiles
+
 void launch_mlp_grad(hipStream_t s, const float *P, int64_t n, const float *X, const float *T,
                      float *grad, float *loss, float *partials, int max_groups)
 {
     const int64_t tiles = (n + 31) / 32;
-    const int groups = mlp_grad_groups(n, max_groups);
+    const int groups = mlp_grad_groups(
+        n, std::min(max_groups, tiles < kGradLaunchTwice ? kGradLaunch : 2 * kGradLaunch));
     const int tpg = (int)((tiles + groups - 1) / groups);
-    hipLaunchKernelGGL(k_mlp_grad, dim3(groups), dim3(64), 0, s, P, n, X, T, tpg, partials);
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((NPARAM + 1 + 255) / 256), dim3(256), 0, s, groups,
+    hipLaunchKernelGGL(k_mlp_grad, dim3(groups), dim3(256), 0, s, P, n, X, T, tpg, partials);
+    hipLaunchKernelGGL(k_mlp_reduce, dim3((NPARAM + 1 + 31) / 32), dim3(256), 0, s, groups,
                        partials, n, grad, loss);
 }
 
