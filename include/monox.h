@@ -284,7 +284,7 @@ MDX_API mdx_status mdx_set_profiling(mdx_ctx *ctx, int32_t every_n);
  *                        indices as 16-bit offsets from a per-slice base,
  *                        2 bytes per stored entry instead of 4; 0 reads the
  *                        32-bit indices.  Results are bitwise the same.
- *   MDX_TUNE_ONCHIP_POLLS  single mesh: a solve whose matrix fits the
+ *   MDX_TUNE_ONCHIP_POLLS  a solve whose matrix fits the
  *                        registers and LDS of the device runs as one launch
  *                        whose workgroups (at most one per CU) exchange their
  *                        sums through memory; the value is how often a
@@ -295,7 +295,12 @@ MDX_API mdx_status mdx_set_profiling(mdx_ctx *ctx, int32_t every_n);
  *                        uses the streaming kernels.  MAX_GROUPS and
  *                        SPMV_MAX_GROUPS other than their defaults and
  *                        ITER_SCHEME 1 choose among the streaming kernels and
- *                        so select them too, as does a profiled step.
+ *                        so select them too, as does a profiled step.  In a
+ *                        batched context every instance has workgroups of its
+ *                        own; FORMAT, LANES_PER_ROW and TILES_PER_GROUP set by
+ *                        hand (not by mdx_autotune), PERSISTENT and a profiled
+ *                        step select the streaming kernels, and GRAPH has no
+ *                        effect on the single launch.
  * MAX_GROUPS, SPMV_MAX_GROUPS and ITER_SCHEME take effect at the next
  * mdx_prepare / mdx_run;
  * the batched keys need a prepared batched context and act at once. */

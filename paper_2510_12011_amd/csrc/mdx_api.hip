@@ -457,6 +457,7 @@ mdx_status mdx_prepare(mdx_ctx *ctx, double dt, void *scratch, size_t scratch_by
     if (mdx_status e = build_onchip(ctx, st)) return e;
     ctx->onchip_seen = 0;
     ctx->onchip_off = false;
+    ctx->layout_set = false;
     ctx->tiling = make_tiling(ctx->npad, ctx->max_groups);
     ctx->tiling_spmv = make_tiling(ctx->npad, ctx->spmv_max_groups);
     release_graphs(ctx);
@@ -603,6 +604,7 @@ mdx_status mdx_autotune(mdx_ctx *ctx, int32_t reps, mdx_tune_report *rep)
     if (st_) return st_;
     if (mdx_status e = set_iter_layout(ctx, best_fmt, best_lpr)) return e;
     if (mdx_status e = install_groups(ctx, best_tpb)) return e;
+    ctx->layout_set = false;
     r.format = best_fmt;
     r.lanes_per_row = best_lpr;
     r.tiles_per_group = best_tpb;
@@ -664,6 +666,7 @@ mdx_status mdx_set_tuning(mdx_ctx *ctx, int32_t key, int64_t value)
         if (value < 0 || value > 1000000000)
             return fail(ctx, MDX_ERR_INVALID_ARG, "onchip_polls must lie in [0, 10^9]");
         ctx->onchip_polls = (int)value;
+        release_graphs(ctx);
         return MDX_OK;
     case MDX_TUNE_ITER_SCHEME:
         if (value != 0 && value != 1) return fail(ctx, MDX_ERR_INVALID_ARG, "scheme is 0 or 1");
@@ -675,6 +678,7 @@ mdx_status mdx_set_tuning(mdx_ctx *ctx, int32_t key, int64_t value)
             return fail(ctx, MDX_ERR_STATE, "needs a prepared batched context");
         GUARD_BEGIN
         HIPCHK(hipSetDevice(ctx->device));
+        ctx->layout_set = true;
         return set_iter_layout(ctx, (int)value, value == 1 ? 8 : 1);
         GUARD_END
     case MDX_TUNE_LANES_PER_ROW:
@@ -683,6 +687,7 @@ mdx_status mdx_set_tuning(mdx_ctx *ctx, int32_t key, int64_t value)
             return fail(ctx, MDX_ERR_STATE, "needs a prepared batched context");
         GUARD_BEGIN
         HIPCHK(hipSetDevice(ctx->device));
+        ctx->layout_set = true;
         if (key == MDX_TUNE_LANES_PER_ROW) {
             if (value < 1 || value > 16) return fail(ctx, MDX_ERR_INVALID_ARG, "bad lanes per row");
             return set_iter_layout(ctx, ctx->fmt, (int)value);

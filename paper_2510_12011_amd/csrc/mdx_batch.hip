@@ -31,6 +31,9 @@
 // that raises a fault flag instead of hanging) between the SpMV, the update
 // and the direction, and each instance iterates until its next residual
 // replacement.
+//
+// Where the instances' matrices fit the registers and LDS of the device, the
+// whole solve is one launch instead (k_onchip_batch in mdx_onchip.hip).
 #include "mdx_device.h"
 #include "mdx_internal.h"
 
@@ -187,7 +190,7 @@ __global__ __launch_bounds__(256) void k_b_rhs_init(
     const double *__restrict__ Mv, const double *__restrict__ Kv, const double *__restrict__ dinv,
     const float *__restrict__ dinv32, StepParams sp, const GV3 *__restrict__ gv,
     double *__restrict__ x, double *__restrict__ b, float *__restrict__ r32,
-    float *__restrict__ delta, double *__restrict__ partial)
+    float *__restrict__ delta, double *__restrict__ partial, int keep_r)
 {
     const int g = logical_group(t.groups);
     const int4 gr = t.grp[g];
@@ -213,10 +216,10 @@ __global__ __launch_bounds__(256) void k_b_rhs_init(
         const double bi = sp.chi * mv - cK_old * kv;
         const double ri = bi - (cM_new * mx + cK_new * kx);
         x[row] = gv[row].x;
-        b[row] = bi;
+        b[row] = keep_r ? ri : bi;   // the single-launch solve updates the residual
         const float rf = (float)ri;
         r32[row] = rf;
-        delta[row] = 0.0f;
+        if (!keep_r) delta[row] = 0.0f;
         const float zf = dinv32[row] * rf;
         const double zi = dinv[row] * ri, di = dinv[row] * bi;
         acc[0] += (double)rf * (double)zf;
@@ -807,12 +810,12 @@ void launch_b_rhs_init(hipStream_t s, const SegTiling &t, SellView P, const doub
                        const double *Kv, const double *dinv, const float *dinv32,
                        const StepParams &sp, int64_t n_rows, const double *V, const double *Vprev,
                        const double *src, double *gv, double *x, double *b, float *r32,
-                       float *delta, double *partial, bool nt)
+                       float *delta, double *partial, bool nt, bool keep_r)
 {
     hipLaunchKernelGGL(k_b_gather_prep, dim3((unsigned)((n_rows + 255) / 256)), dim3(256), 0, s,
                        n_rows, sp, V, Vprev, src, (GV3 *)gv);
     MDX_LAUNCH_NT(nt, k_b_rhs_init, dim3(t.groups), dim3(TILE), 0, s, t, P.slice_ptr, P.col, Mv, Kv,
-                  dinv, dinv32, sp, (const GV3 *)gv, x, b, r32, delta, partial);
+                  dinv, dinv32, sp, (const GV3 *)gv, x, b, r32, delta, partial, keep_r ? 1 : 0);
 }
 
 void launch_b_init_finalize(hipStream_t s, const SegTiling &t, const double *partial,

@@ -65,26 +65,68 @@ mdx_status persistent_fault(mdx_ctx *c)
     return MDX_OK;
 }
 
-// ionic update, right-hand side and initial residual, `iters` PCG iterations
-// of every running instance, one residual-replacement pass.  With `timed`,
-// event pairs bracket the SpMV launches.
+// right-hand side and initial residual; keep_r: for the single-launch solve
+void enqueue_rhs(mdx_ctx *c, hipStream_t st, const BatchPtrs &q, bool keep_r)
+{
+    launch_b_rhs_init(st, c->seg, q.P, q.Mv, q.Kv, q.dinv, q.dinv32, step_params(c), c->npad,
+                      c->vec(0), c->vec(1), q.s, c->dev<double>(c->L.gv), c->vec(2), q.b, q.r32,
+                      q.delta, q.part0, use_nt(c, 20.0 * slots(c)), keep_r);
+    if (keep_r) return;
+    launch_b_init_finalize(st, c->seg, q.part0, batch_params(c), q.bsc);
+    launch_b_set_direction(st, c->seg, q.dinv32, q.r32, q.p32, q.bsc);
+}
+
+// The solve as one launch where the instances fit on chip; the tunings that
+// choose among the streaming kernels select those.
+bool batch_onchip(const mdx_ctx *c, bool profiling)
+{
+    return c->onchip_ready && c->onchip.shape[2] && c->onchip_polls > 0 && !c->onchip_off &&
+           !c->persistent && !c->layout_set && !profiling;
+}
+
+void enqueue_onchip(mdx_ctx *c, hipStream_t st, const BatchPtrs &q)
+{
+    OnchipBatch a{};
+    a.map = c->onchip_map;
+    a.grp = c->dev<int4>(c->L.oc_team);
+    a.part = q.part0;
+    a.part_groups = c->seg.groups;
+    a.inst_grp = c->seg.inst_grp;
+    a.bp = batch_params(c);
+    a.r = q.b;
+    a.x = c->vec(2);
+    a.dinv = q.dinv;
+    a.r32 = q.r32;
+    a.dinv32 = q.dinv32;
+    a.zb = c->dev<float>(c->L.oc_z);
+    a.words = c->dev<unsigned long long>(c->L.words);
+    a.polls = c->onchip_polls;
+    a.lanes = c->fmt <= 1 ? c->lpr : 1;   // sliced ELL or CSR; 4-entry loads add in column order
+    a.turn = c->dev<int32_t>(c->L.oc_turn);
+    a.sc = q.bsc;
+    launch_onchip_batch(st, c->onchip, a);
+}
+
+// ionic update, right-hand side and initial residual, then the solve in one
+// launch (iters < 0) or `iters` PCG iterations of every running instance and
+// one residual-replacement pass.  With `timed`, event pairs bracket the SpMV
+// launches.
 void enqueue_batched_step(mdx_ctx *c, hipStream_t st, int iters, const double *istim, bool timed)
 {
     const BatchPtrs q = batch_ptrs(c);
     const BParams bp = batch_params(c);
-    const StepParams sp = step_params(c);
-    double *V = c->vec(0), *Vprev = c->vec(1), *X = c->vec(2);
+    double *V = c->vec(0), *X = c->vec(2);
     if (c->opts.precision == MDX_PREC_MIXED_GATES32)
         launch_ionic_step_mixed(st, c->ionic_kind, c->ionic_params.data(), c->npad, c->npad, c->dt,
                                 c->cm, V, q.u, q.g32, istim, q.s, row_mask(c));
     else
         launch_ionic_step(st, c->ionic_kind, c->ionic_params.data(), c->npad, c->npad, c->dt, c->cm,
                           V, q.u, istim, q.s, 0, row_mask(c));
-    launch_b_rhs_init(st, c->seg, q.P, q.Mv, q.Kv, q.dinv, q.dinv32, sp, c->npad, V, Vprev, q.s,
-                      c->dev<double>(c->L.gv), X, q.b, q.r32, q.delta, q.part0,
-                      use_nt(c, 20.0 * slots(c)));
-    launch_b_init_finalize(st, c->seg, q.part0, bp, q.bsc);
-    launch_b_set_direction(st, c->seg, q.dinv32, q.r32, q.p32, q.bsc);
+    enqueue_rhs(c, st, q, iters < 0);
+    if (iters < 0) {
+        enqueue_onchip(c, st, q);
+        return;
+    }
     if (c->persistent) {
         launch_persistent(c, st, q, bp);
         iters = 0;
@@ -156,8 +198,12 @@ mdx_status run_batched(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double 
         if (mdx_status e = update_stimulus(ctx, st, k, any_stim)) return e;
         double *V = ctx->vec(0), *X = ctx->vec(2);
         const bool profiling = ctx->profile_every > 0 && k % ctx->profile_every == 0;
-        const int C = std::max(1, std::min(ctx->last_iters, max_iter));
-        if (ctx->use_graph && !profiling) {
+        const bool onchip = batch_onchip(ctx, profiling);
+        const int C = onchip ? -1 : std::max(1, std::min(ctx->last_iters, max_iter));
+        std::unique_lock<std::mutex> one;
+        if (onchip) one = std::unique_lock<std::mutex>(onchip_mutex(ctx->device));
+        // (six launches: a replay of them as a graph costs 8-10 us a step more)
+        if (ctx->use_graph && !profiling && !onchip) {
             const std::pair<int, int> key{ctx->persistent ? -1 : C, ctx->vb[0]};
             auto it = ctx->graphs.find(key);
             if (it == ctx->graphs.end()) {
@@ -180,6 +226,16 @@ mdx_status run_batched(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double 
         if (mdx_status e = fetch_bscalars(ctx, st)) return e;
         if (ctx->persistent)
             if (mdx_status e = persistent_fault(ctx)) return e;
+        if (onchip) {
+            one.unlock();
+            units = 0;
+            for (int i = 0; i < ctx->n_inst; ++i)
+                if (ctx->bsc_host[i].gave_up) ctx->onchip_off = true;
+            if (ctx->onchip_off) {   // the step's solve again, by the streaming kernels
+                enqueue_rhs(ctx, st, q, false);
+                if (mdx_status e = fetch_bscalars(ctx, st)) return e;
+            }
+        }
         while (!all_done(ctx) && units < max_iter + 1) {
             hipEvent_t e0 = nullptr, e1 = nullptr;
             if (profiling && 2 * units + 1 < (int)ctx->ev.size()) {

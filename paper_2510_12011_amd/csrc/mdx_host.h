@@ -20,6 +20,7 @@
 #include <cstring>
 #include <limits>
 #include <map>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -54,7 +55,7 @@ struct Layout {
     size_t pgrp, pinst_grp, pbar;   // batched form, persistent iteration
     // single-launch solve: exchange slots, block maps, values, z
     size_t words, oc_row, oc_col, oc_hptr, oc_hrow, oc_hat, oc_val64, oc_dinv64, oc_val32,
-        oc_dinv32, oc_away, oc_z;
+        oc_dinv32, oc_away, oc_z, oc_team, oc_turn, oc_quads;
     size_t csr_ptr, csr_col, csr_val, gv;
     size_t total;
     size_t x_xyz, x_tets, x_fibre, x_sig, x_vol, x_ek, x_cptr, x_contrib, x_total;
@@ -142,6 +143,7 @@ struct mdx_ctx {
     uint32_t onchip_launch = 0;  // launches so far
     uint32_t onchip_seen = 0;    // the last launch known to have given up
     bool onchip_off = false;     // one gave up: streaming kernels until the next prepare
+    bool layout_set = false;     // batched: a streaming layout was chosen by hand
 
     // batched form: instances, each a contiguous row range starting on a
     // TILE boundary (a single-mesh context has one instance, rows [0, n))
@@ -205,6 +207,9 @@ uint64_t hilbert_key(uint32_t x0, uint32_t x1, uint32_t x2, int bits);
 void hilbert_order(const std::vector<double> &xyz, int64_t p0, int64_t p1,
                    std::vector<int32_t> &out);
 void compact_columns(mdx_ctx *c);
+// held while a single-launch solve is in flight: two whose workgroups share
+// the CUs would each wait for workgroups that the other keeps off the chip
+std::mutex &onchip_mutex(int device);
 mdx_status build_onchip(mdx_ctx *c, hipStream_t st);
 SellView step_view(const mdx_ctx *c);
 int64_t sell_slot(const mdx_ctx *c, int64_t r, int32_t colv);

@@ -17,6 +17,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <vector>
+
 #include <cstdint>
 #include <type_traits>
 
@@ -207,6 +209,8 @@ struct OnchipMap {
     const int32_t *row;     // [position] row, -1 past the block's last
     const uint2 *col;       // [pass][quad][thread] window positions of 4 entries: the
                             //   block's own rows, then its halo
+    const int32_t *quads;   // [pass][wavefront] quads of its longest row, rounded up to
+                            //   even (uneven plans)
     const int32_t *halo_ptr, *halo_row;   // halo: row and position of each entry
     const uint32_t *halo_at;
     double *val64, *dinv64;   // [pass][pair][thread][2], [position]
@@ -235,10 +239,14 @@ struct OnchipSolve {
 struct OnchipPlan {
     int groups = 0;                  // 0: the matrix does not fit
     int rows = 0, width = 0;
-    const void *shape[2] = {nullptr, nullptr};   // FP64, FP32 (null: does not fit)
+    bool uneven = false;             // a block's rows sorted by length
+    const void *shape[3] = {nullptr, nullptr, nullptr};   // FP64, FP32, batched (null: does not fit)
+    std::vector<int> first;          // first workgroup of each system, then the end
 };
 // n rows, the longest of `width` entries
 OnchipPlan onchip_plan(int device, int64_t n, int width);
+// independent systems of n[i] rows, each with workgroups of its own
+OnchipPlan onchip_plan_batch(int device, const std::vector<int64_t> &n, int width);
 void launch_onchip_values(hipStream_t s, const OnchipPlan &p, const OnchipMap &m,
                           const int64_t *slice_ptr, const double *A, const double *dinv,
                           const float *A32, const float *dinv32);
@@ -332,7 +340,7 @@ struct alignas(128) BScalars {
     int32_t redirect;   // replacement did not stop: p = z + beta p pending
     int32_t nonfinite;  // a non-finite value reached a reduction
     int32_t failed;     // iteration cap reached without convergence
-    int32_t pad_;
+    int32_t gave_up;    // a single-launch solve gave up (stays set)
 };
 
 struct BParams {
@@ -341,6 +349,27 @@ struct BParams {
     int rr;             // replacement interval (0: only at the stopping test and the cap)
     int rel_mode;       // 0: relative to ||z_0||, 1: relative to ||D^-1 b||
 };
+
+// The batched solve in one launch (mdx_onchip.hip): every instance by its own
+// workgroups, from the right-hand-side pass's r64, r32 and partials to x.
+struct OnchipBatch {
+    OnchipMap map;
+    const int4 *grp;                 // [workgroup] {instance, its first workgroup, count, 0}
+    const double *part;              // right-hand-side partials of part_groups workgroups, an
+    int part_groups;                 //   instance's from inst_grp[instance] on
+    const int32_t *inst_grp;
+    BParams bp;
+    double *r, *x;                   // FP64 residual (in: of the warm start), solution
+    const double *dinv;
+    const float *r32, *dinv32;
+    float *zb;                       // by block position
+    unsigned long long *words;       // kOnchipWords
+    int polls;
+    int lanes;                       // of a row in the streaming layout (1, 2, 4, 8, 16)
+    int32_t *turn;                   // [instance] turn of its next exchange
+    BScalars *sc;
+};
+void launch_onchip_batch(hipStream_t s, const OnchipPlan &p, const OnchipBatch &a);
 
 // Alternative layout of the iteration matrix for lpr lanes per row
 // (lpr in {1, 2, 4}; 64 / lpr rows per wavefront): slices of 64/lpr rows;
@@ -379,7 +408,7 @@ void launch_b_rhs_init(hipStream_t s, const SegTiling &t, SellView P, const doub
                        const double *Kv, const double *dinv, const float *dinv32,
                        const StepParams &sp, int64_t n_rows, const double *V, const double *Vprev,
                        const double *src, double *gv, double *x, double *b, float *r32,
-                       float *delta, double *partial, bool nt);
+                       float *delta, double *partial, bool nt, bool keep_r);
 void launch_b_init_finalize(hipStream_t s, const SegTiling &t, const double *partial,
                             const BParams &bp, BScalars *sc);
 void launch_b_set_direction(hipStream_t s, const SegTiling &t, const float *dinv32,

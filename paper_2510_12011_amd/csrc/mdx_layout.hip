@@ -111,11 +111,11 @@ struct Bisection {
         run(lo, mid, p, parts / 2);
         run(mid, hi, p + parts / 2, parts - parts / 2);
     }
-    void all(int64_t n, int parts)
+    // parts [p, p + parts) of rows [lo, hi)
+    void all(int64_t lo, int64_t hi, int p, int parts)
     {
-        end.assign(parts, 0);
         struct Range { int64_t lo, hi; int p, parts; };
-        std::vector<Range> level{{0, n, 0, parts}};
+        std::vector<Range> level{{lo, hi, p, parts}};
         for (int d = 0; d < 3; ++d) {   // the first cuts one after another, then in parallel
             std::vector<Range> next(2 * level.size(), Range{0, 0, 0, 0});
             parallel_for((int)level.size(), [&](int k) {
@@ -136,6 +136,12 @@ struct Bisection {
     }
 };
 
+std::mutex &onchip_mutex(int device)
+{
+    static std::mutex m[64];
+    return m[device & 63];
+}
+
 // Builds the blocks' maps and copies them to the device; leaves onchip_ready
 // false where a block's halo exceeds the window.
 mdx_status build_onchip(mdx_ctx *c, hipStream_t st)
@@ -145,14 +151,25 @@ mdx_status build_onchip(mdx_ctx *c, hipStream_t st)
     const OnchipPlan &o = c->onchip;
     if (o.groups == 0) return MDX_OK;
     const int OB = kOnchipThreads, own = o.rows * OB, quads = (o.width + 1) / 4;
-    std::vector<int32_t> rows(c->n);
-    for (int64_t i = 0; i < c->n; ++i) rows[i] = (int32_t)i;
-    Bisection cut{c, rows.data(), {}};
-    cut.all(c->n, o.groups);
+    std::vector<int32_t> rows;   // system after system
+    rows.reserve(c->n);
+    for (int64_t r = 0; r < c->npad; ++r)
+        if (c->perm[r] >= 0) rows.push_back((int32_t)r);
+    Bisection cut{c, rows.data(), std::vector<int64_t>(o.groups, 0)};
+    std::vector<int4> team(o.groups);
+    for (int i = 0; i + 1 < (int)o.first.size(); ++i) {
+        const int p = o.first[i], parts = o.first[i + 1] - p;
+        cut.all(c->inst_node_ptr[i], c->inst_node_ptr[i + 1], p, parts);
+        for (int g = p; g < p + parts; ++g) team[g] = {i, p, parts, 0};
+    }
     const size_t pos = (size_t)o.groups * own;
-    std::vector<int32_t> at(c->n), row(pos, -1);
+    std::vector<int32_t> at(c->npad), row(pos, -1);
     parallel_for(o.groups, [&](int g) {
         const int64_t lo = g ? cut.end[g - 1] : 0;
+        if (o.uneven)   // longest first
+            std::stable_sort(rows.begin() + lo, rows.begin() + cut.end[g], [&](int32_t a, int32_t b) {
+                return (c->rowlen[a] + 3) / 4 > (c->rowlen[b] + 3) / 4;
+            });
         for (int64_t i = lo; i < std::min(cut.end[g], lo + own); ++i) {   // equal parts fit
             at[rows[i]] = (int32_t)((int64_t)g * own + (i - lo));
             row[(size_t)g * own + (i - lo)] = rows[i];
@@ -206,7 +223,13 @@ mdx_status build_onchip(mdx_ctx *c, hipStream_t st)
         }
         hptr[g + 1] = (int32_t)hat.size();
     }
+    std::vector<int32_t> quads4(pos / SLICE, 0);   // even: the products take two at a time
+    for (size_t k = 0; k < pos; ++k)
+        if (row[k] >= 0)
+            quads4[k / SLICE] = std::max(quads4[k / SLICE], (c->rowlen[row[k]] + 7) / 8 * 2);
     const Layout &L = c->L;
+    HIPCHK(hipMemcpyAsync(c->dev<int32_t>(L.oc_quads), quads4.data(), sizeof(int32_t) * quads4.size(),
+                          hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(c->dev<int32_t>(L.oc_row), row.data(), sizeof(int32_t) * row.size(),
                           hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(c->dev<uint16_t>(L.oc_col), col.data(), sizeof(uint16_t) * col.size(),
@@ -220,6 +243,7 @@ mdx_status build_onchip(mdx_ctx *c, hipStream_t st)
     OnchipMap &m = c->onchip_map;
     m.row = c->dev<int32_t>(L.oc_row);
     m.col = c->dev<uint2>(L.oc_col);
+    m.quads = c->dev<int32_t>(L.oc_quads);
     m.halo_ptr = c->dev<int32_t>(L.oc_hptr);
     m.halo_row = c->dev<int32_t>(L.oc_hrow);
     m.halo_at = c->dev<uint32_t>(L.oc_hat);
@@ -231,6 +255,11 @@ mdx_status build_onchip(mdx_ctx *c, hipStream_t st)
     m.d_away = m.r_away + pos;
     launch_onchip_values(st, o, m, c->dev<int64_t>(L.slice_ptr), c->dev<double>(L.Av),
                          c->dev<double>(L.dinv), c->dev<float>(L.A32), c->dev<float>(L.dinv32));
+    if (c->batched) {
+        HIPCHK(hipMemcpyAsync(c->dev<int4>(L.oc_team), team.data(), sizeof(int4) * team.size(),
+                              hipMemcpyHostToDevice, st));
+        launch_fill(st, (c->n_inst + 1) / 2, 0.0, c->dev<double>(L.oc_turn));
+    }
     // no slot holds a value: all bits set
     const uint64_t empty = ~(uint64_t)0;
     double bits;
@@ -307,10 +336,14 @@ void compute_layout(mdx_ctx *c)
         L.oc_hptr = take(sizeof(int32_t) * (g + 1));
         L.oc_hrow = take(sizeof(int32_t) * g * kOnchipHalo);
         L.oc_hat = take(sizeof(int32_t) * g * kOnchipHalo);
-        L.oc_val64 = take(o.shape[0] ? sizeof(double) * (o.width + 1) * pos : 1);
-        L.oc_dinv64 = take(o.shape[0] ? sizeof(double) * pos : 1);
-        L.oc_val32 = take(o.shape[1] ? sizeof(float) * (o.width + 1) * pos : 1);
-        L.oc_dinv32 = take(o.shape[1] ? sizeof(float) * pos : 1);
+        const bool f64 = o.shape[0] || o.shape[2], f32 = o.shape[1] || o.shape[2];
+        L.oc_val64 = take(f64 ? sizeof(double) * (o.width + 1) * pos : 1);
+        L.oc_dinv64 = take(f64 ? sizeof(double) * pos : 1);
+        L.oc_val32 = take(f32 ? sizeof(float) * (o.width + 1) * pos : 1);
+        L.oc_dinv32 = take(f32 ? sizeof(float) * pos : 1);
+        L.oc_team = take(sizeof(int4) * g);
+        L.oc_turn = take(sizeof(int32_t) * (c->n_inst + 1));
+        L.oc_quads = take(sizeof(int32_t) * pos / SLICE);
         L.oc_away = take(o.shape[1] ? 2 * sizeof(float) * pos : 1);
         L.oc_z = take(sizeof(double) * pos);
     }
@@ -874,12 +907,18 @@ mdx_status set_mesh_impl(mdx_ctx *ctx, int32_t n_inst, const int64_t *node_ptr, 
     compact_columns(ctx);
     ctx->batched = batched;
     ctx->onchip = OnchipPlan{};
-    if (!batched && ctx->device >= 0) {
+    if (ctx->device >= 0) {
         int width = 0;
         for (int64_t sl = 0; sl < nslices; ++sl)
             width = std::max(width, (int)((ctx->slice_ptr[sl + 1] - ctx->slice_ptr[sl]) / SLICE));
         HIPCHK(hipSetDevice(ctx->device));
-        ctx->onchip = onchip_plan(ctx->device, n_nodes, width);
+        if (batched) {
+            std::vector<int64_t> nodes(n_inst);
+            for (int32_t i = 0; i < n_inst; ++i) nodes[i] = node_ptr[i + 1] - node_ptr[i];
+            ctx->onchip = onchip_plan_batch(ctx->device, nodes, width);
+        } else {
+            ctx->onchip = onchip_plan(ctx->device, n_nodes, width);
+        }
     }
     ctx->n_inst = n_inst;
     ctx->inst_node_ptr.assign(node_ptr, node_ptr + n_inst + 1);

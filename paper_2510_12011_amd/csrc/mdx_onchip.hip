@@ -102,18 +102,25 @@ struct ExchangeLds {
     int ok;
 };
 
-// Sum v over all threads of all G workgroups; false when the wait gave up.
+// The workgroups that exchange: those of one system, g0 .. g0 + G - 1.
+struct Team {
+    u64 *words;
+    int polls, g, g0, G;
+};
+
+// Sum v over all threads of the team; false when the wait gave up.
 // turn: 0, 1, 2, 0, ... in successive exchanges.  during() runs once the
 // workgroup's sums are on their way: loads issued there are hidden by the wait
 // (issued before it they would hold up the sums: the store count that orders
 // them counts loads too).
 template <int NV, class F>
-__device__ __forceinline__ bool exchange(double (&v)[NV], ExchangeLds &l, const OnchipSolve &a,
-                                         int g, int G, int &turn, F &&during)
+__device__ __forceinline__ bool exchange(double (&v)[NV], ExchangeLds &l, const Team &team,
+                                         int &turn, F &&during)
 {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     constexpr size_t TURN = NXCD * 2 * kOnchipGroups;   // slots of a turn: [XCD][value][workgroup]
-    u64 *const words = a.words;
+    u64 *const words = team.words;
+    const int g = team.g, G = team.G;
     u64 *buf = words + turn * TURN;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
@@ -139,7 +146,7 @@ __device__ __forceinline__ bool exchange(double (&v)[NV], ExchangeLds &l, const 
     }
     during();
     if (w == 0) {
-        buf += blockIdx.x % NXCD * (2 * kOnchipGroups);
+        buf += blockIdx.x % NXCD * (2 * kOnchipGroups) + team.g0;
         constexpr int C = kOnchipGroups / SLICE;
         double acc[NV];
         int n = 0;
@@ -166,7 +173,7 @@ __device__ __forceinline__ bool exchange(double (&v)[NV], ExchangeLds &l, const 
                         acc[k] += __longlong_as_double((long long)s[c][k]);
                     }
             all = __all(all);
-        } while (!all && ++n < a.polls);
+        } while (!all && ++n < team.polls);
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
             const double t = wave_total63(acc[k]);
@@ -214,6 +221,24 @@ struct Partials {
             for (int k = 0; k < 3; ++k) v[k] += t[j][k];
     }
 };
+// sums over the workgroup, in every thread
+__device__ __forceinline__ void block_totals(double (&v)[3], ExchangeLds &l)
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double t = wave_total63(v[k]);
+        if (lane == 63) l.part[k][w] = t;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        v[k] = l.part[k][0];
+#pragma unroll
+        for (int i = 1; i < OW; ++i) v[k] += l.part[k][i];
+    }
+    __syncthreads();
+}
 __device__ __forceinline__ Start start_of(const OnchipSolve &a, Partials &q, ExchangeLds &l)
 {
     Start s;
@@ -227,21 +252,8 @@ __device__ __forceinline__ Start start_of(const OnchipSolve &a, Partials &q, Exc
         s.done = sc->done != 0;
         return s;
     }
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    double v[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const double t = wave_total63(q.v[k]);
-        if (lane == 63) l.part[k][w] = t;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        v[k] = l.part[k][0];
-#pragma unroll
-        for (int i = 1; i < OW; ++i) v[k] += l.part[k][i];
-    }
-    __syncthreads();
+    double (&v)[3] = q.v;
+    block_totals(v, l);
     s.rho = v[0];
     s.z0 = sqrt(v[1]);
     const double db = sqrt(v[2]);
@@ -287,9 +299,9 @@ template <int W, int R, int LQ>
 struct Rows {
     static constexpr int Q = (W + 3) / 4, NR = Q - LQ;
     uint2 reg[NR > 0 ? R : 1][NR > 0 ? NR : 1];
-    __device__ __forceinline__ void load(const OnchipSolve &a, int g, uint2 (*lds)[OB])
+    __device__ __forceinline__ void load(const uint2 *col, int g, uint2 (*lds)[OB])
     {
-        const uint2 *c = a.map.col + (size_t)g * R * Q * OB + threadIdx.x;
+        const uint2 *c = col + (size_t)g * R * Q * OB + threadIdx.x;
 #pragma unroll
         for (int i = 0; i < R; ++i) {
 #pragma unroll
@@ -336,6 +348,79 @@ struct Rows {
         }
         return s;
     }
+    // sum_j val_j x[col_j] over the wavefront's first nq quads (even; all for
+    // even rows), as L lanes of the streaming product add them: entry j to the
+    // (j mod L)-th of L sums in FP32, then the sums by a butterfly
+    template <int L, bool UNEVEN>
+    __device__ __forceinline__ float product_l(const float (&val)[R][W], const uint2 (*lds)[OB], int i,
+                                               int t, const float *x, int nq) const
+    {
+        constexpr int STEP = UNEVEN ? 2 : Q;   // quads whose gathers go out together
+        float s[L];
+#pragma unroll
+        for (int u = 0; u < L; ++u) s[u] = 0.0f;
+#pragma unroll
+        for (int q0 = 0; q0 < Q; q0 += STEP)
+            if (!UNEVEN || q0 < nq) {
+                float xx[4 * STEP];
+#pragma unroll
+                for (int q = q0; q < q0 + STEP && q < Q; ++q) {
+                    const uint2 c = get(lds, i, q, t);
+                    xx[4 * (q - q0)] = x[c.x & 0xffffu];
+                    xx[4 * (q - q0) + 1] = x[c.x >> 16];
+                    xx[4 * (q - q0) + 2] = x[c.y & 0xffffu];
+                    if (4 * q + 3 < W) xx[4 * (q - q0) + 3] = x[c.y >> 16];
+                }
+#pragma unroll
+                for (int j = 4 * q0; j < 4 * (q0 + STEP) && j < W; ++j)
+                    s[j % L] = __builtin_fmaf(val[i][j], xx[j - 4 * q0], s[j % L]);
+            }
+#pragma unroll
+        for (int off = L / 2; off > 0; off /= 2)
+#pragma unroll
+            for (int u = 0; u < off; ++u) s[u] += s[u + off];
+        return s[0];
+    }
+    template <bool UNEVEN>
+    __device__ __forceinline__ float product_as(int lanes, const float (&val)[R][W],
+                                                const uint2 (*lds)[OB], int i, int t, const float *x,
+                                                int nq) const
+    {
+        switch (lanes) {
+        case 2: return product_l<2, UNEVEN>(val, lds, i, t, x, nq);
+        case 4: return product_l<4, UNEVEN>(val, lds, i, t, x, nq);
+        case 8: return product_l<8, UNEVEN>(val, lds, i, t, x, nq);
+        case 16: return product_l<16, UNEVEN>(val, lds, i, t, x, nq);
+        default: return product_l<1, UNEVEN>(val, lds, i, t, x, nq);
+        }
+    }
+    // the same with FP64 values read here, in pairs (A: the thread's first)
+    __device__ __forceinline__ double streamed(const double2 *A, const uint2 (*lds)[OB], int i, int t,
+                                               const float *x, int nq) const
+    {
+        constexpr int P = (W + 1) / 2;
+        double2 v[P];
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (q < nq) {
+                v[2 * q] = A[(i * P + 2 * q) * OB];
+                v[2 * q + 1] = A[(i * P + 2 * q + 1) * OB];
+            }
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (q < nq) {
+                const uint2 c = get(lds, i, q, t);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (4 * q + j < W) {
+                        const unsigned h = j < 2 ? c.x : c.y;
+                        const double a = j & 1 ? v[2 * q + j / 2].y : v[2 * q + j / 2].x;
+                        s += a * (double)x[j & 1 ? h >> 16 : h & 0xffffu];
+                    }
+            }
+        return s;
+    }
 };
 
 // Has row i's product formed here: the compiler would put the sums off and
@@ -375,6 +460,24 @@ __device__ __forceinline__ void load_values(const float *__restrict__ A, float (
         }
 }
 
+// the first nq quads of pass i of the thread's rows
+template <int W, int R>
+__device__ __forceinline__ void load_values_n(const float *__restrict__ A, float (&val)[R][W], int i,
+                                              int nq)
+{
+    constexpr int P = (W + 3) / 4;
+    const float4 *p = reinterpret_cast<const float4 *>(A) + threadIdx.x;
+#pragma unroll
+    for (int j = 0; j < P; ++j)
+        if (j < nq) {
+            const float4 v = p[(i * P + j) * OB];
+            val[i][4 * j] = v.x;
+            val[i][4 * j + 1] = v.y;
+            val[i][4 * j + 2] = v.z;
+            if (4 * j + 3 < W) val[i][4 * j + 3] = v.w;
+        }
+}
+
 // Halo of the window, filled by all wavefronts but the first (which polls):
 // fetch() reads the entries' places (during an exchange, whose wait hides it),
 // fill() the entries themselves after it.  Lists are padded to whole passes.
@@ -392,18 +495,23 @@ struct Halo {
     template <class T>
     __device__ __forceinline__ void fill(const T *zb, T *win, int passes) const
     {
-        if (threadIdx.x >= SLICE) {
-            const unsigned h = threadIdx.x - SLICE;
-            T v[HR];
-#pragma unroll
-            for (int k = 0; k < HR; ++k)
-                if (k < passes)
-                    v[k] = ld_agent(reinterpret_cast<const T *>(reinterpret_cast<const char *>(zb) + at[k]));
-#pragma unroll
-            for (int k = 0; k < HR; ++k)
-                if (k < passes) win[k * HT + h] = v[k];
-        }
+        combine(zb, win, passes, [](T z, T, int) { return z; });
         __syncthreads();
+    }
+    // win = f(entry, win, pass), without the barrier
+    template <class T, class F>
+    __device__ __forceinline__ void combine(const T *zb, T *win, int passes, F &&f) const
+    {
+        if (threadIdx.x < SLICE) return;
+        const unsigned h = threadIdx.x - SLICE;
+        T v[HR];
+#pragma unroll
+        for (int k = 0; k < HR; ++k)
+            if (k < passes)
+                v[k] = ld_agent(reinterpret_cast<const T *>(reinterpret_cast<const char *>(zb) + at[k]));
+#pragma unroll
+        for (int k = 0; k < HR; ++k)
+            if (k < passes) win[k * HT + h] = f(v[k], win[k * HT + h], k);
     }
 };
 
@@ -417,6 +525,7 @@ __global__ __launch_bounds__(OB) void k_onchip(OnchipSolve a)
     __shared__ double win[own + kOnchipHalo];
     __shared__ double ldv[R][OB];
     const int G = gridDim.x, g = logical_group(G);
+    const Team team = {a.words, a.polls, g, 0, G};
     int t = threadIdx.x;
     unsigned at0 = (unsigned)g * own + t;   // block position of pass i: at0 + i * OB
     double *zb = static_cast<double *>(a.zb);
@@ -425,7 +534,7 @@ __global__ __launch_bounds__(OB) void k_onchip(OnchipSolve a)
     const int h0 = a.map.halo_ptr[g], nh = (a.map.halo_ptr[g + 1] - h0) / HT;   // its passes
     double val[R][W], r[R], p[R], q[R], x[R];
     Rows<W, R, LQ> rows;
-    rows.load(a, g, lcol);
+    rows.load(a.map.col, g, lcol);
     asm volatile("" ::: "memory");   // the columns' registers are free again
     load_values<W, R>(a.map.val64 + (size_t)g * own * (W + 1), val);
 #pragma unroll
@@ -463,7 +572,7 @@ __global__ __launch_bounds__(OB) void k_onchip(OnchipSolve a)
             p[i] = win[i * OB + t] + beta * p[i];
             pq[0] += p[i] * q[i];
         }
-        if (!exchange<1>(pq, xl, a, g, G, turn, nothing)) {
+        if (!exchange<1>(pq, xl, team, turn, nothing)) {
             o.aborted = 1;
             break;
         }
@@ -480,7 +589,7 @@ __global__ __launch_bounds__(OB) void k_onchip(OnchipSolve a)
             v[1] += z * z;
         }
         Halo halo;
-        if (!exchange<2>(v, xl, a, g, G, turn, [&] { halo.fetch<double>(a.map.halo_at + h0, nh); })) {
+        if (!exchange<2>(v, xl, team, turn, [&] { halo.fetch<double>(a.map.halo_at + h0, nh); })) {
             o.aborted = 1;
             break;
         }
@@ -526,6 +635,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
     __shared__ float win[own + kOnchipHalo];
     __shared__ float ldv[AWAY ? 1 : R][OB];
     const int G = gridDim.x, g = logical_group(G);
+    const Team team = {a.words, a.polls, g, 0, G};
     int t = threadIdx.x;
     unsigned at0 = (unsigned)g * own + t;
     float *zb = static_cast<float *>(a.zb);
@@ -536,7 +646,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
     const int h0 = a.map.halo_ptr[g], nh = (a.map.halo_ptr[g + 1] - h0) / HT;   // its passes
     float val[R][W], p[R], q[R], r[R], d[R];
     Rows<W, R, LQ> rows;
-    rows.load(a, g, lcol);
+    rows.load(a.map.col, g, lcol);
     asm volatile("" ::: "memory");   // the columns' registers are free again
     if constexpr (!AWAY) load_values<W, R>(a.map.val32 + (size_t)g * own * (W + 1), val);
 #pragma unroll
@@ -583,7 +693,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
             p[i] = win[i * OB + t] + bf * p[i];
             pq[0] += (double)p[i] * (double)q[i];
         }
-        if (!exchange<1>(pq, xl, a, g, G, turn, nothing)) {
+        if (!exchange<1>(pq, xl, team, turn, nothing)) {
             o.aborted = 1;
             break;
         }
@@ -611,7 +721,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
             v[1] += (double)z * (double)z;
         }
         Halo halo;
-        if (!exchange<2>(v, xl, a, g, G, turn, [&] { halo.fetch<float>(a.map.halo_at + h0, nh); })) {
+        if (!exchange<2>(v, xl, team, turn, [&] { halo.fetch<float>(a.map.halo_at + h0, nh); })) {
             o.aborted = 1;
             break;
         }
@@ -639,7 +749,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
             st_agent(zb + at0 + i * OB, di);
         }
         double none[1] = {0.0};
-        if (!exchange<1>(none, xl, a, g, G, turn, nothing)) {
+        if (!exchange<1>(none, xl, team, turn, nothing)) {
             o.aborted = 1;
             break;
         }
@@ -668,7 +778,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
                 d[i] = 0.0f;
             }
         }
-        if (!exchange<2>(v, xl, a, g, G, turn, nothing)) {
+        if (!exchange<2>(v, xl, team, turn, nothing)) {
             o.aborted = 1;
             break;
         }
@@ -695,7 +805,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
             win[i * OB + t] = z;
             st_agent(zb + at0 + i * OB, z);
         }
-        if (!exchange<1>(none, xl, a, g, G, turn, nothing)) {
+        if (!exchange<1>(none, xl, team, turn, nothing)) {
             o.aborted = 1;
             break;
         }
@@ -704,6 +814,229 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
     o.it = it;
     o.rho = rho;
     report(a, st, o, turn);
+}
+
+// ---- batched: independent systems, FP32 iteration, FP64 replacement ----------
+// The recurrences of mdx_batch.hip, every instance by a team of workgroups of
+// its own that leaves when the instance is done.  The window holds the search
+// direction: a workgroup forms its own rows' p = D^-1 r + beta p and, from the r
+// that their owners wrote, its halo's, with the same operations and so the
+// same bits, and q = A p needs no recurrence.  A row's FP32 sum is added up as
+// the installed streaming layout does (lanes per row), so iterates and counts
+// are the streaming kernels' but for the order of the FP64 sums (an instance
+// alone and in a batch agree to that order too, bitwise where both take the
+// same rows a thread).  The replacement updates the FP64 residual by the
+// correction (r64 -= A delta, FP64 values of A streamed by block), which is
+// b - A (x + delta) up to the rounding of x.
+//
+// Solve of a step, streaming kernels -> this (and the whole step): 12
+// unstructured shells of 232,472 nodes in all, 4.0 iterations, 130 -> 46 us
+// (187 -> 111); 8 surfaces of 1,310,736, 1.8 iterations, 165 -> 79 (280 -> 211).
+// Bound by one read of the values and columns (23 and 45 MB), the replacement's
+// read of the FP64 values and some 3 us per exchange.
+//
+// UNEVEN: unstructured meshes, whose rows' lengths spread (12 to 33 entries,
+// 16 on average): a block's rows are sorted by length and a wavefront forms
+// the quads that its longest row has.
+template <int W, int R, bool UNEVEN>
+__global__ __launch_bounds__(OB) void k_onchip_batch(OnchipBatch a)
+{
+    constexpr int LQ = (W + 3) / 4, own = R * OB;
+    __shared__ ExchangeLds xl;
+    __shared__ uint2 lcol[R * LQ][OB];
+    __shared__ float win[own + kOnchipHalo];
+    __shared__ float ldv[R][OB];
+    const int g = logical_group(gridDim.x);
+    const int4 gr = a.grp[g];
+    const Team team = {a.words, a.polls, g, gr.y, gr.z};
+    int t = threadIdx.x;
+    unsigned at0 = (unsigned)g * own + t;
+    // the instance's partials, summed by each of its workgroups in one order
+    Start st;
+    {
+        double v[3] = {0.0, 0.0, 0.0};
+        const int i1 = a.inst_grp[gr.x + 1];
+        for (int i = a.inst_grp[gr.x] + t; i < i1; i += OB)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) v[k] += a.part[k * a.part_groups + i];
+        block_totals(v, xl);
+        st.rho = v[0];
+        st.z0 = sqrt(v[1]);
+        const double db = sqrt(v[2]);
+        st.ref = a.bp.rel_mode == 1 ? db : st.z0;
+        st.floor_ = 1e-15 * db;
+        st.finite = isfinite(st.z0) && isfinite(db) && isfinite(v[0]);
+        st.done = !st.finite || st.z0 <= st.floor_ || st.z0 < a.bp.atol;
+    }
+    BScalars &s = a.sc[gr.x];
+    const bool lead = g == gr.y && t == 0;
+    if (lead) {
+        s.alpha = s.beta = 0.0;
+        s.ref = st.ref;
+        s.floor_ = st.floor_;
+        s.z0 = st.z0;
+        s.replace = s.redirect = 0;
+    }
+    if (st.done) {
+        if (lead) {
+            s.rho = st.rho;
+            s.znorm = st.z0;
+            s.it = s.iters = s.failed = 0;
+            s.nonfinite = st.finite ? 0 : 1;
+            s.done = 1;
+        }
+        return;
+    }
+    const int h0 = a.map.halo_ptr[g], nh = (a.map.halo_ptr[g + 1] - h0) / HT;   // its passes
+    float val[R][W], q[R], r[R], d[R];
+    Rows<W, R, LQ> rows;
+    rows.load(a.map.col, g, lcol);
+    asm volatile("" ::: "memory");   // the columns' registers are free again
+    int nq[R];   // quads of the wavefront's rows
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+        nq[i] = UNEVEN ? __builtin_amdgcn_readfirstlane(a.map.quads[(g * R + i) * OW + (t >> 6)]) : LQ;
+    if constexpr (UNEVEN) {
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+            load_values_n<W, R>(a.map.val32 + (size_t)g * own * (W + 1), val, i, nq[i]);
+    } else {
+        load_values<W, R>(a.map.val32 + (size_t)g * own * (W + 1), val);
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int row = a.map.row[at0 + i * OB];
+        const float ri = a.r32[max(row, 0)], dv = a.map.dinv32[at0 + i * OB];   // 0 past the last row
+        r[i] = row < 0 ? 0.0f : ri;
+        d[i] = 0.0f;
+        ldv[i][t] = dv;
+        win[i * OB + t] = dv * r[i];
+    }
+    float hdv[HR];   // D^-1 of the thread's halo entries
+    if (t >= SLICE)
+#pragma unroll
+        for (int k = 0; k < HR; ++k)
+            if (k < nh) {
+                const int h = k * HT + t - SLICE, row = a.map.halo_row[h0 + h];
+                hdv[k] = a.dinv32[row];
+                win[own + h] = hdv[k] * a.r32[row];
+            }
+    int turn = a.turn[gr.x];
+    __syncthreads();
+    const StopTest test = {a.bp.atol, a.bp.rtol, st.ref, st.floor_};
+    double rho = st.rho, znorm = st.z0;
+    int it = 0;
+    bool gave_up = false, nonfinite = false, failed = false;
+    for (;;) {
+        asm volatile("" : "+v"(at0), "+v"(t));   // as in k_onchip
+        double pq[1] = {0.0};
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            q[i] = rows.template product_as<UNEVEN>(a.lanes, val, lcol, i, t, win, nq[i]);
+            formed(q[i]);
+            pq[0] += (double)win[i * OB + t] * (double)q[i];
+        }
+        gave_up = !exchange<1>(pq, xl, team, turn, nothing);
+        if (gave_up) break;
+        const float alpha = (float)(rho / pq[0]);
+        double v[2] = {0.0, 0.0};
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            d[i] += alpha * win[i * OB + t];
+            r[i] -= alpha * q[i];
+            const float z = ldv[i][t] * r[i];
+            st_agent(a.zb + at0 + i * OB, r[i]);
+            v[0] += (double)r[i] * (double)z;
+            v[1] += (double)z * (double)z;
+        }
+        Halo halo;
+        gave_up = !exchange<2>(v, xl, team, turn, [&] { halo.fetch<float>(a.map.halo_at + h0, nh); });
+        if (gave_up) break;
+        ++it;
+        znorm = sqrt(v[1]);
+        nonfinite = !isfinite(znorm) || !isfinite(v[0]);
+        if (nonfinite) break;
+        const bool pass = passes(test, znorm);
+        if (!pass && !(a.bp.rr > 0 && it % a.bp.rr == 0) && it < a.bp.max_iter) {
+            const float bf = (float)(v[0] / rho);
+            rho = v[0];
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+                win[i * OB + t] = __builtin_fmaf(ldv[i][t], r[i], bf * win[i * OB + t]);
+            halo.combine(a.zb, win + own, nh, [&](float rh, float p, int k) {
+                return __builtin_fmaf(hdv[k], rh, bf * p);
+            });
+            __syncthreads();
+            continue;
+        }
+        // ---- replacement: r64 -= A delta, x64 += delta, the test on r64 ----
+        float p[R];
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            p[i] = win[i * OB + t];
+            win[i * OB + t] = d[i];
+            st_agent(a.zb + at0 + i * OB, d[i]);
+        }
+        double none[1] = {0.0};
+        gave_up = !exchange<1>(none, xl, team, turn, nothing);
+        if (gave_up) break;
+        halo.fill(a.zb, win + own, nh);
+        v[0] = v[1] = 0.0;
+        const double2 *A = reinterpret_cast<const double2 *>(a.map.val64) + (size_t)g * (own * (W + 1) / 2) + t;
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const int row = a.map.row[at0 + i * OB];
+            double ad = rows.streamed(A, lcol, i, t, win, nq[i]);
+            formed(ad);
+            float ri = 0.0f;
+            if (row >= 0) {
+                const double r64 = a.r[row] - ad;
+                a.r[row] = r64;
+                a.x[row] += (double)d[i];
+                ri = (float)r64;
+                const double zi = a.dinv[row] * r64;
+                v[1] += zi * zi;
+            }
+            r[i] = ri;
+            d[i] = 0.0f;
+            v[0] += (double)ri * (double)(ldv[i][t] * ri);
+        }
+        gave_up = !exchange<2>(v, xl, team, turn, nothing);
+        if (gave_up) break;
+        znorm = sqrt(v[1]);
+        nonfinite = !isfinite(znorm) || !isfinite(v[0]);
+        if (nonfinite || passes(test, znorm)) break;
+        if (it >= a.bp.max_iter) {
+            failed = true;
+            break;
+        }
+        // restart (p = z) where the recursive residual had passed, the
+        // recurrence kept after a periodic replacement
+        const float bf = (float)(pass ? 0.0 : v[0] / rho);
+        rho = v[0];
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const float pi = __builtin_fmaf(ldv[i][t], r[i], bf * p[i]);
+            win[i * OB + t] = pi;
+            st_agent(a.zb + at0 + i * OB, pi);
+        }
+        gave_up = !exchange<1>(none, xl, team, turn, nothing);
+        if (gave_up) break;
+        halo.fill(a.zb, win + own, nh);
+    }
+    if (gave_up) {
+        if (t == 0) st_agent(&s.gave_up, 1);
+        return;
+    }
+    if (lead) {
+        s.rho = rho;
+        s.znorm = znorm;
+        s.it = s.iters = it;
+        s.nonfinite = nonfinite ? 1 : 0;
+        s.failed = failed ? 1 : 0;
+        s.done = 1;
+        a.turn[gr.x] = turn;
+    }
 }
 
 // values and diagonals of the blocks' rows from the sliced layout
@@ -737,6 +1070,10 @@ struct OnchipShape {
     int width, rows;   // entries of a row, rows per thread
     void (*k)(OnchipSolve);
 };
+struct OnchipBatchShape {
+    int width, rows;
+    void (*k)(OnchipBatch);
+};
 #define MDX_OC(w, r) {w, r, k_onchip<w, r>}
 const OnchipShape kShapes64[] = {
     MDX_OC(7, 1),  MDX_OC(7, 2),  MDX_OC(7, 3),  MDX_OC(7, 4),  MDX_OC(7, 6),  MDX_OC(15, 1),
@@ -751,12 +1088,19 @@ const OnchipShape kShapes32[] = {
     {15, 10, k_onchip32<15, 10, 3, true>}, MDX_OC(31, 1), MDX_OC(31, 2), MDX_OC(31, 3), MDX_OC(31, 4),
 };
 #undef MDX_OC
-constexpr int kRows[] = {1, 2, 3, 4, 6, 7, 8, 10, 12};
+#define MDX_OCB(w, r) {w, r, k_onchip_batch<w, r, (w > 15)>}
+const OnchipBatchShape kShapesB[] = {
+    MDX_OCB(7, 1),  MDX_OCB(7, 2),  MDX_OCB(7, 3),  MDX_OCB(7, 4),  MDX_OCB(7, 6),  MDX_OCB(7, 7),
+    MDX_OCB(7, 8),  MDX_OCB(7, 10), MDX_OCB(7, 11), MDX_OCB(7, 12), MDX_OCB(15, 1), MDX_OCB(15, 2), MDX_OCB(15, 3),
+    MDX_OCB(15, 4), MDX_OCB(15, 6), MDX_OCB(15, 7), MDX_OCB(39, 1), MDX_OCB(39, 2), MDX_OCB(39, 3),
+};
+#undef MDX_OCB
+constexpr int kRows[] = {1, 2, 3, 4, 6, 7, 8, 10, 11, 12};
 
-template <int N>
-const OnchipShape *pick(const OnchipShape (&s)[N], int width, int rows)
+template <class S, int N>
+const S *pick(const S (&s)[N], int width, int rows)
 {
-    for (const OnchipShape &c : s)
+    for (const S &c : s)
         if (width == c.width && rows == c.rows) return &c;
     return nullptr;
 }
@@ -775,7 +1119,7 @@ OnchipPlan onchip_plan(int device, int64_t n, int width)
     if (width > 31) return p;
     const int64_t need = (n + cap * OB - 1) / (cap * OB);
     for (int r : kRows)
-        if (r >= need) {
+        if (r >= need && (pick(kShapes64, p.width, r) || pick(kShapes32, p.width, r))) {
             p.rows = r;
             break;
         }
@@ -788,6 +1132,39 @@ OnchipPlan onchip_plan(int device, int64_t n, int width)
             p.shape[i] = s[i];
     }
     if (p.shape[0] || p.shape[1]) p.groups = (int)std::min(cap, (n + OB - 1) / OB);
+    p.first = {0, p.groups};
+    return p;
+}
+
+OnchipPlan onchip_plan_batch(int device, const std::vector<int64_t> &n, int width)
+{
+    OnchipPlan p;
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
+        return p;
+    const int64_t cap = std::min(cus, kOnchipGroups);
+    p.width = width <= 7 ? 7 : width <= 15 ? 15 : 39;
+    if (width > 39 || (int64_t)n.size() > cap) return p;
+    p.uneven = p.width == 39;
+    // the fewest rows a thread with which every instance has workgroups enough
+    for (int r : kRows) {
+        int64_t need = 0;
+        for (int64_t k : n) need += (k + r * OB - 1) / (r * OB);
+        if (need > cap) continue;
+        const OnchipBatchShape *s = pick(kShapesB, p.width, r);
+        int resident = 0;
+        if (!s || hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, s->k, OB, 0) != hipSuccess ||
+            resident < 1)
+            return p;
+        p.rows = r;
+        p.shape[2] = s;
+        for (int64_t k : n) {
+            p.first.push_back(p.groups);
+            p.groups += (int)((k + r * OB - 1) / (r * OB));
+        }
+        p.first.push_back(p.groups);
+        return p;
+    }
     return p;
 }
 
@@ -797,10 +1174,10 @@ void launch_onchip_values(hipStream_t s, const OnchipPlan &p, const OnchipMap &m
 {
     const int64_t n = (int64_t)p.groups * p.rows * OB;
     const dim3 grid((unsigned)((n + 255) / 256)), block(256);
-    if (p.shape[0])
+    if (p.shape[0] || p.shape[2])
         hipLaunchKernelGGL((k_onchip_values<double, double>), grid, block, 0, s, n, p.rows, p.width, m,
                            slice_ptr, A, dinv, m.val64, m.dinv64);
-    if (p.shape[1])
+    if (p.shape[1] || p.shape[2])
         hipLaunchKernelGGL((k_onchip_values<float, float>), grid, block, 0, s, n, p.rows, p.width, m,
                            slice_ptr, A32, dinv32, m.val32, m.dinv32);
 }
@@ -808,6 +1185,12 @@ void launch_onchip_values(hipStream_t s, const OnchipPlan &p, const OnchipMap &m
 void launch_onchip(hipStream_t s, const OnchipPlan &p, bool fp32, const OnchipSolve &a)
 {
     const OnchipShape *sh = static_cast<const OnchipShape *>(p.shape[fp32 ? 1 : 0]);
+    hipLaunchKernelGGL(sh->k, dim3(p.groups), dim3(OB), 0, s, a);
+}
+
+void launch_onchip_batch(hipStream_t s, const OnchipPlan &p, const OnchipBatch &a)
+{
+    const OnchipBatchShape *sh = static_cast<const OnchipBatchShape *>(p.shape[2]);
     hipLaunchKernelGGL(sh->k, dim3(p.groups), dim3(OB), 0, s, a);
 }
 

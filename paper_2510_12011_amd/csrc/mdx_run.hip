@@ -12,18 +12,6 @@
 
 #include <mutex>
 
-namespace {
-
-// One single-launch solve per device at a time: two whose workgroups share the
-// CUs would each wait for workgroups that the other keeps off the chip.
-std::mutex &onchip_mutex(int device)
-{
-    static std::mutex m[64];
-    return m[device & 63];
-}
-
-}  // namespace
-
 extern "C" {
 
 mdx_status mdx_run(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double *v_out)
