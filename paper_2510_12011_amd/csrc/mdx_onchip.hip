@@ -394,6 +394,27 @@ struct Rows {
         default: return product_l<1, UNEVEN>(val, lds, i, t, x, nq);
         }
     }
+    // FP64 sum with the FP32 values read here again (A: the thread's first)
+    __device__ __forceinline__ double reread(const float4 *A, const uint2 (*lds)[OB], int i, int t,
+                                             const float *x) const
+    {
+        float4 v[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) v[q] = A[(i * Q + q) * OB];
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const uint2 c = get(lds, i, q, t);
+            const float a[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (4 * q + j < W) {
+                    const unsigned h = j < 2 ? c.x : c.y;
+                    s += (double)a[j] * (double)x[j & 1 ? h >> 16 : h & 0xffffu];
+                }
+        }
+        return s;
+    }
     // the same with FP64 values read here, in pairs (A: the thread's first)
     __device__ __forceinline__ double streamed(const double2 *A, const uint2 (*lds)[OB], int i, int t,
                                                const float *x, int nq) const
@@ -664,12 +685,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
         }
     }
     for (int h = t; h < nh * HT; h += OB) win[own + h] = a.z32[a.map.halo_row[h0 + h]];
-    if constexpr (AWAY) {
-        asm volatile("" ::: "memory");
-        load_values<W, R>(a.map.val32 + (size_t)g * own * (W + 1), val);
-    } else {
-        st = start_of(a, parts, xl);
-    }
+    if constexpr (!AWAY) st = start_of(a, parts, xl);
     Outcome o{st.rho, st.z0, 0, 1, st.finite ? 0 : 2, 0};
     int turn = a.turn;
     if (st.done) {
@@ -682,64 +698,76 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
     int it = 0;
     o.done = 0;
     for (;;) {
-        asm volatile("" : "+v"(at0), "+v"(t));   // as in k_onchip
-        const float bf = (float)beta;
-        double pq[1] = {0.0};
-        float dv[R];
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            q[i] = rows.template product<float>(val, lcol, i, t, win) + bf * q[i];
-            formed(q[i]);
-            p[i] = win[i * OB + t] + bf * p[i];
-            pq[0] += (double)p[i] * (double)q[i];
-        }
-        if (!exchange<1>(pq, xl, team, turn, nothing)) {
-            o.aborted = 1;
-            break;
-        }
-        const float alpha = (float)(rho / pq[0]);
-        double v[2] = {0.0, 0.0};
-#pragma unroll
-        for (int i = 0; i < R; ++i)
-            if constexpr (AWAY) {
-                dv[i] = a.map.dinv32[at0 + i * OB];
-                r[i] = a.map.r_away[at0 + i * OB];
-                d[i] = a.map.d_away[at0 + i * OB];
-            }
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            d[i] += alpha * p[i];
-            r[i] -= alpha * q[i];
-            if constexpr (AWAY) {
-                a.map.d_away[at0 + i * OB] = d[i];
-                a.map.r_away[at0 + i * OB] = r[i];
-            }
-            const float z = (AWAY ? dv[i] : ldv[AWAY ? 0 : i][t]) * r[i];
-            win[i * OB + t] = z;
-            st_agent(zb + at0 + i * OB, z);
-            v[0] += (double)r[i] * (double)z;
-            v[1] += (double)z * (double)z;
+        // AWAY: the values are read for each run of iterations and again, row
+        // by row, for its replacement: held through it they would be spilled
+        if constexpr (AWAY) {
+            asm volatile("" ::: "memory");
+            load_values<W, R>(a.map.val32 + (size_t)g * own * (W + 1), val);
         }
         Halo halo;
-        if (!exchange<2>(v, xl, team, turn, [&] { halo.fetch<float>(a.map.halo_at + h0, nh); })) {
-            o.aborted = 1;
-            break;
-        }
-        ++it;
-        double zn = sqrt(v[1]);
-        o.znorm = zn;
-        if (!isfinite(zn)) {
-            o.nonfinite = 2;
-            o.done = 1;
-            break;
-        }
-        const bool pass = passes(test, zn);
-        if (!pass && !(a.rr > 0 && it % a.rr == 0) && it < a.max_iter) {
+        double v[2], zn;
+        bool pass, out = false;
+        for (;;) {
+            asm volatile("" : "+v"(at0), "+v"(t));   // as in k_onchip
+            const float bf = (float)beta;
+            double pq[1] = {0.0};
+            float dv[R];
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                q[i] = rows.template product<float>(val, lcol, i, t, win) + bf * q[i];
+                formed(q[i]);
+                p[i] = win[i * OB + t] + bf * p[i];
+                pq[0] += (double)p[i] * (double)q[i];
+            }
+            if (!exchange<1>(pq, xl, team, turn, nothing)) {
+                o.aborted = 1;
+                out = true;
+                break;
+            }
+            const float alpha = (float)(rho / pq[0]);
+            v[0] = v[1] = 0.0;
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+                if constexpr (AWAY) {
+                    dv[i] = a.map.dinv32[at0 + i * OB];
+                    r[i] = a.map.r_away[at0 + i * OB];
+                    d[i] = a.map.d_away[at0 + i * OB];
+                }
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                d[i] += alpha * p[i];
+                r[i] -= alpha * q[i];
+                if constexpr (AWAY) {
+                    a.map.d_away[at0 + i * OB] = d[i];
+                    a.map.r_away[at0 + i * OB] = r[i];
+                }
+                const float z = (AWAY ? dv[i] : ldv[AWAY ? 0 : i][t]) * r[i];
+                win[i * OB + t] = z;
+                st_agent(zb + at0 + i * OB, z);
+                v[0] += (double)r[i] * (double)z;
+                v[1] += (double)z * (double)z;
+            }
+            if (!exchange<2>(v, xl, team, turn, [&] { halo.fetch<float>(a.map.halo_at + h0, nh); })) {
+                o.aborted = 1;
+                out = true;
+                break;
+            }
+            ++it;
+            zn = sqrt(v[1]);
+            o.znorm = zn;
+            if (!isfinite(zn)) {
+                o.nonfinite = 2;
+                o.done = 1;
+                out = true;
+                break;
+            }
+            pass = passes(test, zn);
+            if (pass || (a.rr > 0 && it % a.rr == 0) || it >= a.max_iter) break;
             beta = v[0] / rho;
             rho = v[0];
             halo.fill(zb, win + own, nh);
-            continue;
         }
+        if (out) break;
         // ---- replacement: r64 -= A delta, x64 += delta, the test on r64 ----
         // (zb is overwritten: no workgroup reads z from it at this exchange)
 #pragma unroll
@@ -748,25 +776,50 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
             win[i * OB + t] = di;
             st_agent(zb + at0 + i * OB, di);
         }
+        // AWAY: with the values gone there is room to read ahead
+        constexpr int RA = AWAY ? R : 1;
+        int rw[RA];
+        double r0[RA], x0[RA], d0[RA];
         double none[1] = {0.0};
-        if (!exchange<1>(none, xl, team, turn, nothing)) {
+        const bool there = exchange<1>(none, xl, team, turn, [&] {
+            if constexpr (AWAY) {
+#pragma unroll
+                for (int i = 0; i < R; ++i) rw[i] = a.map.row[at0 + i * OB];
+#pragma unroll
+                for (int i = 0; i < R; ++i) {
+                    const int at = max(rw[i], 0);
+                    r0[i] = a.r[at];
+                    x0[i] = a.x[at];
+                    d0[i] = a.dinv[at];
+                }
+            }
+        });
+        if (!there) {
             o.aborted = 1;
             break;
         }
         halo.fill(zb, win + own, nh);
         v[0] = v[1] = 0.0;
+        const float4 *A = reinterpret_cast<const float4 *>(a.map.val32) + (size_t)g * (own * (W + 1) / 4) + t;
 #pragma unroll
         for (int i = 0; i < R; ++i) {
-            const int row = a.map.row[at0 + i * OB];
-            double ad = rows.template product<double>(val, lcol, i, t, win);
+            int row;
+            double ad;
+            if constexpr (AWAY) {
+                row = rw[i];
+                ad = rows.reread(A, lcol, i, t, win);
+            } else {
+                row = a.map.row[at0 + i * OB];
+                ad = rows.template product<double>(val, lcol, i, t, win);
+            }
             formed(ad);
             float ri = 0.0f;
             if (row >= 0) {
-                const double r64 = a.r[row] - ad;
+                const double r64 = (AWAY ? r0[AWAY ? i : 0] : a.r[row]) - ad;
                 a.r[row] = r64;
-                a.x[row] += (double)win[i * OB + t];
+                a.x[row] = (AWAY ? x0[AWAY ? i : 0] : a.x[row]) + (double)win[i * OB + t];
                 ri = (float)r64;
-                const double zi = a.dinv[row] * r64;
+                const double zi = (AWAY ? d0[AWAY ? i : 0] : a.dinv[row]) * r64;
                 v[1] += zi * zi;
             }
             v[0] += (double)ri * (double)(a.map.dinv32[at0 + i * OB] * ri);
