@@ -473,6 +473,7 @@ mdx_status mdx_prepare(mdx_ctx *ctx, double dt, void *scratch, size_t scratch_by
         // fault flag with the same synchronisation
         HIPCHK(hipHostMalloc((void **)&ctx->bsc_host, sizeof(BScalars) * (ctx->n_inst + 1),
                              hipHostMallocDefault));
+        HIPCHK(hipHostGetDevicePointer((void **)&ctx->bsc_host_dev, ctx->bsc_host, 0));
         std::memset((void *)ctx->bsc_host, 0, sizeof(BScalars) * (ctx->n_inst + 1));
         HIPCHK(hipMemcpyAsync(ctx->dev<BScalars>(L.bsc), ctx->bsc_host,
                               sizeof(BScalars) * ctx->n_inst, hipMemcpyHostToDevice, st));

@@ -158,31 +158,14 @@ __global__ __launch_bounds__(256) void k_build_csr(int64_t n_rows, const int64_t
     }
 }
 
-// Per node, the three values the right-hand-side pass gathers, as one
-// 32-byte record: {Cm V + dt s, V, x0, 0} (x0 = 2 V - V_prev or V), so each
-// nonzero costs one gather instead of three scattered ones.
-// The per-node values the right-hand-side pass gathers at each column: a =
-// Cm V + dt s (for M), V (for K) and the warm start x0 (for A); 24 bytes
-// (a 32-byte record measured 1.4% more step time on the 12M-node cohort).
+// The per-node values the right-hand-side pass gathers at each column (written
+// by the ionic update, GatherOut): a = Cm V + dt s (for M), V (for K) and the
+// warm start x0 (for A), so each nonzero costs one gather instead of three
+// scattered ones; 24 bytes (a 32-byte record measured 1.4% more step time on
+// the 12M-node cohort).
 struct GV3 {
     double a, v, x;
 };
-__global__ __launch_bounds__(256) void k_b_gather_prep(int64_t n, StepParams sp,
-                                                       const double *__restrict__ V,
-                                                       const double *__restrict__ Vprev,
-                                                       const double *__restrict__ src,
-                                                       GV3 *__restrict__ gv)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const double v = V[i];
-    GV3 r;
-    r.a = sp.cm * v + sp.dt * src[i];
-    r.v = v;
-    r.x = sp.warm_start == 1 ? 2.0 * v - Vprev[i] : v;
-    gv[i] = r;
-}
-
 // ---------------------------------------------------------------------------
 template <bool NT>
 __global__ __launch_bounds__(256) void k_b_rhs_init(
@@ -255,6 +238,24 @@ __global__ __launch_bounds__(256) void k_b_init_finalize(int groups,
     const bool finite = isfinite(z0) && isfinite(db) && isfinite(v[0]);
     s.nonfinite = finite ? 0 : 1;
     s.done = (!finite || z0 <= s.floor_ || z0 < bp.atol) ? 1 : 0;
+}
+
+__global__ __launch_bounds__(256) void k_b_publish(const BScalars *__restrict__ sc, int n_inst,
+                                                   BScalars *__restrict__ rec,
+                                                   int32_t *__restrict__ ready, const Scalars *scal,
+                                                   Published *pub, int32_t seq)
+{
+    constexpr int words = (int)(sizeof(BScalars) / 4);
+    const int32_t *src = reinterpret_cast<const int32_t *>(sc);
+    int32_t *dst = reinterpret_cast<int32_t *>(rec);
+    for (int w = threadIdx.x; w < n_inst * words; w += 256) dst[w] = src[w];
+    int bad = 0;
+    for (int i = threadIdx.x; i < n_inst; i += 256)
+        if (!sc[i].done || sc[i].nonfinite || sc[i].gave_up) bad = 1;
+    __threadfence_system();
+    bad = __syncthreads_or(bad);
+    if (threadIdx.x == 0) *ready = bad ? 0 : 1;
+    if (threadIdx.x < SLICE) publish_scalars(scal, pub, seq);
 }
 
 // p = D^-1 r for the groups of running instances
@@ -808,14 +809,17 @@ void launch_relayout(hipStream_t s, int lpr, int64_t n_slices, const int64_t *sp
 
 void launch_b_rhs_init(hipStream_t s, const SegTiling &t, SellView P, const double *Mv,
                        const double *Kv, const double *dinv, const float *dinv32,
-                       const StepParams &sp, int64_t n_rows, const double *V, const double *Vprev,
-                       const double *src, double *gv, double *x, double *b, float *r32,
+                       const StepParams &sp, const double *gv, double *x, double *b, float *r32,
                        float *delta, double *partial, bool nt, bool keep_r)
 {
-    hipLaunchKernelGGL(k_b_gather_prep, dim3((unsigned)((n_rows + 255) / 256)), dim3(256), 0, s,
-                       n_rows, sp, V, Vprev, src, (GV3 *)gv);
     MDX_LAUNCH_NT(nt, k_b_rhs_init, dim3(t.groups), dim3(TILE), 0, s, t, P.slice_ptr, P.col, Mv, Kv,
                   dinv, dinv32, sp, (const GV3 *)gv, x, b, r32, delta, partial, keep_r ? 1 : 0);
+}
+
+void launch_b_publish(hipStream_t s, const BScalars *sc, int n_inst, BScalars *rec, int32_t *ready,
+                      const Scalars *scal, Published *pub, int32_t seq)
+{
+    hipLaunchKernelGGL(k_b_publish, dim3(1), dim3(256), 0, s, sc, n_inst, rec, ready, scal, pub, seq);
 }
 
 void launch_b_init_finalize(hipStream_t s, const SegTiling &t, const double *partial,

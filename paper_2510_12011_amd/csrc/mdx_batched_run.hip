@@ -24,7 +24,6 @@ BatchPtrs batch_ptrs(mdx_ctx *c)
     q.dinv = c->dev<double>(L.dinv);
     q.dinv32 = c->dev<float>(L.dinv32);
     q.b = c->dev<double>(L.b);
-    q.s = c->dev<double>(L.s);
     q.u = ionic_nstates(c->ionic_kind) ? c->dev<double>(L.u) : nullptr;
     q.part0 = c->dev<double>(L.partial);
     q.part_pq = q.part0 + 3 * kPartialCap;
@@ -68,9 +67,9 @@ mdx_status persistent_fault(mdx_ctx *c)
 // right-hand side and initial residual; keep_r: for the single-launch solve
 void enqueue_rhs(mdx_ctx *c, hipStream_t st, const BatchPtrs &q, bool keep_r)
 {
-    launch_b_rhs_init(st, c->seg, q.P, q.Mv, q.Kv, q.dinv, q.dinv32, step_params(c), c->npad,
-                      c->vec(0), c->vec(1), q.s, c->dev<double>(c->L.gv), c->vec(2), q.b, q.r32,
-                      q.delta, q.part0, use_nt(c, 20.0 * slots(c)), keep_r);
+    launch_b_rhs_init(st, c->seg, q.P, q.Mv, q.Kv, q.dinv, q.dinv32, step_params(c),
+                      c->dev<double>(c->L.gv), c->vec(2), q.b, q.r32, q.delta, q.part0,
+                      use_nt(c, 20.0 * slots(c)), keep_r);
     if (keep_r) return;
     launch_b_init_finalize(st, c->seg, q.part0, batch_params(c), q.bsc);
     launch_b_set_direction(st, c->seg, q.dinv32, q.r32, q.p32, q.bsc);
@@ -107,21 +106,31 @@ void enqueue_onchip(mdx_ctx *c, hipStream_t st, const BatchPtrs &q)
     launch_onchip_batch(st, c->onchip, a);
 }
 
-// ionic update, right-hand side and initial residual, then the solve in one
-// launch (iters < 0) or `iters` PCG iterations of every running instance and
-// one residual-replacement pass.  With `timed`, event pairs bracket the SpMV
+// ionic update at V (Vprev the one before it); times: the activation and
+// repolarisation times of the step that gave V, recorded with it
+void enqueue_ionic(mdx_ctx *c, hipStream_t st, const BatchPtrs &q, const double *V,
+                   const double *Vprev, const double *istim, const int32_t *guard,
+                   const StepTimes &times)
+{
+    const GatherOut gather{c->dev<double>(c->L.gv), Vprev, c->cm, c->dt, c->opts.warm_start};
+    if (c->opts.precision == MDX_PREC_MIXED_GATES32)
+        launch_ionic_step_mixed(st, c->ionic_kind, c->ionic_params.data(), c->npad, c->npad, c->dt,
+                                c->cm, V, q.u, q.g32, istim, nullptr, row_mask(c), guard, times,
+                                gather);
+    else
+        launch_ionic_step(st, c->ionic_kind, c->ionic_params.data(), c->npad, c->npad, c->dt, c->cm,
+                          V, q.u, istim, nullptr, 0, row_mask(c), guard, times, gather);
+}
+
+// right-hand side and initial residual, then the solve in one launch (iters <
+// 0) or `iters` PCG iterations of every running instance and one
+// residual-replacement pass.  With `timed`, event pairs bracket the SpMV
 // launches.
-void enqueue_batched_step(mdx_ctx *c, hipStream_t st, int iters, const double *istim, bool timed)
+void enqueue_batched_step(mdx_ctx *c, hipStream_t st, int iters, bool timed)
 {
     const BatchPtrs q = batch_ptrs(c);
     const BParams bp = batch_params(c);
-    double *V = c->vec(0), *X = c->vec(2);
-    if (c->opts.precision == MDX_PREC_MIXED_GATES32)
-        launch_ionic_step_mixed(st, c->ionic_kind, c->ionic_params.data(), c->npad, c->npad, c->dt,
-                                c->cm, V, q.u, q.g32, istim, q.s, row_mask(c));
-    else
-        launch_ionic_step(st, c->ionic_kind, c->ionic_params.data(), c->npad, c->npad, c->dt, c->cm,
-                          V, q.u, istim, q.s, 0, row_mask(c));
+    double *X = c->vec(2);
     enqueue_rhs(c, st, q, iters < 0);
     if (iters < 0) {
         enqueue_onchip(c, st, q);
@@ -192,11 +201,24 @@ mdx_status run_batched(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double 
     int64_t n_out = 0;
     auto t_start = std::chrono::steady_clock::now();
 
+    // a step's activation and repolarisation times are recorded by the next
+    // step's ionic update, or by a launch of their own
+    double *lat = ctx->dev<double>(L.lat), *lrt = ctx->dev<double>(L.lrt);
+    int32_t *ready = ctx->dev<int32_t>(L.oc_turn) + ctx->n_inst;
+    bool times_due = false;
+    bool ionic_queued = false;   // this step's ionic update was queued by the previous step
+    auto record_times = [&]() {
+        if (times_due)
+            launch_epilogue(st, ctx->npad, (double)ctx->step * ctx->dt, ctx->vec(1), ctx->vec(0),
+                            lat, lrt, sc);
+        times_due = false;
+    };
+
     for (int64_t j = 0; j < n_steps; ++j) {
         const int64_t k = ctx->step;
         bool any_stim = false;
         if (mdx_status e = update_stimulus(ctx, st, k, any_stim)) return e;
-        double *V = ctx->vec(0), *X = ctx->vec(2);
+        double *X = ctx->vec(2);
         const bool profiling = ctx->profile_every > 0 && k % ctx->profile_every == 0;
         const bool onchip = batch_onchip(ctx, profiling);
         const int C = onchip ? -1 : std::max(1, std::min(ctx->last_iters, max_iter));
@@ -204,12 +226,14 @@ mdx_status run_batched(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double 
         if (onchip) one = std::unique_lock<std::mutex>(onchip_mutex(ctx->device));
         // (six launches: a replay of them as a graph costs 8-10 us a step more)
         if (ctx->use_graph && !profiling && !onchip) {
+            record_times();   // the replayed ionic update does not
             const std::pair<int, int> key{ctx->persistent ? -1 : C, ctx->vb[0]};
             auto it = ctx->graphs.find(key);
             if (it == ctx->graphs.end()) {
                 hipGraph_t g = nullptr;
                 HIPCHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-                enqueue_batched_step(ctx, st, C, istim_dev, false);
+                enqueue_ionic(ctx, st, q, ctx->vec(0), ctx->vec(1), istim_dev, nullptr, StepTimes{});
+                enqueue_batched_step(ctx, st, C, false);
                 HIPCHK(hipStreamEndCapture(st, &g));
                 hipGraphExec_t ex = nullptr;
                 hipError_t ie = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
@@ -219,22 +243,50 @@ mdx_status run_batched(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double 
             }
             HIPCHK(hipGraphLaunch(it->second, st));
         } else {
-            enqueue_batched_step(ctx, st, C, any_stim ? istim_dev : nullptr, profiling);
+            if (!ionic_queued) {
+                StepTimes times;
+                if (times_due)
+                    times = StepTimes{(double)k * ctx->dt, ctx->vec(1), lat, lrt, sc};
+                times_due = false;
+                enqueue_ionic(ctx, st, q, ctx->vec(0), ctx->vec(1), any_stim ? istim_dev : nullptr,
+                              nullptr, times);
+            }
+            enqueue_batched_step(ctx, st, C, profiling);
         }
         HIPCHK(hipGetLastError());
         int units = C;
-        if (mdx_status e = fetch_bscalars(ctx, st)) return e;
-        if (ctx->persistent)
-            if (mdx_status e = persistent_fault(ctx)) return e;
+        ionic_queued = false;
         if (onchip) {
+            // the records published, and the next step's ionic update queued
+            // behind (it acts only if every instance is done), so that the
+            // device is busy while the host reads them and queues the rest
+            launch_b_publish(st, q.bsc, ctx->n_inst, ctx->bsc_host_dev, ready, sc, ctx->pub_dev,
+                             ++ctx->pub_seq);
+            if (j + 1 < n_steps) {
+                bool any_next = false;
+                if (mdx_status e = update_stimulus(ctx, st, k + 1, any_next)) return e;
+                enqueue_ionic(ctx, st, q, X, ctx->vec(0), any_next ? istim_dev : nullptr, ready,
+                              StepTimes{(double)(k + 1) * ctx->dt, ctx->vec(0), lat, lrt, sc});
+                ionic_queued = true;
+            }
+            HIPCHK(hipGetLastError());
+            auto w0 = std::chrono::steady_clock::now();
+            if (mdx_status e = wait_published(ctx, st, ctx->pub_seq)) return e;
+            ctx->stats.host_wait_seconds +=
+                std::chrono::duration<double>(std::chrono::steady_clock::now() - w0).count();
             one.unlock();
             units = 0;
             for (int i = 0; i < ctx->n_inst; ++i)
                 if (ctx->bsc_host[i].gave_up) ctx->onchip_off = true;
             if (ctx->onchip_off) {   // the step's solve again, by the streaming kernels
+                ionic_queued = false;
                 enqueue_rhs(ctx, st, q, false);
                 if (mdx_status e = fetch_bscalars(ctx, st)) return e;
             }
+        } else {
+            if (mdx_status e = fetch_bscalars(ctx, st)) return e;
+            if (ctx->persistent)
+                if (mdx_status e = persistent_fault(ctx)) return e;
         }
         while (!all_done(ctx) && units < max_iter + 1) {
             hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -297,8 +349,7 @@ mdx_status run_batched(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double 
                 ctx->stats.spmv_bytes += bytes;
             }
         }
-        launch_epilogue(st, ctx->npad, (double)(k + 1) * ctx->dt, V, X, ctx->dev<double>(L.lat),
-                        ctx->dev<double>(L.lrt), sc);
+        times_due = !ionic_queued;
         int old_prev = ctx->vb[1];
         ctx->vb[1] = ctx->vb[0];
         ctx->vb[0] = ctx->vb[2];
@@ -312,11 +363,12 @@ mdx_status run_batched(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double 
             ++n_out;
         }
     }
+    record_times();
     HIPCHK(hipMemcpyAsync(ctx->sc_host, sc, sizeof(Scalars), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     ctx->stats.step_loop_seconds +=
         std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();
-    if (ctx->sc_host->nonfinite)
+    if (ctx->sc_host->nonfinite || ctx->sc_host->nonfinite_v)
         return fail(ctx, MDX_ERR_NONFINITE, "non-finite V after step %lld", (long long)ctx->step);
     return result;
 }

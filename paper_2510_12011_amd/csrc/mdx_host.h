@@ -164,6 +164,7 @@ struct mdx_ctx {
     SegTiling pseg{};                     // its group table (all groups resident)
     SegTiling seg{};
     BScalars *bsc_host = nullptr;         // pinned, n_inst
+    BScalars *bsc_host_dev = nullptr;   // its device address
     std::vector<int32_t> inst_iters_hist; // per step, n_inst each
     bool use_graph = false;
     hipStream_t own_stream = nullptr;
@@ -193,7 +194,7 @@ struct BatchPtrs {
     IterMatrix IM;
     const double *Mv, *Kv, *Av, *dinv;
     const float *dinv32;
-    double *b, *s, *u, *part0, *part_pq, *part_rz;
+    double *b, *u, *part0, *part_pq, *part_rz;
     float *r32, *p32, *q32, *delta, *g32;
     BScalars *bsc;
 };

@@ -147,10 +147,20 @@ struct StepTimes {
     double *lat = nullptr, *lrt = nullptr;
     Scalars *sc = nullptr;   // its nonfinite_v flag
 };
+// The batched form's right-hand side gathers three values per column,
+// {Cm V + dt s, V, x0} (x0 = 2 V - V_prev or V): with gv the ionic update
+// writes them ([row][3]; zeros for padding rows) in place of the source s.
+struct GatherOut {
+    double *gv = nullptr;
+    const double *Vprev = nullptr;
+    double cm = 0.0, dt = 0.0;
+    int warm_start = 0;
+};
 void launch_ionic_step(hipStream_t s, int kind, const double *params, int64_t n, int64_t ld,
                        double dt, double cm, const double *V, double *u, const double *istim,
                        double *out, int raw, const int32_t *tile_real = nullptr,
-                       const int32_t *guard = nullptr, const StepTimes &times = StepTimes{});
+                       const int32_t *guard = nullptr, const StepTimes &times = StepTimes{},
+                       const GatherOut &gather = GatherOut{});
 
 // Mixed-precision form: gates in FP32 (g32, ionic_gate_rows(kind) rows of ld
 // floats), concentrations and the current in FP64 (u).  The FP64 array u
@@ -163,7 +173,8 @@ void launch_ionic_step_mixed(hipStream_t s, int kind, const double *params, int6
                              const double *istim, double *out,
                              const int32_t *tile_real = nullptr,
                              const int32_t *guard = nullptr,
-                             const StepTimes &times = StepTimes{});
+                             const StepTimes &times = StepTimes{},
+                             const GatherOut &gather = GatherOut{});
 void launch_gates_to_f32(hipStream_t s, int kind, int64_t ld, const double *u, float *g32);
 void launch_gates_to_f64(hipStream_t s, int kind, int64_t ld, const float *g32, double *u);
 
@@ -403,12 +414,16 @@ void launch_relayout_v4(hipStream_t s, int64_t n_slices, const int64_t *sptr_new
 void launch_build_csr(hipStream_t s, int64_t n_rows, SellView base, const float *A32,
                       const int32_t *rptr, int32_t *col_csr, float *val_csr);
 
-// gv: scratch of 3 doubles per row (the gathered per-node values)
+// gv: the gathered per-node values (GatherOut)
 void launch_b_rhs_init(hipStream_t s, const SegTiling &t, SellView P, const double *Mv,
                        const double *Kv, const double *dinv, const float *dinv32,
-                       const StepParams &sp, int64_t n_rows, const double *V, const double *Vprev,
-                       const double *src, double *gv, double *x, double *b, float *r32,
+                       const StepParams &sp, const double *gv, double *x, double *b, float *r32,
                        float *delta, double *partial, bool nt, bool keep_r);
+// The instances' records into host memory (rec: n_inst records' device address),
+// then the sequence number that the host waits for; *ready = 1 if every
+// instance is done with a finite result (what is queued behind may act).
+void launch_b_publish(hipStream_t s, const BScalars *sc, int n_inst, BScalars *rec, int32_t *ready,
+                      const Scalars *scal, Published *pub, int32_t seq);
 void launch_b_init_finalize(hipStream_t s, const SegTiling &t, const double *partial,
                             const BParams &bp, BScalars *sc);
 void launch_b_set_direction(hipStream_t s, const SegTiling &t, const float *dinv32,

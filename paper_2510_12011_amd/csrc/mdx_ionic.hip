@@ -737,6 +737,17 @@ __device__ __forceinline__ bool real_row(int64_t i, int64_t n, const int32_t *ti
     return tile_real ? (int)(i & (TILE - 1)) < tile_real[i / TILE] : i < n;
 }
 
+// The right-hand side's gathered values of row i, written where they are
+// formed: as a kernel of its own this pass read V, V_prev and the source again
+// (12 us of a step of 1,310,736 nodes, 4 of 232,472).
+__device__ __forceinline__ void put_gather(const GatherOut &g, int64_t i, double v, double src,
+                                           double vprev)
+{
+    g.gv[3 * i] = g.cm * v + g.dt * src;
+    g.gv[3 * i + 1] = v;
+    g.gv[3 * i + 2] = g.warm_start == 1 ? 2.0 * v - vprev : v;
+}
+
 // ---------------------------------------------------------------------------
 // The ten Tusscher-Panfilov and Courtemanche-Ramirez-Nattel updates were bound
 // by instruction issue: ~4,000 vector instructions a wavefront, half of them
@@ -747,7 +758,7 @@ __device__ __forceinline__ bool real_row(int64_t i, int64_t n, const int32_t *ti
 // 58 -> 41 and 55 -> 42 us.  Gates are streamed, loaded three ahead of their
 // use: 108 and 117 registers, four wavefronts per SIMD with no spills (with
 // the CRN states held in registers it was 179 and two wavefronts, 134 us).
-template <int KIND>
+template <int KIND, bool GATHER>
 __global__ __launch_bounds__(256) void k_ionic_step(IonicParams P, int64_t n, int64_t ld, double dt,
                                                     double cm, const double *__restrict__ V,
                                                     double *__restrict__ u,
@@ -755,13 +766,16 @@ __global__ __launch_bounds__(256) void k_ionic_step(IonicParams P, int64_t n, in
                                                     double *__restrict__ out, int raw,
                                                     const int32_t *__restrict__ tile_real,
                                                     const int32_t *__restrict__ guard,
-                                                    StepTimes times)
+                                                    StepTimes times, GatherOut gather)
 {
     if (guard && !*guard) return;   // enqueued ahead of a solve that is not done
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     if (!real_row(i, n, tile_real)) {
-        out[i] = 0.0;
+        if constexpr (GATHER)
+            put_gather(gather, i, 0.0, 0.0, 0.0);
+        else
+            out[i] = 0.0;
         return;
     }
     double v = V[i];
@@ -787,10 +801,15 @@ __global__ __launch_bounds__(256) void k_ionic_step(IonicParams P, int64_t n, in
 #pragma unroll
         for (int s = 0; s < 5; ++s) u[s * ld + i] = c[s];
     }
-    if (raw)
+    if (raw) {
         out[i] = iion;
+        return;
+    }
+    const double src = (istim ? istim[i] : 0.0) - cm * iion;
+    if constexpr (GATHER)
+        put_gather(gather, i, v, src, gather.Vprev[i]);
     else
-        out[i] = (istim ? istim[i] : 0.0) - cm * iion;
+        out[i] = src;
 }
 
 template <int KIND>
@@ -825,7 +844,7 @@ __global__ __launch_bounds__(256) void k_ionic_init(IonicParams P, int64_t n, in
 // (g32[s * ld + i], s over the model's gates), concentration-type states and
 // the current in FP64 (u[s * ld + i], rows 0..5 for the ten Tusscher-Panfilov
 // model; Mitchell-Schaeffer has only its gate h).
-template <int KIND>
+template <int KIND, bool GATHER>
 __global__ __launch_bounds__(256) void k_ionic_step_mixed(IonicParams P, int64_t n, int64_t ld,
                                                           double dt, double cm,
                                                           const double *__restrict__ V,
@@ -835,13 +854,16 @@ __global__ __launch_bounds__(256) void k_ionic_step_mixed(IonicParams P, int64_t
                                                           double *__restrict__ out,
                                                           const int32_t *__restrict__ tile_real,
                                                           const int32_t *__restrict__ guard,
-                                                          StepTimes times)
+                                                          StepTimes times, GatherOut gather)
 {
     if (guard && !*guard) return;   // enqueued ahead of a solve that is not done
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     if (!real_row(i, n, tile_real)) {
-        out[i] = 0.0;
+        if constexpr (GATHER)
+            put_gather(gather, i, 0.0, 0.0, 0.0);
+        else
+            out[i] = 0.0;
         return;
     }
     const double v = V[i];
@@ -860,7 +882,11 @@ __global__ __launch_bounds__(256) void k_ionic_step_mixed(IonicParams P, int64_t
 #pragma unroll
         for (int s = 0; s < 6; ++s) u[s * ld + i] = c[s];
     }
-    out[i] = (istim ? istim[i] : 0.0) - cm * iion;
+    const double src = (istim ? istim[i] : 0.0) - cm * iion;
+    if constexpr (GATHER)
+        put_gather(gather, i, v, src, gather.Vprev[i]);
+    else
+        out[i] = src;
 }
 
 // copy rows [row0, row0 + rows) of an FP64 SoA state block to FP32 or back
@@ -927,23 +953,24 @@ void launch_ionic_init(hipStream_t s, int kind, const double *params, int64_t n,
 void launch_ionic_step(hipStream_t s, int kind, const double *params, int64_t n, int64_t ld,
                        double dt, double cm, const double *V, double *u, const double *istim,
                        double *out, int raw, const int32_t *tile_real, const int32_t *guard,
-                       const StepTimes &times)
+                       const StepTimes &times, const GatherOut &gather)
 {
     if (n <= 0) return;
     IonicParams P = pack(kind, params);
     dim3 grid((unsigned)((n + 255) / 256)), block(256);
+    void (*k)(IonicParams, int64_t, int64_t, double, double, const double *, double *, const double *,
+              double *, int, const int32_t *, const int32_t *, StepTimes, GatherOut);
+    const bool gv = gather.gv != nullptr;
     if (kind == 1)
-        hipLaunchKernelGGL(k_ionic_step<MDX_KIND_MS>, grid, block, 0, s, P, n, ld, dt, cm, V, u,
-                           istim, out, raw, tile_real, guard, times);
+        k = gv ? k_ionic_step<MDX_KIND_MS, true> : k_ionic_step<MDX_KIND_MS, false>;
     else if (kind == 2)
-        hipLaunchKernelGGL(k_ionic_step<MDX_KIND_TT>, grid, block, 0, s, P, n, ld, dt, cm, V, u,
-                           istim, out, raw, tile_real, guard, times);
+        k = gv ? k_ionic_step<MDX_KIND_TT, true> : k_ionic_step<MDX_KIND_TT, false>;
     else if (kind == 3)
-        hipLaunchKernelGGL(k_ionic_step<MDX_KIND_CRN>, grid, block, 0, s, P, n, ld, dt, cm, V, u,
-                           istim, out, raw, tile_real, guard, times);
+        k = gv ? k_ionic_step<MDX_KIND_CRN, true> : k_ionic_step<MDX_KIND_CRN, false>;
     else
-        hipLaunchKernelGGL(k_ionic_step<MDX_KIND_NONE>, grid, block, 0, s, P, n, ld, dt, cm, V, u,
-                           istim, out, raw, tile_real, guard, times);
+        k = gv ? k_ionic_step<MDX_KIND_NONE, true> : k_ionic_step<MDX_KIND_NONE, false>;
+    hipLaunchKernelGGL(k, grid, block, 0, s, P, n, ld, dt, cm, V, u, istim, out, raw, tile_real, guard,
+                       times, gather);
 }
 
 int ionic_gate_rows(int kind) { return kind == 1 ? 1 : kind == 2 ? 12 : 0; }
@@ -952,20 +979,22 @@ int ionic_gate_row0(int kind) { return kind == 1 ? 0 : kind == 2 ? 6 : 0; }
 void launch_ionic_step_mixed(hipStream_t s, int kind, const double *params, int64_t n, int64_t ld,
                              double dt, double cm, const double *V, double *u, float *g32,
                              const double *istim, double *out, const int32_t *tile_real,
-                             const int32_t *guard, const StepTimes &times)
+                             const int32_t *guard, const StepTimes &times, const GatherOut &gather)
 {
     if (n <= 0) return;
     IonicParams P = pack(kind, params);
     dim3 grid((unsigned)((n + 255) / 256)), block(256);
+    void (*k)(IonicParams, int64_t, int64_t, double, double, const double *, double *, float *,
+              const double *, double *, const int32_t *, const int32_t *, StepTimes, GatherOut);
+    const bool gv = gather.gv != nullptr;
     if (kind == 1)
-        hipLaunchKernelGGL(k_ionic_step_mixed<MDX_KIND_MS>, grid, block, 0, s, P, n, ld, dt, cm, V,
-                           u, g32, istim, out, tile_real, guard, times);
+        k = gv ? k_ionic_step_mixed<MDX_KIND_MS, true> : k_ionic_step_mixed<MDX_KIND_MS, false>;
     else if (kind == 2)
-        hipLaunchKernelGGL(k_ionic_step_mixed<MDX_KIND_TT>, grid, block, 0, s, P, n, ld, dt, cm, V,
-                           u, g32, istim, out, tile_real, guard, times);
+        k = gv ? k_ionic_step_mixed<MDX_KIND_TT, true> : k_ionic_step_mixed<MDX_KIND_TT, false>;
     else
-        hipLaunchKernelGGL(k_ionic_step_mixed<MDX_KIND_NONE>, grid, block, 0, s, P, n, ld, dt, cm,
-                           V, u, g32, istim, out, tile_real, guard, times);
+        k = gv ? k_ionic_step_mixed<MDX_KIND_NONE, true> : k_ionic_step_mixed<MDX_KIND_NONE, false>;
+    hipLaunchKernelGGL(k, grid, block, 0, s, P, n, ld, dt, cm, V, u, g32, istim, out, tile_real, guard,
+                       times, gather);
 }
 
 void launch_gates_to_f32(hipStream_t s, int kind, int64_t ld, const double *u, float *g32)

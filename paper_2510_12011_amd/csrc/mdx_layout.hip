@@ -258,7 +258,7 @@ mdx_status build_onchip(mdx_ctx *c, hipStream_t st)
     if (c->batched) {
         HIPCHK(hipMemcpyAsync(c->dev<int4>(L.oc_team), team.data(), sizeof(int4) * team.size(),
                               hipMemcpyHostToDevice, st));
-        launch_fill(st, (c->n_inst + 1) / 2, 0.0, c->dev<double>(L.oc_turn));
+        launch_fill(st, (c->n_inst + 2) / 2, 0.0, c->dev<double>(L.oc_turn));
     }
     // no slot holds a value: all bits set
     const uint64_t empty = ~(uint64_t)0;
@@ -342,7 +342,7 @@ void compute_layout(mdx_ctx *c)
         L.oc_val32 = take(f32 ? sizeof(float) * (o.width + 1) * pos : 1);
         L.oc_dinv32 = take(f32 ? sizeof(float) * pos : 1);
         L.oc_team = take(sizeof(int4) * g);
-        L.oc_turn = take(sizeof(int32_t) * (c->n_inst + 1));
+        L.oc_turn = take(sizeof(int32_t) * (c->n_inst + 2));   // and the ready flag
         L.oc_quads = take(sizeof(int32_t) * pos / SLICE);
         L.oc_away = take(o.shape[1] ? 2 * sizeof(float) * pos : 1);
         L.oc_z = take(sizeof(double) * pos);
