@@ -366,8 +366,15 @@ mdx_status mdx_prepare(mdx_ctx *ctx, double dt, void *scratch, size_t scratch_by
             return fail(ctx, MDX_ERR_BAD_MESH, "contribution out of range");
 
     HIPCHK(hipSetDevice(ctx->device));
-    if (!ctx->stage) HIPCHK(hipHostMalloc((void **)&ctx->stage, sizeof(double) * ctx->npad,
-                                          hipHostMallocDefault));
+    if (ctx->stage && ctx->stage_len < ctx->npad) {   // a larger mesh than the last one's
+        (void)hipHostFree(ctx->stage);
+        ctx->stage = nullptr;
+    }
+    if (!ctx->stage) {
+        HIPCHK(hipHostMalloc((void **)&ctx->stage, sizeof(double) * ctx->npad, hipHostMallocDefault));
+        ctx->stage_len = ctx->npad;
+        HIPCHK(hipHostGetDevicePointer((void **)&ctx->stage_dev, ctx->stage, 0));
+    }
     const Layout &L = ctx->L;
     char *x = (char *)scratch;
     hipStream_t st = ctx->stream;
@@ -423,6 +430,8 @@ mdx_status mdx_prepare(mdx_ctx *ctx, double dt, void *scratch, size_t scratch_by
     launch_to_f32(st, ctx->npad, ctx->dev<double>(L.dinv), ctx->dev<float>(L.dinv32));
     HIPCHK(hipGetLastError());
 
+    HIPCHK(hipMemcpyAsync(ctx->dev<int32_t>(L.iperm), ctx->iperm.data(), sizeof(int32_t) * ctx->n,
+                          hipMemcpyHostToDevice, st));
     // state: rest values, zeroed work vectors, LAT/LRT = +inf
     ctx->vb[0] = 0;
     ctx->vb[1] = 1;

@@ -55,7 +55,7 @@ struct Layout {
     size_t pgrp, pinst_grp, pbar;   // batched form, persistent iteration
     // single-launch solve: exchange slots, block maps, values, z
     size_t words, oc_row, oc_col, oc_hptr, oc_hrow, oc_hat, oc_val64, oc_dinv64, oc_val32,
-        oc_dinv32, oc_away, oc_z, oc_team, oc_turn, oc_quads;
+        oc_dinv32, oc_away, oc_z, oc_team, oc_turn, oc_quads, iperm;
     size_t csr_ptr, csr_col, csr_val, gv;
     size_t total;
     size_t x_xyz, x_tets, x_fibre, x_sig, x_vol, x_ek, x_cptr, x_contrib, x_total;
@@ -119,6 +119,8 @@ struct mdx_ctx {
     Published *pub = nullptr, *pub_dev = nullptr;
     int32_t pub_seq = 0;
     double *stage = nullptr;      // pinned, npad doubles
+    double *stage_dev = nullptr;  // its device address
+    int64_t stage_len = 0;
 
     // learned warm start
     bool mlp_set = false;

@@ -64,6 +64,15 @@ __global__ __launch_bounds__(256) void k_fill(int64_t n, double v, double *__res
     if (i < n) x[i] = v;
 }
 
+// y[i] = x[at[i]]
+__global__ __launch_bounds__(256) void k_reorder(int64_t n, const int32_t *__restrict__ at,
+                                                 const double *__restrict__ x,
+                                                 double *__restrict__ y)
+{
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) y[i] = x[at[i]];
+}
+
 __global__ __launch_bounds__(256) void k_stim_add(int64_t n_idx, const int32_t *__restrict__ idx,
                                                   double amp, double *__restrict__ istim)
 {
@@ -375,6 +384,11 @@ inline unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 void launch_fill(hipStream_t s, int64_t n, double v, double *x)
 {
     if (n > 0) hipLaunchKernelGGL(k_fill, dim3(blocks_for(n)), dim3(256), 0, s, n, v, x);
+}
+
+void launch_reorder(hipStream_t s, int64_t n, const int32_t *at, const double *x, double *y)
+{
+    if (n > 0) hipLaunchKernelGGL(k_reorder, dim3(blocks_for(n)), dim3(256), 0, s, n, at, x, y);
 }
 
 void launch_stim_add(hipStream_t s, int64_t n_idx, const int32_t *idx, double amp, double *istim)
