@@ -536,6 +536,26 @@ struct Halo {
     }
 };
 
+// The FP64 values that a residual replacement reads and writes of the thread's
+// rows (rows: the thread's first place).
+template <int R>
+struct Ahead {
+    int at[R];   // -1 past the block's last row
+    double r[R], x[R], d[R];
+    __device__ __forceinline__ void places(const int32_t *rows)
+    {
+#pragma unroll
+        for (int i = 0; i < R; ++i) at[i] = rows[i * OB];
+    }
+    __device__ __forceinline__ void read(const double *r64, const double *x64, const double *dinv, int i)
+    {
+        const int k = max(at[i], 0);
+        r[i] = r64[k];
+        x[i] = x64[k];
+        d[i] = dinv[k];
+    }
+};
+
 // ---- plain FP64 ------------------------------------------------------------
 template <int W, int R>
 __global__ __launch_bounds__(OB) void k_onchip(OnchipSolve a)
@@ -776,23 +796,17 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
             win[i * OB + t] = di;
             st_agent(zb + at0 + i * OB, di);
         }
-        // AWAY: with the values gone there is room to read ahead
-        constexpr int RA = AWAY ? R : 1;
-        int rw[RA];
-        double r0[RA], x0[RA], d0[RA];
+        // the rows' FP64 residual, solution and D^-1 are read ahead: all of
+        // them where the values are gone, else a row ahead of its product
+        Ahead<R> row;
         double none[1] = {0.0};
         const bool there = exchange<1>(none, xl, team, turn, [&] {
-            if constexpr (AWAY) {
+            row.places(a.map.row + at0);
+            if constexpr (AWAY)
 #pragma unroll
-                for (int i = 0; i < R; ++i) rw[i] = a.map.row[at0 + i * OB];
-#pragma unroll
-                for (int i = 0; i < R; ++i) {
-                    const int at = max(rw[i], 0);
-                    r0[i] = a.r[at];
-                    x0[i] = a.x[at];
-                    d0[i] = a.dinv[at];
-                }
-            }
+                for (int i = 0; i < R; ++i) row.read(a.r, a.x, a.dinv, i);
+            else
+                row.read(a.r, a.x, a.dinv, 0);
         });
         if (!there) {
             o.aborted = 1;
@@ -803,23 +817,21 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
         const float4 *A = reinterpret_cast<const float4 *>(a.map.val32) + (size_t)g * (own * (W + 1) / 4) + t;
 #pragma unroll
         for (int i = 0; i < R; ++i) {
-            int row;
             double ad;
             if constexpr (AWAY) {
-                row = rw[i];
                 ad = rows.reread(A, lcol, i, t, win);
             } else {
-                row = a.map.row[at0 + i * OB];
+                if (i + 1 < R) row.read(a.r, a.x, a.dinv, i + 1);
                 ad = rows.template product<double>(val, lcol, i, t, win);
             }
             formed(ad);
             float ri = 0.0f;
-            if (row >= 0) {
-                const double r64 = (AWAY ? r0[AWAY ? i : 0] : a.r[row]) - ad;
-                a.r[row] = r64;
-                a.x[row] = (AWAY ? x0[AWAY ? i : 0] : a.x[row]) + (double)win[i * OB + t];
+            if (row.at[i] >= 0) {
+                const double r64 = row.r[i] - ad;
+                a.r[row.at[i]] = r64;
+                a.x[row.at[i]] = row.x[i] + (double)win[i * OB + t];
                 ri = (float)r64;
-                const double zi = (AWAY ? d0[AWAY ? i : 0] : a.dinv[row]) * r64;
+                const double zi = row.d[i] * r64;
                 v[1] += zi * zi;
             }
             v[0] += (double)ri * (double)(a.map.dinv32[at0 + i * OB] * ri);
@@ -1030,24 +1042,28 @@ __global__ __launch_bounds__(OB) void k_onchip_batch(OnchipBatch a)
             win[i * OB + t] = d[i];
             st_agent(a.zb + at0 + i * OB, d[i]);
         }
+        Ahead<R> row;
         double none[1] = {0.0};
-        gave_up = !exchange<1>(none, xl, team, turn, nothing);
+        gave_up = !exchange<1>(none, xl, team, turn, [&] {
+            row.places(a.map.row + at0);
+            row.read(a.r, a.x, a.dinv, 0);
+        });
         if (gave_up) break;
         halo.fill(a.zb, win + own, nh);
         v[0] = v[1] = 0.0;
         const double2 *A = reinterpret_cast<const double2 *>(a.map.val64) + (size_t)g * (own * (W + 1) / 2) + t;
 #pragma unroll
         for (int i = 0; i < R; ++i) {
-            const int row = a.map.row[at0 + i * OB];
+            if (i + 1 < R) row.read(a.r, a.x, a.dinv, i + 1);
             double ad = rows.streamed(A, lcol, i, t, win, nq[i]);
             formed(ad);
             float ri = 0.0f;
-            if (row >= 0) {
-                const double r64 = a.r[row] - ad;
-                a.r[row] = r64;
-                a.x[row] += (double)d[i];
+            if (row.at[i] >= 0) {
+                const double r64 = row.r[i] - ad;
+                a.r[row.at[i]] = r64;
+                a.x[row.at[i]] = row.x[i] + (double)d[i];
                 ri = (float)r64;
-                const double zi = a.dinv[row] * r64;
+                const double zi = row.d[i] * r64;
                 v[1] += zi * zi;
             }
             r[i] = ri;
