@@ -16,10 +16,12 @@
 // slab (17.2 a step; 256 workgroups of 4 rows a thread) the products take
 // 1.1 us, the update 0.7, the halo 0.9 and each exchange 3 (1.3 with 20
 // workgroups); an exchange alone measured 1.8 us at 256 workgroups, 3.0 with
-// one copy of the slots, 2.1-2.3 over two levels.  Time steps before -> after
-// (streaming kernels -> this): 9,261-node cube 283 -> 83 us, 58,176-node slab
-// 406 -> 143, 442,401-node slab 696 -> 292, FP32 iteration on 871,221 nodes
-// 464 -> 331, on the 1,255,450-node shell with the network 727 -> 684.
+// one copy of the slots, 2.1-2.3 over two levels.  Time steps, streaming
+// kernels -> this: 9,261-node cube 283 -> 83 us, 58,176-node slab 406 -> 143,
+// 442,401-node slab 696 -> 292 (solve 169), FP32 iteration on 871,221 nodes
+// 464 -> 331 (solve 110 since its replacement reads ahead), on the
+// 1,255,450-node shell with the network 727 -> 684 and, with the values read
+// again instead of spilled, 650 (solve 295).
 // Gathering z through the caches instead of LDS took 4.3 us of the FP64 slab's
 // iteration and 14 of the shell's.
 //
