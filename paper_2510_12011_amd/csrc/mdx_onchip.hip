@@ -896,9 +896,10 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
 // correction (r64 -= A delta, FP64 values of A streamed by block), which is
 // b - A (x + delta) up to the rounding of x.
 //
-// Solve of a step, streaming kernels -> this (and the whole step): 12
-// unstructured shells of 232,472 nodes in all, 4.0 iterations, 130 -> 46 us
-// (187 -> 111); 8 surfaces of 1,310,736, 1.8 iterations, 165 -> 79 (280 -> 211).
+// Solve of a step, streaming kernels -> this (and the whole step, with the
+// ionic update's fused passes): 12 unstructured shells of 232,472 nodes in
+// all, 4.0 iterations, 130 -> 47 us (187 -> 96); 8 surfaces of 1,310,736, 1.8
+// iterations, 165 -> 69 (280 -> 171; 79 with 12 rows a thread where 11 do).
 // Bound by one read of the values and columns (23 and 45 MB), the replacement's
 // read of the FP64 values and some 3 us per exchange.
 //
