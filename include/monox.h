@@ -301,6 +301,12 @@ MDX_API mdx_status mdx_set_profiling(mdx_ctx *ctx, int32_t every_n);
  *                        hand (not by mdx_autotune), PERSISTENT and a profiled
  *                        step select the streaming kernels, and GRAPH has no
  *                        effect on the single launch.
+ *   MDX_TUNE_ONCHIP_GIVE_UP  for tests of that fallback: e * 512 + w * 256 + g
+ *                        has workgroup g of such a launch stop looking at its
+ *                        e-th exchange of sums (e >= 1; 0, the default: none);
+ *                        with w = 1 not before the launch's outcome is known
+ *                        or ONCHIP_POLLS looks have passed.  Results are valid
+ *                        with any value.
  * MAX_GROUPS, SPMV_MAX_GROUPS and ITER_SCHEME take effect at the next
  * mdx_prepare / mdx_run;
  * the batched keys need a prepared batched context and act at once. */
@@ -315,7 +321,8 @@ enum {
     MDX_TUNE_COMPACT_COLUMNS = 8,
     MDX_TUNE_SPMV_MAX_GROUPS = 9,
     MDX_TUNE_PERSISTENT = 10,
-    MDX_TUNE_ONCHIP_POLLS = 11
+    MDX_TUNE_ONCHIP_POLLS = 11,
+    MDX_TUNE_ONCHIP_GIVE_UP = 12
 };
 MDX_API mdx_status mdx_set_tuning(mdx_ctx *ctx, int32_t key, int64_t value);
 

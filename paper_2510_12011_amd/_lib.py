@@ -35,6 +35,7 @@ MDX_TUNE_COMPACT_COLUMNS = 8
 MDX_TUNE_SPMV_MAX_GROUPS = 9
 MDX_TUNE_PERSISTENT = 10
 MDX_TUNE_ONCHIP_POLLS = 11
+MDX_TUNE_ONCHIP_GIVE_UP = 12
 MDX_TUNE_MAX_CANDIDATES = 32
 
 

@@ -464,7 +464,6 @@ mdx_status mdx_prepare(mdx_ctx *ctx, double dt, void *scratch, size_t scratch_by
     HIPCHK(hipStreamSynchronize(st));
 
     if (mdx_status e = build_onchip(ctx, st)) return e;
-    ctx->onchip_seen = 0;
     ctx->onchip_off = false;
     ctx->layout_set = false;
     ctx->tiling = make_tiling(ctx->npad, ctx->max_groups);
@@ -677,6 +676,11 @@ mdx_status mdx_set_tuning(mdx_ctx *ctx, int32_t key, int64_t value)
             return fail(ctx, MDX_ERR_INVALID_ARG, "onchip_polls must lie in [0, 10^9]");
         ctx->onchip_polls = (int)value;
         release_graphs(ctx);
+        return MDX_OK;
+    case MDX_TUNE_ONCHIP_GIVE_UP:
+        if (value < 0 || value > 0xffffff)
+            return fail(ctx, MDX_ERR_INVALID_ARG, "onchip_give_up must lie in [0, 2^24)");
+        ctx->onchip_give_up = {(int)(value >> 9), (int)(value & 0xff), (int)(value >> 8 & 1)};
         return MDX_OK;
     case MDX_TUNE_ITER_SCHEME:
         if (value != 0 && value != 1) return fail(ctx, MDX_ERR_INVALID_ARG, "scheme is 0 or 1");

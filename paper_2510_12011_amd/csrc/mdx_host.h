@@ -142,8 +142,8 @@ struct mdx_ctx {
     OnchipMap onchip_map{};
     bool onchip_ready = false;   // blocks built by the last prepare
     int onchip_turn = 0;         // turn of the next exchange
-    uint32_t onchip_launch = 0;  // launches so far
-    uint32_t onchip_seen = 0;    // the last launch known to have given up
+    uint32_t onchip_launch = 0;  // number of the last launch
+    OnchipGiveUp onchip_give_up{};
     bool onchip_off = false;     // one gave up: streaming kernels until the next prepare
     bool layout_set = false;     // batched: a streaming layout was chosen by hand
 

@@ -62,8 +62,10 @@ struct alignas(256) Scalars {
     int32_t use_mlp;    // learned warm start: the MLP guess was chosen this step
     double beta;        // beta of the next iteration (0: restart with p = z)
     double alpha;       // alpha of the current iteration
-    uint32_t onchip_abort;   // number of the last single-launch solve that gave up (0: none)
+    uint32_t onchip_verdict; // 2 x number of the last single-launch solve that exchanged, + 1
+                             // if it gave up: decided once per launch (mdx_onchip.hip)
     int32_t onchip_turn;     // turn of the next exchange after the last single-launch solve
+    int32_t onchip_gave_up;  // that solve gave up
 };
 
 // Scalars as published to host memory (coherent pinned): the host spins on
@@ -228,6 +230,12 @@ struct OnchipMap {
     float *val32, *dinv32;    // [pass][quad][thread][4], [position]
     float *r_away, *d_away;   // [position]: FP32 r and correction of the largest blocks
 };
+// For tests: workgroup `group` stops looking at its `exchange`-th exchange (1:
+// the first; 0: none); with `wait` only once the launch's outcome is known, or
+// its polls are used up.
+struct OnchipGiveUp {
+    int exchange, group, wait;
+};
 struct OnchipSolve {
     OnchipMap map;
     const double *z;                 // FP64 form: z0, r, x; FP32 form: r32, z32 and the
@@ -242,7 +250,8 @@ struct OnchipSolve {
     int polls;                       // of an exchange before the launch gives up
     unsigned long long *words;       // kOnchipWords
     int turn;                        // of the first exchange
-    unsigned launch;                 // number of this launch (not 0)
+    unsigned launch;                 // number of this launch, 1 .. 2^31 - 1
+    OnchipGiveUp give_up;
     Scalars *sc;
     Published *pub;
     int32_t seq;
@@ -261,9 +270,9 @@ OnchipPlan onchip_plan_batch(int device, const std::vector<int64_t> &n, int widt
 void launch_onchip_values(hipStream_t s, const OnchipPlan &p, const OnchipMap &m,
                           const int64_t *slice_ptr, const double *A, const double *dinv,
                           const float *A32, const float *dinv32);
-// the whole solve: every exit publishes the scalars (seq); done = 0 and
-// onchip_abort = launch where it gave up (the caller forms the right-hand
-// side again and solves with the streaming kernels)
+// the whole solve: every exit publishes the scalars (seq); onchip_gave_up = 1 and
+// done = 0 where it gave up (the caller forms the right-hand side again and
+// solves with the streaming kernels)
 void launch_onchip(hipStream_t s, const OnchipPlan &p, bool fp32, const OnchipSolve &a);
 
 // ---- learned warm start network (mdx_mlp.hip) ------------------------------
@@ -376,6 +385,7 @@ struct OnchipBatch {
     float *zb;                       // by block position
     unsigned long long *words;       // kOnchipWords
     int polls;
+    OnchipGiveUp give_up;
     int lanes;                       // of a row in the streaming layout (1, 2, 4, 8, 16)
     int32_t *turn;                   // [instance] turn of its next exchange
     BScalars *sc;

@@ -47,9 +47,17 @@
 // The wait needs every workgroup resident: at most one per CU is launched and
 // the host lets one such launch per device be in flight.  Polls are bounded:
 // where other work keeps a workgroup off the chip for long, the launch gives
-// up, marks its number in the scalars and changes nothing but scratch and x;
-// the host then forms the step's right-hand side again and solves it with the
-// streaming kernels.
+// up and changes nothing but scratch and x; the host then forms the step's
+// right-hand side again and solves it with the streaming kernels.
+//
+// A launch has one outcome: a workgroup whose polls are used up enters "gave
+// up", the first workgroup "finished" where it has seen the last exchange, and
+// the first of these entries holds (settle()).  A workgroup that comes too late
+// to give up keeps looking: its exchange is the last one, which the first
+// workgroup has seen whole, so the sums it lacks have been stored and arrive.
+// One that has finished where the launch gave up has only written rows of x.  So
+// what the first workgroup publishes, and what kernels behind the launch read in
+// the scalars, holds for all workgroups.
 #include "mdx_device.h"
 #include "mdx_internal.h"
 
@@ -98,6 +106,19 @@ __device__ __forceinline__ void st_agent(T *p, T v)
 // this wavefront's stores have reached the agent's point of coherence
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// The launch's outcome if it has one, else this one: word holds 2 * launch +
+// (1: gave up) from then on.
+__device__ __forceinline__ bool settle(uint32_t *word, unsigned launch, bool gave_up)
+{
+    uint32_t now = ld_agent(word);
+    while (now >> 1 != launch)   // at most one other entry gets in between
+        if (__hip_atomic_compare_exchange_strong(word, &now, launch << 1 | (gave_up ? 1u : 0u),
+                                                 __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT))
+            return gave_up;
+    return now & 1;
+}
+
 struct ExchangeLds {
     double part[3][OW];
     double tot[2];
@@ -108,15 +129,37 @@ struct ExchangeLds {
 struct Team {
     u64 *words;
     int polls, g, g0, G;
+    int left;   // 2 x exchanges until this workgroup stops looking + OnchipGiveUp::wait (below 2: none)
 };
+// a workgroup's part in a launch with one outcome
+struct SolveTeam : Team {
+    uint32_t *verdict;
+    unsigned launch;
+    // no more looking: true if the launch gives up
+    __device__ __forceinline__ bool gives_up() const
+    {
+        const int r = (threadIdx.x & 63) == 0 && settle(verdict, launch, true);
+        return __builtin_amdgcn_readfirstlane(r) != 0;
+    }
+    __device__ __forceinline__ bool settled() const { return ld_agent(verdict) >> 1 == launch; }
+};
+// the batched form: a kernel behind it looks at every instance's outcome
+struct BatchTeam : Team {
+    __device__ __forceinline__ bool gives_up() const { return true; }
+    __device__ __forceinline__ bool settled() const { return true; }
+};
+__device__ __forceinline__ Team team_of(u64 *words, int polls, const OnchipGiveUp &t, int g, int g0, int G)
+{
+    return {words, polls, g, g0, G, t.group == g ? 2 * t.exchange + t.wait : 0};
+}
 
 // Sum v over all threads of the team; false when the wait gave up.
 // turn: 0, 1, 2, 0, ... in successive exchanges.  during() runs once the
 // workgroup's sums are on their way: loads issued there are hidden by the wait
 // (issued before it they would hold up the sums: the store count that orders
 // them counts loads too).
-template <int NV, class F>
-__device__ __forceinline__ bool exchange(double (&v)[NV], ExchangeLds &l, const Team &team,
+template <int NV, class T, class F>
+__device__ __forceinline__ bool exchange(double (&v)[NV], ExchangeLds &l, T &team,
                                          int &turn, F &&during)
 {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -147,11 +190,21 @@ __device__ __forceinline__ bool exchange(double (&v)[NV], ExchangeLds &l, const 
         }
     }
     during();
+    bool stop = false;
+    if (team.left > 1) {
+        team.left -= 2;
+        stop = team.left < 2;
+    }
     if (w == 0) {
         buf += blockIdx.x % NXCD * (2 * kOnchipGroups) + team.g0;
         constexpr int C = kOnchipGroups / SLICE;
         double acc[NV];
         int n = 0;
+        if (stop) {
+            if (team.left)
+                while (!team.settled() && n < team.polls) ++n;
+            n = team.polls;
+        }
         bool all;
         do {
             u64 s[C][NV];
@@ -174,8 +227,8 @@ __device__ __forceinline__ bool exchange(double (&v)[NV], ExchangeLds &l, const 
                         all = all && s[c][k] != kEmpty;
                         acc[k] += __longlong_as_double((long long)s[c][k]);
                     }
-            all = __all(all);
-        } while (!all && ++n < team.polls);
+            all = __all(all) && !(stop && n == team.polls);
+        } while (!all && (++n < team.polls || !team.gives_up()));
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
             const double t = wave_total63(acc[k]);
@@ -273,10 +326,11 @@ struct Outcome {
 };
 __device__ void report(const OnchipSolve &a, const Start &s, const Outcome &o, int turn)
 {
-    if (o.aborted && threadIdx.x == 0) st_agent(&a.sc->onchip_abort, a.launch);
     if (blockIdx.x != 0 || threadIdx.x >= SLICE) return;
     Scalars *sc = a.sc;
     if (threadIdx.x == 0) {
+        // (without an exchange nobody can have given up)
+        const int gave_up = o.aborted || (o.it > 0 && settle(&sc->onchip_verdict, a.launch, false));
         st_agent(&sc->rho[o.it & 1], o.rho);
         st_agent(&sc->ref, s.ref);
         st_agent(&sc->floor_, s.floor_);
@@ -288,7 +342,8 @@ __device__ void report(const OnchipSolve &a, const Start &s, const Outcome &o, i
         st_agent(&sc->beta, 0.0);
         st_agent(&sc->it_next, o.it);
         st_agent(&sc->onchip_turn, turn);
-        st_agent(&sc->done, o.aborted ? 0 : o.done);
+        st_agent(&sc->onchip_gave_up, gave_up);
+        st_agent(&sc->done, gave_up ? 0 : o.done);
     }
     stores_done();
     publish_scalars(sc, a.pub, a.seq);
@@ -568,7 +623,7 @@ __global__ __launch_bounds__(OB) void k_onchip(OnchipSolve a)
     __shared__ double win[own + kOnchipHalo];
     __shared__ double ldv[R][OB];
     const int G = gridDim.x, g = logical_group(G);
-    const Team team = {a.words, a.polls, g, 0, G};
+    SolveTeam team = {team_of(a.words, a.polls, a.give_up, g, 0, G), &a.sc->onchip_verdict, a.launch};
     int t = threadIdx.x;
     unsigned at0 = (unsigned)g * own + t;   // block position of pass i: at0 + i * OB
     double *zb = static_cast<double *>(a.zb);
@@ -678,7 +733,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
     __shared__ float win[own + kOnchipHalo];
     __shared__ float ldv[AWAY ? 1 : R][OB];
     const int G = gridDim.x, g = logical_group(G);
-    const Team team = {a.words, a.polls, g, 0, G};
+    SolveTeam team = {team_of(a.words, a.polls, a.give_up, g, 0, G), &a.sc->onchip_verdict, a.launch};
     int t = threadIdx.x;
     unsigned at0 = (unsigned)g * own + t;
     float *zb = static_cast<float *>(a.zb);
@@ -916,7 +971,7 @@ __global__ __launch_bounds__(OB) void k_onchip_batch(OnchipBatch a)
     __shared__ float ldv[R][OB];
     const int g = logical_group(gridDim.x);
     const int4 gr = a.grp[g];
-    const Team team = {a.words, a.polls, g, gr.y, gr.z};
+    BatchTeam team = {team_of(a.words, a.polls, a.give_up, g, gr.y, gr.z)};
     int t = threadIdx.x;
     unsigned at0 = (unsigned)g * own + t;
     // the instance's partials, summed by each of its workgroups in one order

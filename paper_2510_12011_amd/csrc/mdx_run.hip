@@ -100,17 +100,10 @@ mdx_status mdx_run(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double *v_o
     os.max_iter = max_iter;
     os.rr = ctx->opts.rr_interval;
     os.polls = ctx->onchip_polls;
+    os.give_up = ctx->onchip_give_up;
     os.words = ctx->dev<unsigned long long>(L.words);
     os.sc = sc;
     os.pub = ctx->pub_dev;
-    // a launch that gave up after it had been taken for done (its first
-    // workgroup saw every sum that another did not)
-    auto late_abort = [&]() -> mdx_status {
-        if (ctx->sc_host->onchip_abort == ctx->onchip_seen) return MDX_OK;
-        ctx->onchip_seen = ctx->sc_host->onchip_abort;
-        ctx->onchip_off = true;
-        return fail(ctx, MDX_ERR_DEVICE, "a single-launch solve was interrupted");
-    };
     bool ionic_queued = false;   // this step's ionic update was queued by the previous step
 
     for (int64_t j = 0; j < n_steps; ++j) {
@@ -218,19 +211,17 @@ mdx_status mdx_run(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double *v_o
             std::lock_guard<std::mutex> one(onchip_mutex(ctx->device));
             os.x = X;
             os.turn = ctx->onchip_turn;
-            if (++ctx->onchip_launch == 0) ctx->onchip_launch = 1;
+            ctx->onchip_launch = ctx->onchip_launch % 0x7fffffffu + 1;
             os.launch = ctx->onchip_launch;
             os.seq = ++ctx->pub_seq;   // the launch publishes the scalars itself
             launch_onchip(st, ctx->onchip, mixed, os);
             if (mdx_status e = end_chunk()) return e;
             ctx->onchip_turn = ctx->sc_host->onchip_turn;
-            if (ctx->sc_host->onchip_abort == os.launch) {
-                ctx->onchip_seen = os.launch;
+            if (ctx->sc_host->onchip_gave_up) {   // what is queued behind it does not act
                 ctx->onchip_off = true;
                 onchip = false;
                 queue_rhs();
             } else {
-                if (mdx_status e = late_abort()) return e;
                 done = ctx->sc_host->done != 0;
             }
         }
@@ -346,7 +337,6 @@ mdx_status mdx_run(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double *v_o
     HIPCHK(hipStreamSynchronize(st));
     ctx->stats.step_loop_seconds +=
         std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();
-    if (mdx_status e = late_abort()) return e;
     if (ctx->sc_host->nonfinite || ctx->sc_host->nonfinite_v)
         return fail(ctx, MDX_ERR_NONFINITE, "non-finite V after step %lld", (long long)ctx->step);
     return result;
