@@ -141,7 +141,6 @@ struct mdx_ctx {
     OnchipPlan onchip;           // shape chosen with the mesh
     OnchipMap onchip_map{};
     bool onchip_ready = false;   // blocks built by the last prepare
-    int onchip_turn = 0;         // turn of the next exchange
     uint32_t onchip_launch = 0;  // number of the last launch
     OnchipGiveUp onchip_give_up{};
     bool onchip_off = false;     // one gave up: streaming kernels until the next prepare

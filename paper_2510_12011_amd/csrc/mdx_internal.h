@@ -64,7 +64,8 @@ struct alignas(256) Scalars {
     double alpha;       // alpha of the current iteration
     uint32_t onchip_verdict; // 2 x number of the last single-launch solve that exchanged, + 1
                              // if it gave up: decided once per launch (mdx_onchip.hip)
-    int32_t onchip_turn;     // turn of the next exchange after the last single-launch solve
+    int32_t onchip_turn;     // turn of the next single-launch solve's first exchange: kept with
+                             // the slots, whatever the host has seen of the last one
     int32_t onchip_gave_up;  // that solve gave up
 };
 
@@ -249,7 +250,6 @@ struct OnchipSolve {
     int max_iter, rr;
     int polls;                       // of an exchange before the launch gives up
     unsigned long long *words;       // kOnchipWords
-    int turn;                        // of the first exchange
     unsigned launch;                 // number of this launch, 1 .. 2^31 - 1
     OnchipGiveUp give_up;
     Scalars *sc;

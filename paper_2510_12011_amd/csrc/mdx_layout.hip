@@ -267,7 +267,6 @@ mdx_status build_onchip(mdx_ctx *c, hipStream_t st)
     launch_fill(st, (int64_t)kOnchipWords, bits, c->dev<double>(L.words));
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(st));   // the host arrays end here
-    c->onchip_turn = 0;
     c->onchip_ready = true;
     return MDX_OK;
 }

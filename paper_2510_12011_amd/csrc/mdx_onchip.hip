@@ -648,7 +648,7 @@ __global__ __launch_bounds__(OB) void k_onchip(OnchipSolve a)
     for (int h = t; h < nh * HT; h += OB) win[own + h] = a.z[a.map.halo_row[h0 + h]];
     const Start st = start_of(a, parts, xl);
     Outcome o{st.rho, st.z0, 0, 1, st.finite ? 0 : 2, 0};
-    int turn = a.turn;
+    int turn = a.sc->onchip_turn;   // the first workgroup writes it after every exchange
     if (st.done) {
         report(a, st, o, turn);
         return;
@@ -764,7 +764,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
     for (int h = t; h < nh * HT; h += OB) win[own + h] = a.z32[a.map.halo_row[h0 + h]];
     if constexpr (!AWAY) st = start_of(a, parts, xl);
     Outcome o{st.rho, st.z0, 0, 1, st.finite ? 0 : 2, 0};
-    int turn = a.turn;
+    int turn = a.sc->onchip_turn;   // the first workgroup writes it after every exchange
     if (st.done) {
         report(a, st, o, turn);
         return;

@@ -210,13 +210,11 @@ mdx_status mdx_run(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double *v_o
         if (onchip) {
             std::lock_guard<std::mutex> one(onchip_mutex(ctx->device));
             os.x = X;
-            os.turn = ctx->onchip_turn;
             ctx->onchip_launch = ctx->onchip_launch % 0x7fffffffu + 1;
             os.launch = ctx->onchip_launch;
             os.seq = ++ctx->pub_seq;   // the launch publishes the scalars itself
             launch_onchip(st, ctx->onchip, mixed, os);
             if (mdx_status e = end_chunk()) return e;
-            ctx->onchip_turn = ctx->sc_host->onchip_turn;
             if (ctx->sc_host->onchip_gave_up) {   // what is queued behind it does not act
                 ctx->onchip_off = true;
                 onchip = false;

@@ -89,3 +89,28 @@ def test_tuning_range():
     for value, ok in ((0, True), (0xffffff, True), (-1, False), (1 << 24, False)):
         r = L.lib().mdx_set_tuning(s._h, L.MDX_TUNE_ONCHIP_GIVE_UP, value)
         assert r == (L.MDX_OK if ok else L.MDX_ERR_INVALID_ARG)
+
+
+@pytest.mark.parametrize("first", [5, 18, 20, 22, 35])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_goes_on_after_an_error_of_another_call(precision, first):
+    """A run that ends with an error that another call of the thread left behind,
+    its solve being in flight; from the state before it the next run is right."""
+    from paper_2510_12011_amd import _lib as L, sim
+    spec = inputs.tiny_cube(n=20)
+    s, w = (sim.from_spec(spec, precision=precision) for _ in range(2))
+    w.set_tuning(onchip_polls=0)
+    s.run(first)
+    state = s.get_state()
+    print("[case]", precision, first, s.iterations(first), flush=True)
+    assert L.lib().hipSetDevice(99) != 0        # no such device: an error for the caller
+    with pytest.raises(L.MdxError) as e:
+        s.run(10)
+    assert e.value.status == L.MDX_ERR_DEVICE
+    out = []
+    for t in (s, w):
+        t.set_state(**state)
+        _, st = t.run(20)
+        out.append((t.get_state(), t.iterations(20), st))
+    print("  iterations", out[0][1], out[1][1], flush=True)
+    _same(*out, BAR[precision], 0.01)
