@@ -110,8 +110,8 @@ __device__ __forceinline__ VOnly v_only(const cell::Coef &C, const IonicParams &
 {
     using namespace cell;
     VOnly o;
-    V = clip(V, 1.5e4);   // every exponential below stays in range
-    const double phi = V * (1.0 / RTONF);
+    // below -15 V e^{-phi} would leave the range; all that it enters has saturated
+    const double phi = (V < -1.5e4 ? -1.5e4 : V) * (1.0 / RTONF);
     const double e1 = exp_(C, -phi), up = exp_(C, NCX_GAMMA * phi), down = up * e1;
     constexpr double nao3 = NA_O * NA_O * NA_O;
     constexpr double ncx_den = (KM_NAI * KM_NAI * KM_NAI + nao3) * (KM_CA + CA_O);
@@ -121,9 +121,9 @@ __device__ __forceinline__ VOnly v_only(const cell::Coef &C, const IonicParams &
     o.nak = P.v[10] * (K_O / (K_O + KM_K)) * rn;
     o.ncx_up = P.v[11] * CA_O * (rx * up);
     o.ncx_down = P.v[11] * (nao3 * NCX_ALPHA) * (rx * down);
-    const double w = clip((V - 15.0) * (2.0 / RTONF), 700.0);
+    const double w = (V - 15.0) * (2.0 / RTONF);
     double ew, em1;
-    exp_expm1(C, w, ew, em1);
+    exp_expm1(C, clip(w, 700.0), ew, em1);
     o.ical_drive = w == 0.0 ? 2.0 * Far : 2.0 * Far * (w * rcp(em1));
     o.ical_ew = 0.25 * ew;
     o.ipk = P.v[9] * rcp(1.0 + exp_(C, (25.0 - clip(V, 2400.0)) * (1.0 / 5.98)));
@@ -531,18 +531,19 @@ __device__ const double CRN_U0[CRN_NS] = {11.17,  139.0,  1.013e-4, 1.488,    1.
                                           4.966e-3, 0.9986, 3.296e-5, 1.869e-2, 1.367e-4,
                                           0.9996, 0.7755, 0.0,      1.0,      0.9992};
 
-// x / (1 - e^{-x/s}), whose limit at x = 0 is s; e receives e^{-x/s}
-__device__ __forceinline__ double rise_ratio(const cell::Coef &C, double x, double s, double &e)
+// x / (1 - e^{-x/s}), whose limit at x = 0 is s; e receives e^{-x/s}.  xe stands
+// in for x in the exponential: x held in its range
+__device__ __forceinline__ double rise_ratio(const cell::Coef &C, double x, double xe, double s, double &e)
 {
     double em1;
-    cell::exp_expm1(C, -x * (1.0 / s), e, em1);
+    cell::exp_expm1(C, -xe * (1.0 / s), e, em1);
     return x != 0.0 ? cell::div(x, -em1) : s;
 }
 // x / (e^{x/s} - 1), whose limit at x = 0 is s
-__device__ __forceinline__ double fall_ratio(const cell::Coef &C, double x, double s)
+__device__ __forceinline__ double fall_ratio(const cell::Coef &C, double x, double xe, double s)
 {
     double e, em1;
-    cell::exp_expm1(C, x * (1.0 / s), e, em1);
+    cell::exp_expm1(C, xe * (1.0 / s), e, em1);
     return x != 0.0 ? cell::div(x, em1) : s;
 }
 // 1 / (1 + e^{-x}), |x| < 700
@@ -578,7 +579,7 @@ __device__ __forceinline__ CrnCurrents crn_currents(const cell::Coef &C, const I
     const double na = y[0], k = y[1], ca = y[2];
     const double e_na = RT_F * log_ratio(C, 4.941642422609304, 4.344622201918654e-16, na), e_k = RT_F * log_ratio(C, 1.6863989535702286, 7.914947588915769e-17, k);
     const double e_ca = 0.5 * RT_F * log_ratio(C, 0.5877866649021191, -5.2182156685858313e-17, ca);
-    const double v = clip(V, 9e3), u = v * (1.0 / RT_F);   // every exponential stays in range
+    const double v = clip(V, 9e3), u = v * (1.0 / RT_F);   // every exponential but e_in stays in range
     CrnCurrents c;
     c.iNa = P.v[0] * gp.na * (V - e_na);
     c.iK1 = P.v[1] * (V - e_k) * logistic(C, -0.07 * (v + 80.0));
@@ -592,7 +593,7 @@ __device__ __forceinline__ CrnCurrents crn_currents(const cell::Coef &C, const I
     const double na_ratio = NAK_KM_NA * rcp(na);
     const double pump_na = rcp(1.0 + na_ratio * sqrt(na_ratio));
     c.iNaK = P.v[8] * pump_v * pump_na * (K_OUT / (K_OUT + NAK_KM_K));
-    const double e_in = exp_(C, NACA_GAMMA * u), e_out = exp_(C, (NACA_GAMMA - 1.0) * u);
+    const double e_in = exp_(C, NACA_GAMMA * (V * (1.0 / RT_F))), e_out = exp_(C, (NACA_GAMMA - 1.0) * u);
     const double km3 = NACA_KM_NA * NACA_KM_NA * NACA_KM_NA, nao3 = NA_OUT * NA_OUT * NA_OUT;
     c.iNaCa = div(P.v[9] * (e_in * (na * na * na) * CA_OUT - e_out * nao3 * ca),
                   (km3 + nao3) * (NACA_KM_CA + CA_OUT) * (1.0 + NACA_SAT * e_out));
@@ -613,7 +614,8 @@ __device__ double crn_point(const IonicParams &P, double dt, double V, double *y
     using namespace cell;
     const Coef C = make_coef();
     // ---- gates: Rush-Larsen with the rate 1/tau at V^k, which is held within
-    // +-3000 mV: every gate has saturated there and no exponential overflows ----
+    // +-3000 mV in the exponentials: none overflows, and every gate's limit and
+    // what they give of its rate have saturated there ----
     const double v = clip(V, 3000.0), ndt = -dt;
     // gates are loaded three ahead of their use
     double gy[15];
@@ -630,7 +632,7 @@ __device__ double crn_point(const IonicParams &P, double dt, double V, double *y
     CrnGates po, pn;
     double e, o0, o1, o2, n0, n1, n2;
     {   // fast sodium m, h, j from their opening and closing rates
-        const double am = 0.32 * rise_ratio(C, v + 47.13, 10.0, e), bm = 0.08 * exp_(C, v * (-1.0 / 11.0));
+        const double am = 0.32 * rise_ratio(C, V + 47.13, v + 47.13, 10.0, e), bm = 0.08 * exp_(C, v * (-1.0 / 11.0));
         n0 = adv(0, div(am, am + bm), am + bm, o0);
         double ah = 0.0, bh, aj = 0.0, bj;
         if (v < -40.0) {
@@ -641,7 +643,7 @@ __device__ double crn_point(const IonicParams &P, double dt, double V, double *y
             bj = 0.1212 * exp_(C, -0.01052 * v) * logistic(C, 0.1378 * (v + 40.14));
         } else {
             bh = (1.0 / 0.13) * logistic(C, (v + 10.66) * (1.0 / 11.1));
-            bj = 0.3 * exp_(C, -2.535e-7 * v) * logistic(C, 0.1 * (v + 32.0));
+            bj = 0.3 * exp_(C, -2.535e-7 * V) * logistic(C, 0.1 * (v + 32.0));
         }
         n1 = adv(1, div(ah, ah + bh), ah + bh, o1);
         n2 = adv(2, div(aj, aj + bj), aj + bj, o2);
@@ -666,17 +668,17 @@ __device__ double crn_point(const IonicParams &P, double dt, double V, double *y
         pn.kur = n0 * n0 * n0 * n1;
     }
     {   // rapid and slow delayed rectifiers
-        const double a_r = 0.0003 * rise_ratio(C, v + 14.1, 5.0, e);
-        const double b_r = 7.3898e-5 * fall_ratio(C, v - 3.3328, 5.1237);
+        const double a_r = 0.0003 * rise_ratio(C, V + 14.1, v + 14.1, 5.0, e);
+        const double b_r = 7.3898e-5 * fall_ratio(C, V - 3.3328, v - 3.3328, 5.1237);
         pn.kr = adv(7, logistic(C, (v + 14.1) * (1.0 / 6.5)), a_r + b_r, po.kr);
-        const double a_s = 4e-5 * rise_ratio(C, v - 19.9, 17.0, e);
-        const double b_s = 3.5e-5 * fall_ratio(C, v - 19.9, 9.0);
+        const double a_s = 4e-5 * rise_ratio(C, V - 19.9, v - 19.9, 17.0, e);
+        const double b_s = 3.5e-5 * fall_ratio(C, V - 19.9, v - 19.9, 9.0);
         pn.ks = adv(8, sqrt(logistic(C, (v - 19.9) * (1.0 / 12.7))), 2.0 * (a_s + b_s), po.ks);
     }
     {   // L-type calcium d, f, fCa
         const double x = v + 10.0;
         // 1/tau_d = 0.035 x (1 + e^{-x/6.24}) / (1 - e^{-x/6.24})
-        const double r_x = rise_ratio(C, x, 6.24, e), r_d = 0.035 * r_x * (1.0 + e);
+        const double r_x = rise_ratio(C, V + 10.0, x, 6.24, e), r_d = 0.035 * r_x * (1.0 + e);
         n0 = adv(9, logistic(C, x * (1.0 / 8.0)), r_d, o0);
         const double r_f = (0.0197 * exp_(C, -(0.0337 * 0.0337) * x * x) + 0.02) * (1.0 / 9.0);
         n1 = adv(10, logistic(C, (v + 28.0) * (-1.0 / 6.9)), r_f, o1);
@@ -715,9 +717,8 @@ __device__ double crn_point(const IonicParams &P, double dt, double V, double *y
         adv(12, on_u, 1.0 / 8.0, o0);
         const double v_inf = 1.0 - logistic(C, clip((fn - 6.835e-14) * (1.0 / 13.67e-16), 700.0));
         adv(13, v_inf, rcp(1.91 + 2.09 * on_u), o0);
-        const double xw = v - 7.9;
         // 1/tau_w = x (1 + 0.3 e^{-x/5}) / (6 (1 - e^{-x/5}))
-        const double r_x = rise_ratio(C, xw, 5.0, e), r_w = r_x * (1.0 + 0.3 * e) * (1.0 / 6.0);
+        const double r_x = rise_ratio(C, V - 7.9, v - 7.9, 5.0, e), r_w = r_x * (1.0 + 0.3 * e) * (1.0 / 6.0);
         adv(14, 1.0 - logistic(C, (v - 40.0) * (1.0 / 17.0)), r_w, o0);
     }
     // ---- forward Euler for the concentrations ----

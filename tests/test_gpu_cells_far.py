@@ -1,0 +1,38 @@
+"""Cell steps at potentials far beyond the ranges within which the kernels hold
+V in their exponentials, against the oracle, wherever the oracle's value is
+finite (its own exponentials overflow here and there).  Rates that grow with V
+itself go on growing, and the exchanger's current with e^{0.35 V F / R T}.  The
+largest exponent is 400 and carries a rounding of 400 x 2^-53, and some ten such
+factors meet in a product: bar 1e-11.
+"""
+import numpy as np
+import pytest
+
+import oracle.orc as orc
+
+pytestmark = pytest.mark.gpu
+
+FAR = (2401.0, 3001.0, 3500.0, 5000.0, 8000.0, 9001.0, 9340.0, 9490.0, 12000.0, 14900.0, 15001.0, 20000.0,
+       30000.0)
+
+
+@pytest.mark.parametrize("dt", [0.005, 0.02])
+@pytest.mark.parametrize("kind", ["tt", "crn"])
+def test_cell_step_far_potentials(kind, dt):
+    import torch
+    from paper_2510_12011_amd import sim
+    s = sim.Simulation(0)
+    s.set_ionic(kind)
+    V = np.array([v * f for v in FAR for f in (1.0, -1.0)])
+    _, u = orc.ionic_init(kind, V.size)
+    u = np.ascontiguousarray(u)
+    u_or = u.copy()
+    i_or = orc.ionic_step(kind, V, u_or, dt)
+    Vd, ud = torch.tensor(V, device="cuda:0"), torch.tensor(u, device="cuda:0")
+    i_gpu = s.ionic_step(dt, Vd, ud).cpu().numpy()
+    u_gpu = ud.cpu().numpy()
+    fin = np.isfinite(u_or)
+    assert fin.mean() > 0.9
+    np.testing.assert_allclose(u_gpu[fin], u_or[fin], rtol=1e-11, atol=1e-15)
+    fin = np.isfinite(i_or)
+    np.testing.assert_allclose(i_gpu[fin], i_or[fin], rtol=1e-11, atol=1e-11)
