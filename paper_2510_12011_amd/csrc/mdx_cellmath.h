@@ -122,6 +122,12 @@ __device__ __forceinline__ double log_ratio(const Coef &c, double hi, double lo,
     return y;
 }
 
+// x (hi + lo), lo what the rounding of a constant to hi leaves
+__device__ __forceinline__ double times(double x, double hi, double lo)
+{
+    return __builtin_fma(x, hi, x * lo);
+}
+
 // x held in [-lim, lim]; NaN stays
 __device__ __forceinline__ double clip(double x, double lim)
 {

@@ -368,9 +368,12 @@ __device__ __forceinline__ void tt_gates64(const cell::Coef &C, double V, double
     pn.ks = n0 * n0;
     // fast sodium m, h, j
     {
+        // (1/5 with what its rounding leaves: that times the exponents' size is a
+        // third of m's rms error, 3.4e-16 without at dt 0.005, 2.5e-16 with it,
+        // 3.1e-16 with library functions and divisions throughout)
         const double q = 1.0 + exp_(C, (-56.86 - v) * (1.0 / 9.03));
-        const double e1 = exp_(C, (-60.0 - v) * (1.0 / 5.0));
-        const double e2 = exp_(C, (v + 35.0) * (1.0 / 5.0)), e3 = exp_(C, (v - 50.0) * (1.0 / 200.0));
+        const double e1 = exp_(C, times(-60.0 - v, 0.2, -0x1.999999999999ap-57));
+        const double e2 = exp_(C, times(v + 35.0, 0.2, -0x1.999999999999ap-57)), e3 = exp_(C, (v - 50.0) * (1.0 / 200.0));
         ra = rcp(q * q);
         rb = rcp(2.0 + e2 + e3);
         n0 = adv(3, ra, 10.0 * (1.0 + e1) * (1.0 + e2) * (1.0 + e3) * rb, o0);
