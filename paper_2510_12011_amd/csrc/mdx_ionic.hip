@@ -517,7 +517,7 @@ constexpr double FARADAY = 96.4867;                   // C/mmol
 constexpr double CAP = 100.0;                         // pF
 constexpr double VOL_I = 13668.0, VOL_UP = 1109.52, VOL_REL = 96.48;   // um^3
 constexpr double K_OUT = 5.4, NA_OUT = 140.0, CA_OUT = 1.8;
-constexpr double NAK_KM_NA = 10.0, NAK_KM_K = 1.5;
+constexpr double NAK_KM_NA_3_2 = 31.622776601683793, NAK_KM_K = 1.5;   // 10 mM to the 3/2
 constexpr double NACA_KM_NA = 87.5, NACA_KM_CA = 1.38, NACA_SAT = 0.1, NACA_GAMMA = 0.35;
 constexpr double REL_RATE = 30.0, UP_KM = 0.00092, UP_CA_MAX = 15.0, TR_TAU = 180.0;
 constexpr double CMDN_TOT = 0.05, CMDN_KM = 0.00238, TRPN_TOT = 0.07, TRPN_KM = 0.0005;
@@ -593,8 +593,9 @@ __device__ __forceinline__ CrnCurrents crn_currents(const cell::Coef &C, const I
     c.iKs = P.v[4] * (gp.ks * gp.ks) * (V - e_k);
     c.iCaL = P.v[5] * gp.cal * (V - 65.0);
     const double pump_v = rcp(1.0 + 0.1245 * exp_(C, -0.1 * u) + 0.0365 * nak_sigma() * exp_(C, -u));
-    const double na_ratio = NAK_KM_NA * rcp(na);
-    const double pump_na = rcp(1.0 + na_ratio * sqrt(na_ratio));
+    // 1 / (1 + (K_m / Na)^{3/2}), defined without sodium too
+    const double na_3_2 = na * sqrt(na);
+    const double pump_na = na_3_2 * rcp(na_3_2 + NAK_KM_NA_3_2);
     c.iNaK = P.v[8] * pump_v * pump_na * (K_OUT / (K_OUT + NAK_KM_K));
     const double e_in = exp_(C, NACA_GAMMA * (V * (1.0 / RT_F))), e_out = exp_(C, (NACA_GAMMA - 1.0) * u);
     const double km3 = NACA_KM_NA * NACA_KM_NA * NACA_KM_NA, nao3 = NA_OUT * NA_OUT * NA_OUT;

@@ -36,3 +36,29 @@ def test_cell_step_far_potentials(kind, dt):
     np.testing.assert_allclose(u_gpu[fin], u_or[fin], rtol=1e-11, atol=1e-15)
     fin = np.isfinite(i_or)
     np.testing.assert_allclose(i_gpu[fin], i_or[fin], rtol=1e-11, atol=1e-11)
+
+
+@pytest.mark.parametrize("kind", ["tt", "crn"])
+def test_cell_step_states_of_zero(kind):
+    """One state of a cell at rest is zero: an infinite reversal potential where
+    it is a concentration.  States as the oracle's wherever those are numbers,
+    infinities included; the current, formed from states that may be infinite by
+    then, wherever that is finite."""
+    import torch
+    from paper_2510_12011_amd import sim
+    s = sim.Simulation(0)
+    s.set_ionic(kind)
+    n = orc.ionic_init(kind, 1)[1].shape[0]
+    V, u = orc.ionic_init(kind, n)
+    u = np.ascontiguousarray(u)
+    u[np.arange(n), np.arange(n)] = 0.0
+    u_or = u.copy()
+    i_or = orc.ionic_step(kind, V, u_or, 0.01)
+    Vd, ud = torch.tensor(V, device="cuda:0"), torch.tensor(u, device="cuda:0")
+    i_gpu = s.ionic_step(0.01, Vd, ud).cpu().numpy()
+    u_gpu = ud.cpu().numpy()
+    num = ~np.isnan(u_or)
+    np.testing.assert_allclose(u_gpu[num], u_or[num], rtol=1e-11, atol=1e-15)
+    fin = np.isfinite(i_or)
+    assert fin.sum() >= n - 3
+    np.testing.assert_allclose(i_gpu[fin], i_or[fin], rtol=1e-11, atol=1e-11)
