@@ -300,7 +300,13 @@ MDX_API mdx_status mdx_set_profiling(mdx_ctx *ctx, int32_t every_n);
  *                        own; FORMAT, LANES_PER_ROW and TILES_PER_GROUP set by
  *                        hand (not by mdx_autotune), PERSISTENT and a profiled
  *                        step select the streaming kernels, and GRAPH has no
- *                        effect on the single launch.
+ *                        effect on the single launch.  Launches of contexts
+ *                        in several threads run side by side where their
+ *                        workgroups find room, else in turn.  Where each of
+ *                        them fills the device (single meshes from about
+ *                        330,000 nodes with 7 entries a row, 65,000 with 15)
+ *                        and a solve takes an iteration or two, 0 is the
+ *                        faster choice for four threads and more.
  *   MDX_TUNE_ONCHIP_GIVE_UP  for tests of that fallback: e * 512 + w * 256 + g
  *                        has workgroup g of such a launch stop looking at its
  *                        e-th exchange of sums (e >= 1; 0, the default: none);

@@ -215,6 +215,7 @@ mdx_status run_batched(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double 
         times_due = false;
     };
 
+    OnchipCus cus(ctx);
     for (int64_t j = 0; j < n_steps; ++j) {
         const int64_t k = ctx->step;
         bool any_stim = false;
@@ -223,8 +224,6 @@ mdx_status run_batched(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double 
         const bool profiling = ctx->profile_every > 0 && k % ctx->profile_every == 0;
         const bool onchip = batch_onchip(ctx, profiling);
         const int C = onchip ? -1 : std::max(1, std::min(ctx->last_iters, max_iter));
-        std::unique_lock<std::mutex> one;
-        if (onchip) one = std::unique_lock<std::mutex>(onchip_mutex(ctx->device));
         // (six launches: a replay of them as a graph costs 8-10 us a step more)
         if (ctx->use_graph && !profiling && !onchip) {
             record_times();   // the replayed ionic update does not
@@ -242,6 +241,8 @@ mdx_status run_batched(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double 
                 HIPCHK(ie);
                 it = ctx->graphs.emplace(key, ex).first;
             }
+            if (ctx->persistent)
+                if (mdx_status e = cus.enter(-1, 1)) return e;
             HIPCHK(hipGraphLaunch(it->second, st));
         } else {
             if (!ionic_queued) {
@@ -252,6 +253,10 @@ mdx_status run_batched(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double 
                 enqueue_ionic(ctx, st, q, ctx->vec(0), ctx->vec(1), any_stim ? istim_dev : nullptr,
                               nullptr, times);
             }
+            if (onchip)
+                if (mdx_status e = cus.enter(ctx->onchip.groups, ctx->onchip.per_cu[2])) return e;
+            if (ctx->persistent)
+                if (mdx_status e = cus.enter(-1, 1)) return e;
             enqueue_batched_step(ctx, st, C, profiling);
         }
         HIPCHK(hipGetLastError());
@@ -275,7 +280,7 @@ mdx_status run_batched(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double 
             if (mdx_status e = wait_published(ctx, st, ctx->pub_seq)) return e;
             ctx->stats.host_wait_seconds +=
                 std::chrono::duration<double>(std::chrono::steady_clock::now() - w0).count();
-            one.unlock();
+            cus.ended();
             units = 0;
             for (int i = 0; i < ctx->n_inst; ++i)
                 if (ctx->bsc_host[i].gave_up) ctx->onchip_off = true;
@@ -286,6 +291,7 @@ mdx_status run_batched(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double 
             }
         } else {
             if (mdx_status e = fetch_bscalars(ctx, st)) return e;
+            cus.ended();
             if (ctx->persistent)
                 if (mdx_status e = persistent_fault(ctx)) return e;
         }
@@ -295,16 +301,19 @@ mdx_status run_batched(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double 
                 e0 = ctx->ev[2 * units];
                 e1 = ctx->ev[2 * units + 1];
             }
-            if (ctx->persistent)
+            if (ctx->persistent) {
+                if (mdx_status e = cus.enter(-1, 1)) return e;
                 launch_persistent(ctx, st, q, bp);
-            else
+            } else {
                 launch_b_iteration(st, ctx->seg, q.IM, bp, q.dinv32, q.p32, q.q32, q.delta, q.r32,
                                    q.part_pq, q.part_rz, q.bsc, e0, e1);
+            }
             launch_b_replacement(st, ctx->seg, q.P, bp, q.Av, X, q.delta, q.b, q.dinv, q.dinv32, q.r32,
                                  q.p32, q.part0, q.bsc, use_nt(ctx, 12.0 * slots(ctx)));
             HIPCHK(hipGetLastError());
             ++units;
             if (mdx_status e = fetch_bscalars(ctx, st)) return e;
+            cus.ended();
             if (ctx->persistent)
                 if (mdx_status e = persistent_fault(ctx)) return e;
         }

@@ -209,9 +209,24 @@ uint64_t hilbert_key(uint32_t x0, uint32_t x1, uint32_t x2, int bits);
 void hilbert_order(const std::vector<double> &xyz, int64_t p0, int64_t p1,
                    std::vector<int32_t> &out);
 void compact_columns(mdx_ctx *c);
-// held while a single-launch solve is in flight: two whose workgroups share
-// the CUs would each wait for workgroups that the other keeps off the chip
-std::mutex &onchip_mutex(int device);
+// A run's launches whose workgroups wait for one another: in flight beside
+// others' as far as the device's CUs reach, after them beyond that.
+class OnchipCus {
+public:
+    explicit OnchipCus(const mdx_ctx *c) : ctx_(c) {}
+    ~OnchipCus() { ended(); }
+    OnchipCus(const OnchipCus &) = delete;
+    OnchipCus &operator=(const OnchipCus &) = delete;
+    // before such a launch is queued: `groups` workgroups of which a CU can hold
+    // per_cu (groups < 0: the device is full of them); waits its turn
+    mdx_status enter(int groups, int per_cu);
+    bool twice(int groups, int per_cu) const;   // the device holds two such launches
+    void ended();   // it is known to have ended
+
+private:
+    const mdx_ctx *ctx_;
+    bool in_flight_ = false;
+};
 mdx_status build_onchip(mdx_ctx *c, hipStream_t st);
 SellView step_view(const mdx_ctx *c);
 int64_t sell_slot(const mdx_ctx *c, int64_t r, int32_t colv);
@@ -245,7 +260,6 @@ BatchPtrs batch_ptrs(mdx_ctx *c);
 BParams batch_params(const mdx_ctx *c);
 void launch_persistent(mdx_ctx *c, hipStream_t st, const BatchPtrs &q, const BParams &bp);
 mdx_status persistent_fault(mdx_ctx *c);
-void enqueue_batched_step(mdx_ctx *c, hipStream_t st, int iters, const double *istim, bool timed);
 mdx_status fetch_bscalars(mdx_ctx *c, hipStream_t st);
 bool all_done(const mdx_ctx *c);
 mdx_status run_batched(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double *v_out);

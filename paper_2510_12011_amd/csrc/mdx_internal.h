@@ -259,8 +259,10 @@ struct OnchipSolve {
 struct OnchipPlan {
     int groups = 0;                  // 0: the matrix does not fit
     int rows = 0, width = 0;
+    int xcd_cus = 0;                 // CUs of an XCD
     bool uneven = false;             // a block's rows sorted by length
     const void *shape[3] = {nullptr, nullptr, nullptr};   // FP64, FP32, batched (null: does not fit)
+    int per_cu[3] = {0, 0, 0};       // its workgroups that a CU can hold
     std::vector<int> first;          // first workgroup of each system, then the end
 };
 // n rows, the longest of `width` entries

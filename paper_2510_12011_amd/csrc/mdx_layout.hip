@@ -136,10 +136,88 @@ struct Bisection {
     }
 };
 
-std::mutex &onchip_mutex(int device)
+// Launches in flight.  Every workgroup of theirs finds a place: they go to the
+// XCDs in turn, so a launch of G puts at most ceil(G / 8) on an XCD, and together
+// these may be as many as the XCD's CUs hold of the largest kind (where a place is
+// missing, every CU would hold that many).  Launches are let in in the order they
+// come; a thread looks all the time, as where it waits for its own solve (with a
+// condition variable, or with the order left to the device by events between
+// streams, some 30 us more per step).  Time of a step of one context with 1, 4 and
+// 8 threads that have one each, streaming kernels -> one launch at a time -> this:
+// 9,261-node cube 283, 119, 66 -> 76, 75, 76 -> 77, 40, 21 us; 58,176-node slab
+// 328, 117, 116 -> 126, 123, 122 -> 126, 50, 52; four shells of 40,000 nodes 125,
+// 44, 43 -> 55, 57, 55 -> 57, 31, 31; 163,842-node surface (one iteration a step)
+// 48, 30, 21 -> 46, 47, 48 -> 46, 28, 22 to 30; 655,362 nodes, which fill the
+// device, 71, 50, 56 -> 64, 74, 76: there the streaming kernels are the better in
+// several threads, and only there.
+namespace {
+struct Device {
+    std::mutex m;
+    struct InFlight {
+        const mdx_ctx *ctx;
+        int groups;   // most on an XCD
+        int per_cu;   // of such workgroups a CU can hold
+    };
+    std::vector<InFlight> flight;
+    uint64_t next = 0, serving = 0;      // turns given, the one whose it is
+    std::atomic<uint64_t> changes{0};    // launches let in or ended
+};
+Device &device_of(const mdx_ctx *c)
 {
-    static std::mutex m[64];
-    return m[device & 63];
+    static Device d[64];
+    return d[c->device & 63];
+}
+}  // namespace
+
+// most workgroups of a launch on an XCD
+static int on_xcd(int groups) { return (groups + NXCD - 1) / NXCD; }
+
+bool OnchipCus::twice(int groups, int per_cu) const
+{
+    return 2 * on_xcd(groups) <= ctx_->onchip.xcd_cus * per_cu;
+}
+
+mdx_status OnchipCus::enter(int groups, int per_cu)
+{
+    Device &d = device_of(ctx_);
+    std::unique_lock<std::mutex> lock(d.m);
+    d.flight.reserve(d.flight.size() + 1);
+    const int cus = ctx_->onchip.xcd_cus, n = groups < 0 ? cus : on_xcd(groups);
+    const uint64_t turn = d.next++;
+    for (;;) {
+        int all = n, hold = per_cu;
+        for (const Device::InFlight &o : d.flight) {
+            all += o.groups;
+            hold = std::min(hold, o.per_cu);
+        }
+        if (d.serving == turn && (d.flight.empty() || all <= cus * hold)) break;
+        const uint64_t seen = d.changes;
+        lock.unlock();
+        for (unsigned k = 1; d.changes == seen; ++k) {
+            __builtin_ia32_pause();
+            if (k % 256 == 0) std::this_thread::yield();
+        }
+        lock.lock();
+    }
+    d.flight.push_back({ctx_, n, per_cu});
+    d.serving++;
+    d.changes++;
+    in_flight_ = true;
+    return MDX_OK;
+}
+
+void OnchipCus::ended()
+{
+    if (!in_flight_) return;
+    Device &d = device_of(ctx_);
+    std::lock_guard<std::mutex> lock(d.m);
+    for (size_t i = 0; i < d.flight.size(); ++i)
+        if (d.flight[i].ctx == ctx_) {
+            d.flight.erase(d.flight.begin() + i);
+            break;
+        }
+    in_flight_ = false;
+    d.changes++;
 }
 
 // Builds the blocks' maps and copies them to the device; leaves onchip_ready

@@ -44,8 +44,8 @@
 // (write-through past the XCD's L2, read past it) and complete (vmcnt) before
 // the slot is written, so no cache is flushed or invalidated.
 //
-// The wait needs every workgroup resident: at most one per CU is launched and
-// the host lets one such launch per device be in flight.  Polls are bounded:
+// The wait needs every workgroup resident: at most one per CU is launched, and
+// launches run together only as far as the CUs reach (OnchipCus).  Polls are bounded:
 // where other work keeps a workgroup off the chip for long, the launch gives
 // up and changes nothing but scratch and x; the host then forms the step's
 // right-hand side again and solves it with the streaming kernels.
@@ -613,9 +613,13 @@ struct Ahead {
     }
 };
 
+// The small shapes need few registers more than the 128 with which a CU holds two
+// workgroups, and so two such launches find room where one would (no spills).
+constexpr int waves_per_simd(int W, int R) { return W * R <= 15 ? 4 : 2; }
+
 // ---- plain FP64 ------------------------------------------------------------
 template <int W, int R>
-__global__ __launch_bounds__(OB) void k_onchip(OnchipSolve a)
+__global__ __launch_bounds__(OB, waves_per_simd(W, R)) void k_onchip(OnchipSolve a)
 {
     constexpr int LQ = (W + 3) / 4, own = R * OB;
     __shared__ ExchangeLds xl;
@@ -1240,6 +1244,7 @@ OnchipPlan onchip_plan(int device, int64_t n, int width)
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
         return p;
+    p.xcd_cus = std::max(1, cus / NXCD);
     const int64_t cap = std::min(cus, kOnchipGroups);
     if (cap < 1 || n < 1) return p;
     p.width = width <= 7 ? 7 : width <= 15 ? 15 : 31;
@@ -1255,8 +1260,10 @@ OnchipPlan onchip_plan(int device, int64_t n, int width)
     for (int i = 0; i < 2; ++i) {
         int resident = 0;
         if (s[i] && hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, s[i]->k, OB, 0) == hipSuccess &&
-            resident >= 1)
+            resident >= 1) {
             p.shape[i] = s[i];
+            p.per_cu[i] = resident;
+        }
     }
     if (p.shape[0] || p.shape[1]) p.groups = (int)std::min(cap, (n + OB - 1) / OB);
     p.first = {0, p.groups};
@@ -1269,6 +1276,7 @@ OnchipPlan onchip_plan_batch(int device, const std::vector<int64_t> &n, int widt
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
         return p;
+    p.xcd_cus = std::max(1, cus / NXCD);
     const int64_t cap = std::min(cus, kOnchipGroups);
     p.width = width <= 7 ? 7 : width <= 15 ? 15 : 39;
     if (width > 39 || (int64_t)n.size() > cap) return p;
@@ -1285,6 +1293,7 @@ OnchipPlan onchip_plan_batch(int device, const std::vector<int64_t> &n, int widt
             return p;
         p.rows = r;
         p.shape[2] = s;
+        p.per_cu[2] = resident;
         for (int64_t k : n) {
             p.first.push_back(p.groups);
             p.groups += (int)((k + r * OB - 1) / (r * OB));

@@ -10,8 +10,6 @@
 // instruction.
 #include "mdx_host.h"
 
-#include <mutex>
-
 extern "C" {
 
 mdx_status mdx_run(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double *v_out)
@@ -86,6 +84,7 @@ mdx_status mdx_run(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double *v_o
     const bool onchip_run = ctx->onchip_ready && ctx->onchip.shape[mixed ? 1 : 0] &&
                             ctx->onchip_polls > 0 && ctx->iter_scheme == 0 &&
                             ctx->max_groups == kMaxGroups && ctx->spmv_max_groups == kPartialCap;
+    OnchipCus cus(ctx);
     OnchipSolve os{};
     os.map = ctx->onchip_map;
     os.z = pbuf[1];
@@ -174,6 +173,13 @@ mdx_status mdx_run(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double *v_o
                                 kvp_out, p0_fp64, nt_rhs);
             if (!onchip) launch_init_finalize(st, T, part0, sp.rel_mode, sc);
         };
+        // a solve that fills the device: its step's passes too, or those of other
+        // threads' steps would keep its last workgroups off the CUs on which its
+        // first ones wait (four threads, 655,362 nodes: 160 us a step, so 81)
+        const int per_cu = ctx->onchip.per_cu[mixed ? 1 : 0];
+        const bool fills = onchip && !cus.twice(ctx->onchip.groups, per_cu);
+        if (fills)
+            if (mdx_status e = cus.enter(ctx->onchip.groups, per_cu)) return e;
         queue_rhs();
         ctx->kvp_valid = want_kvp;
 
@@ -208,13 +214,15 @@ mdx_status mdx_run(mdx_ctx *ctx, int64_t n_steps, int64_t out_every, double *v_o
             return MDX_OK;
         };
         if (onchip) {
-            std::lock_guard<std::mutex> one(onchip_mutex(ctx->device));
             os.x = X;
             ctx->onchip_launch = ctx->onchip_launch % 0x7fffffffu + 1;
             os.launch = ctx->onchip_launch;
             os.seq = ++ctx->pub_seq;   // the launch publishes the scalars itself
+            if (!fills)
+                if (mdx_status e = cus.enter(ctx->onchip.groups, per_cu)) return e;
             launch_onchip(st, ctx->onchip, mixed, os);
             if (mdx_status e = end_chunk()) return e;
+            cus.ended();
             if (ctx->sc_host->onchip_gave_up) {   // what is queued behind it does not act
                 ctx->onchip_off = true;
                 onchip = false;
