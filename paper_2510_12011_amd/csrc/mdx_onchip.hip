@@ -110,12 +110,13 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 // (1: gave up) from then on.
 __device__ __forceinline__ bool settle(uint32_t *word, unsigned launch, bool gave_up)
 {
-    uint32_t now = ld_agent(word);
-    while (now >> 1 != launch)   // at most one other entry gets in between
+    uint32_t now = (launch - 1) << 1;   // the last launch's, as a rule: one round trip
+    do {
         if (__hip_atomic_compare_exchange_strong(word, &now, launch << 1 | (gave_up ? 1u : 0u),
                                                  __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT))
             return gave_up;
+    } while (now >> 1 != launch);   // at most one other entry gets in between
     return now & 1;
 }
 
