@@ -4,10 +4,9 @@
 // iteration layouts (lanes per row, 4-entry chunks, CSR), and the intake of
 // a mesh or a batch of meshes.
 #include "mdx_host.h"
+#include "mdx_parallel.h"
 
-#include <exception>
 #include <mutex>
-#include <system_error>
 #include <thread>
 
 namespace mdx {
@@ -34,34 +33,6 @@ void compact_columns(mdx_ctx *c)
             off[e] = (uint16_t)(c->col_sell[e] - base[sl]);
     c->col16.swap(off);
     c->cbase.swap(base);
-}
-
-// Runs f(k) for k in [0, n) on a few host threads (setup only); an exception
-// (host memory) ends the call's other work and is passed on.
-template <class F>
-static void parallel_for(int n, F &&f)
-{
-    const int nt = (int)std::max(1u, std::min({8u, std::thread::hardware_concurrency(), (unsigned)n}));
-    std::atomic<int> next{0};
-    std::exception_ptr err;
-    std::mutex mu;
-    auto work = [&]() {
-        try {
-            for (int k; (k = next.fetch_add(1)) < n;) f(k);
-        } catch (...) {
-            std::lock_guard<std::mutex> g(mu);
-            err = std::current_exception();
-            next = n;
-        }
-    };
-    std::vector<std::thread> th;
-    try {
-        for (int i = 1; i < nt; ++i) th.emplace_back(work);
-    } catch (const std::system_error &) {   // no more threads: those there are do it
-    }
-    work();
-    for (std::thread &t : th) t.join();
-    if (err) std::rethrow_exception(err);
 }
 
 // Blocks of the single-launch solve: the rows cut into `groups` parts of equal
