@@ -941,6 +941,22 @@ mdx_status set_mesh_impl(mdx_ctx *ctx, int32_t n_inst, const int64_t *node_ptr, 
         }
     }
 
+    // the single-launch solve's shape: before the context changes, and with the
+    // thread's device as it was
+    OnchipPlan plan;
+    if (ctx->device >= 0) {
+        int width = 0, cur = ctx->device;
+        for (int64_t sl = 0; sl < nslices; ++sl)
+            width = std::max(width, (int)((sptr[sl + 1] - sptr[sl]) / SLICE));
+        std::vector<int64_t> nodes(n_inst);
+        for (int32_t i = 0; i < n_inst; ++i) nodes[i] = node_ptr[i + 1] - node_ptr[i];
+        HIPCHK(hipGetDevice(&cur));
+        if (cur != ctx->device) HIPCHK(hipSetDevice(ctx->device));
+        plan = batched ? onchip_plan_batch(ctx->device, nodes, width)
+                       : onchip_plan(ctx->device, n_nodes, width);
+        if (cur != ctx->device) HIPCHK(hipSetDevice(cur));
+    }
+
     ctx->n = n_nodes;
     ctx->m = n_tets;
     ctx->npe = npe;
@@ -962,20 +978,7 @@ mdx_status set_mesh_impl(mdx_ctx *ctx, int32_t n_inst, const int64_t *node_ptr, 
     ctx->rowlen.swap(rowlen);
     compact_columns(ctx);
     ctx->batched = batched;
-    ctx->onchip = OnchipPlan{};
-    if (ctx->device >= 0) {
-        int width = 0;
-        for (int64_t sl = 0; sl < nslices; ++sl)
-            width = std::max(width, (int)((ctx->slice_ptr[sl + 1] - ctx->slice_ptr[sl]) / SLICE));
-        HIPCHK(hipSetDevice(ctx->device));
-        if (batched) {
-            std::vector<int64_t> nodes(n_inst);
-            for (int32_t i = 0; i < n_inst; ++i) nodes[i] = node_ptr[i + 1] - node_ptr[i];
-            ctx->onchip = onchip_plan_batch(ctx->device, nodes, width);
-        } else {
-            ctx->onchip = onchip_plan(ctx->device, n_nodes, width);
-        }
-    }
+    ctx->onchip = std::move(plan);
     ctx->n_inst = n_inst;
     ctx->inst_node_ptr.assign(node_ptr, node_ptr + n_inst + 1);
     ctx->inst_row0.swap(row0);
