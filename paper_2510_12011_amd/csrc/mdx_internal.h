@@ -468,7 +468,7 @@ void launch_b_spmv(hipStream_t s, const SegTiling &t, const IterMatrix &A,
 
 // ---- solver (mdx_solver.hip) ---------------------------------------------
 void launch_fill(hipStream_t s, int64_t n, double v, double *x);
-void launch_reorder(hipStream_t s, int64_t n, const int32_t *at, const double *x, double *y);
+hipError_t launch_reorder(hipStream_t s, int64_t n, const int32_t *at, const double *x, double *y);
 void launch_stim_add(hipStream_t s, int64_t n_idx, const int32_t *idx, double amp, double *istim);
 // b, x0, r0 = b - A x0 and the partials (r.z, z.z, |D^-1 b|^2), z = D^-1 r
 // skip (optional): the kernels return at once while *skip is non-zero (the

@@ -457,8 +457,8 @@ mdx_status copy_vec_out(mdx_ctx *ctx, const double *dsrc, double *host)
     int cur = ctx->device;
     HIPCHK(hipGetDevice(&cur));
     if (cur != ctx->device) HIPCHK(hipSetDevice(ctx->device));
-    launch_reorder(ctx->stream, ctx->n, ctx->dev<int32_t>(ctx->L.iperm), dsrc, ctx->stage_dev);
-    const hipError_t e = hipGetLastError();
+    const hipError_t e =   // the launch's own: not what another call may have left
+        launch_reorder(ctx->stream, ctx->n, ctx->dev<int32_t>(ctx->L.iperm), dsrc, ctx->stage_dev);
     if (cur != ctx->device) HIPCHK(hipSetDevice(cur));
     HIPCHK(e);
     HIPCHK(hipStreamSynchronize(ctx->stream));

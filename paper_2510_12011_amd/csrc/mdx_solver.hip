@@ -386,9 +386,11 @@ void launch_fill(hipStream_t s, int64_t n, double v, double *x)
     if (n > 0) hipLaunchKernelGGL(k_fill, dim3(blocks_for(n)), dim3(256), 0, s, n, v, x);
 }
 
-void launch_reorder(hipStream_t s, int64_t n, const int32_t *at, const double *x, double *y)
+hipError_t launch_reorder(hipStream_t s, int64_t n, const int32_t *at, const double *x, double *y)
 {
-    if (n > 0) hipLaunchKernelGGL(k_reorder, dim3(blocks_for(n)), dim3(256), 0, s, n, at, x, y);
+    if (n <= 0) return hipSuccess;
+    void *args[] = {&n, &at, &x, &y};
+    return hipLaunchKernel((const void *)k_reorder, dim3(blocks_for(n)), dim3(256), args, 0, s);
 }
 
 void launch_stim_add(hipStream_t s, int64_t n_idx, const int32_t *idx, double amp, double *istim)
