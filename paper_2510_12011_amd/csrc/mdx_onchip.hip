@@ -959,7 +959,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
 // Solve of a step, streaming kernels -> this (and the whole step, with the
 // ionic update's fused passes): 12 unstructured shells of 232,472 nodes in
 // all, 4.0 iterations, 130 -> 47 us (187 -> 96); 8 surfaces of 1,310,736, 1.8
-// iterations, 165 -> 69 (280 -> 171; 79 with 12 rows a thread where 11 do).
+// iterations, 165 -> 69 (280 -> 171).
 // Bound by one read of the values and columns (23 and 45 MB), the replacement's
 // read of the FP64 values and some 3 us per exchange.
 //
@@ -1206,28 +1206,43 @@ struct OnchipBatchShape {
     int width, rows;
     void (*k)(OnchipBatch);
 };
+// Every count of rows a thread from 1 on: a block's time goes with its count, and
+// a mesh that needs 5 loses a sixth with 6.  The last count of each row length is
+// the last whose block fits the LDS, with spills of at most 152 bytes a lane or,
+// for 15 entries, r and the correction kept away (8 to 10 rows).  In FP64 the
+// lists end earlier: 7 rows of 7 entries would fit (249 registers); 8 of 7, 5 of
+// 15 and 3 of 31 would spill 44, 124 and 256 bytes.  None of these was timed.
+// Above the last count the streaming kernels run, as for single meshes whose
+// longest row has more than 31 entries and for batches beyond 39 (quads of
+// columns and values in registers grow with the longest row of all; the batch's
+// 39 pays for itself by forming only the quads that a wavefront's rows have).
 #define MDX_OC(w, r) {w, r, k_onchip<w, r>}
 const OnchipShape kShapes64[] = {
-    MDX_OC(7, 1),  MDX_OC(7, 2),  MDX_OC(7, 3),  MDX_OC(7, 4),  MDX_OC(7, 6),  MDX_OC(15, 1),
-    MDX_OC(15, 2), MDX_OC(15, 3), MDX_OC(15, 4), MDX_OC(31, 1), MDX_OC(31, 2),
+    MDX_OC(7, 1),  MDX_OC(7, 2),  MDX_OC(7, 3),  MDX_OC(7, 4),  MDX_OC(7, 5),  MDX_OC(7, 6),
+    MDX_OC(15, 1), MDX_OC(15, 2), MDX_OC(15, 3), MDX_OC(15, 4), MDX_OC(31, 1), MDX_OC(31, 2),
 };
 #undef MDX_OC
 #define MDX_OC(w, r) {w, r, k_onchip32<w, r, (w + 3) / 4, false>}
+#define MDX_OC_AWAY(w, r) {w, r, k_onchip32<w, r, 3, true>}
 const OnchipShape kShapes32[] = {
-    MDX_OC(7, 1),  MDX_OC(7, 2),  MDX_OC(7, 3),  MDX_OC(7, 4),  MDX_OC(7, 6),  MDX_OC(7, 7),
-    MDX_OC(7, 8),  MDX_OC(7, 10), MDX_OC(7, 12), MDX_OC(15, 1), MDX_OC(15, 2), MDX_OC(15, 3),
-    MDX_OC(15, 4), MDX_OC(15, 6), MDX_OC(15, 7), {15, 8, k_onchip32<15, 8, 3, true>},
-    {15, 10, k_onchip32<15, 10, 3, true>}, MDX_OC(31, 1), MDX_OC(31, 2), MDX_OC(31, 3), MDX_OC(31, 4),
+    MDX_OC(7, 1),       MDX_OC(7, 2),       MDX_OC(7, 3),        MDX_OC(7, 4),  MDX_OC(7, 5),
+    MDX_OC(7, 6),       MDX_OC(7, 7),       MDX_OC(7, 8),        MDX_OC(7, 9),  MDX_OC(7, 10),
+    MDX_OC(7, 11),      MDX_OC(7, 12),      MDX_OC(15, 1),       MDX_OC(15, 2), MDX_OC(15, 3),
+    MDX_OC(15, 4),      MDX_OC(15, 5),      MDX_OC(15, 6),       MDX_OC(15, 7), MDX_OC_AWAY(15, 8),
+    MDX_OC_AWAY(15, 9), MDX_OC_AWAY(15, 10), MDX_OC(31, 1),      MDX_OC(31, 2), MDX_OC(31, 3),
+    MDX_OC(31, 4),
 };
+#undef MDX_OC_AWAY
 #undef MDX_OC
 #define MDX_OCB(w, r) {w, r, k_onchip_batch<w, r, (w > 15)>}
 const OnchipBatchShape kShapesB[] = {
-    MDX_OCB(7, 1),  MDX_OCB(7, 2),  MDX_OCB(7, 3),  MDX_OCB(7, 4),  MDX_OCB(7, 6),  MDX_OCB(7, 7),
-    MDX_OCB(7, 8),  MDX_OCB(7, 10), MDX_OCB(7, 11), MDX_OCB(7, 12), MDX_OCB(15, 1), MDX_OCB(15, 2), MDX_OCB(15, 3),
-    MDX_OCB(15, 4), MDX_OCB(15, 6), MDX_OCB(15, 7), MDX_OCB(39, 1), MDX_OCB(39, 2), MDX_OCB(39, 3),
+    MDX_OCB(7, 1),  MDX_OCB(7, 2),  MDX_OCB(7, 3),  MDX_OCB(7, 4),  MDX_OCB(7, 5),  MDX_OCB(7, 6),
+    MDX_OCB(7, 7),  MDX_OCB(7, 8),  MDX_OCB(7, 9),  MDX_OCB(7, 10), MDX_OCB(7, 11), MDX_OCB(7, 12),
+    MDX_OCB(15, 1), MDX_OCB(15, 2), MDX_OCB(15, 3), MDX_OCB(15, 4), MDX_OCB(15, 5), MDX_OCB(15, 6),
+    MDX_OCB(15, 7), MDX_OCB(39, 1), MDX_OCB(39, 2), MDX_OCB(39, 3),
 };
 #undef MDX_OCB
-constexpr int kRows[] = {1, 2, 3, 4, 6, 7, 8, 10, 11, 12};
+constexpr int kMostRows = 12;
 
 template <class S, int N>
 const S *pick(const S (&s)[N], int width, int rows)
@@ -1251,12 +1266,8 @@ OnchipPlan onchip_plan(int device, int64_t n, int width)
     p.width = width <= 7 ? 7 : width <= 15 ? 15 : 31;
     if (width > 31) return p;
     const int64_t need = (n + cap * OB - 1) / (cap * OB);
-    for (int r : kRows)
-        if (r >= need && (pick(kShapes64, p.width, r) || pick(kShapes32, p.width, r))) {
-            p.rows = r;
-            break;
-        }
-    if (p.rows == 0) return p;
+    if (need > kMostRows) return p;
+    p.rows = (int)need;
     const OnchipShape *s[2] = {pick(kShapes64, p.width, p.rows), pick(kShapes32, p.width, p.rows)};
     for (int i = 0; i < 2; ++i) {
         int resident = 0;
@@ -1283,7 +1294,7 @@ OnchipPlan onchip_plan_batch(int device, const std::vector<int64_t> &n, int widt
     if (width > 39 || (int64_t)n.size() > cap) return p;
     p.uneven = p.width == 39;
     // the fewest rows a thread with which every instance has workgroups enough
-    for (int r : kRows) {
+    for (int r = 1; r <= kMostRows; ++r) {
         int64_t need = 0;
         for (int64_t k : n) need += (k + r * OB - 1) / (r * OB);
         if (need > cap) continue;
