@@ -119,3 +119,32 @@ def test_batched_shape_matches_streaming_kernels(mesh, rows):
                             n_steps=40)
     print("[case] batch", mesh.__name__, rows, spec.n_nodes, flush=True)
     assert _two_ways(sim.batch_from_spec(spec), 8) <= 1e-8
+
+
+def test_batch_against_each_instance_alone():
+    """The rows a thread, and with them an instance's blocks, follow from the whole
+    batch: 4 here, and alone 1 (the small box) and 2.  Another order of the FP64
+    sums may round alpha to the neighbouring FP32 value, which moves a step's
+    correction (some 1e-2 of V) by 6e-8 of itself: bar 1e-8 of the norm."""
+    from paper_2510_12011_amd import sim
+    inst = []
+    for k, (nx, ny, nz) in enumerate([(70, 56, 50), (9, 8, 7), (70, 56, 50)]):
+        one = inputs.small_box(nx=nx, ny=ny, nz=nz, lx=0.15 * nx, ly=0.15 * ny, lz=0.15 * nz, seed=k)
+        inst.append(inputs.Instance(one.mesh, 0.17, 0.019 * (1 + k), one.stimuli))
+
+    def run(instances):
+        spec = inputs.BatchSpec(name="boxes", instances=instances, chi=140.0, cm=0.01, theta=0.5, ionic="ms",
+                                dt=0.02, n_steps=40)
+        print("[case] batch of", len(instances), spec.n_nodes, flush=True)
+        s = sim.batch_from_spec(spec)
+        v, st = s.run(40, out_every=10)
+        assert st == 0
+        return np.asarray(v), np.asarray(s.instance_iterations(40)), spec.node_ptr()
+
+    v, it, ptr = run(inst)
+    for k, one in enumerate(inst):
+        w, jt, _ = run([one])
+        part = v[:, ptr[k]:ptr[k + 1]]
+        print("  instance", k, "rel", np.linalg.norm(part - w) / np.linalg.norm(w), flush=True)
+        assert np.linalg.norm(part - w) <= 1e-8 * np.linalg.norm(w)
+        assert np.abs(it[:, k] - jt[:, 0]).max() <= 1
