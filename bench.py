@@ -17,12 +17,15 @@ atrial surface stand-in: 655,362-node closed triangle surface), batched_surface
 (16 closed triangle surfaces advanced together).
 
 Also reported, as one JSON line:
-  roofline      the dominant kernel (PCG SpMV with fused p.q): algorithmic
+  roofline      the streaming iteration's SpMV with fused p.q: algorithmic
                 bytes per launch (12 B per structural nonzero + 16 B per row)
                 over its mean duration, measured with HIP events attached to
-                every dispatch of that kernel in the timed region, against
+                its dispatches in a further run after the timed one, against
                 8 TB/s; beside it a measured triad ceiling (c = a + 1.5 b
-                over 1 GiB arrays)
+                over 1 GiB arrays).  A step with such events solves with the
+                streaming kernels; the timed run's steps, which have none, do
+                so only where the matrix does not fit on chip (elsewhere one
+                launch keeps it there and reads it once per solve)
   cpu_baseline  the CPU oracle (plain FP64 C, OpenMP) timed on this host on a
                 bounded prefix of the same workload, and on one thread over a
                 shorter prefix
@@ -95,6 +98,22 @@ def workload(name):
                 "cell, isotropic 0.4 S/m, dt 0.01 ms, apex stimulus, plain FP64, atol 1e-5 and "
                 "rtol 1e-5 of ||D^-1 b||", "fp64")
     raise SystemExit(f"unknown workload {name}")
+
+
+SPMV_RUN = ("a further run after the timed one: its steps solve with the streaming kernels, the timed "
+            "run's in one launch where the matrix fits on chip")
+
+
+def spmv_run(s, steps, every):
+    """The counters of the SpMV launches of every `every`-th of `steps` further steps."""
+    st0 = s.stats()
+    s.set_profiling(every)
+    s.run(steps)
+    s.set_profiling(0)
+    st = s.stats()
+    out = {k: st[k] - st0[k] for k in ("spmv_timed", "spmv_seconds", "spmv_bytes", "spmv_work")}
+    out["nnz"] = st["nnz"]
+    return out
 
 
 def cpu_baseline(spec, steps, threads=None):
@@ -254,7 +273,7 @@ def learned_workload(args):
     def restore(s, c):
         s.set_state(c["V"], c["Vprev"], c["u"], c["lat"], c["lrt"], c["step"])
 
-    def timed(precision, ws, rtol, site=held[0], profile=False):
+    def timed(precision, ws, rtol, site=held[0]):
         s = context(precision, ws)
         s.set_solver(0.0, rtol, 1, 1000, ws, sim.PRECISION[precision], 50)
         c = ckpt[site]
@@ -262,7 +281,6 @@ def learned_workload(args):
             restore(s, c)
             s.run(args.warmup)
         restore(s, c)
-        s.set_profiling(args.profile_every if profile else 0)
         st0 = s.stats()
         torch.cuda.synchronize()
         t1 = time.perf_counter()
@@ -270,12 +288,9 @@ def learned_workload(args):
         torch.cuda.synchronize()
         el = time.perf_counter() - t1
         st1 = s.stats()
-        s.set_profiling(0)
         it = s.iterations(args.steps)
         state = s.get_state()
-        st = {k: st1[k] - st0[k] for k in ("spmv_timed", "spmv_seconds", "spmv_bytes",
-                                           "fallbacks")}
-        st["nnz"] = st1["nnz"]
+        st = {"fallbacks": st1["fallbacks"] - st0["fallbacks"]}
         name = {L.MDX_WS_MLP: "MLP", L.MDX_WS_EXTRAP: "extrapolated", L.MDX_WS_PREV: "previous"}[ws]
         print(f"[bench] site {site} {precision} warm start {name}, rtol {rtol:g}: {args.steps} "
               f"steps in {el:.3f} s, mean CG iterations {it.mean():.2f}, fallbacks "
@@ -291,7 +306,7 @@ def learned_workload(args):
         "learned_fp64_1e-8": timed("fp64", L.MDX_WS_MLP, 1e-8),
         "extrap_mixed_1e-8": timed("mixed", L.MDX_WS_EXTRAP, 1e-8),
         "prev_mixed_1e-8": timed("mixed", L.MDX_WS_PREV, 1e-8),
-        "learned_mixed_3e-9": timed("mixed", L.MDX_WS_MLP, eq, profile=True),
+        "learned_mixed_3e-9": timed("mixed", L.MDX_WS_MLP, eq),
         "plain_fp64_3e-9": timed("fp64", L.MDX_WS_EXTRAP, eq),
         "extrap_mixed_3e-9": timed("mixed", L.MDX_WS_EXTRAP, eq),
     }
@@ -343,7 +358,10 @@ def learned_workload(args):
         print("[bench] WARNING: a run at 3e-9 missed the accuracy bar (1e-5, one dt): "
               "the speed-ups below are not at equal accuracy", flush=True)
     value = lrn["rate"]
-    st = lrn["stats"]
+    s = context("mixed", L.MDX_WS_MLP)
+    s.set_solver(0.0, eq, 1, 1000, L.MDX_WS_MLP, sim.PRECISION["mixed"], 50)
+    restore(s, ckpt[held[0]])
+    st = dict(spmv_run(s, min(args.steps, 100), args.profile_every), fallbacks=lrn["stats"]["fallbacks"])
     launches = max(1, st["spmv_timed"])
     spmv_avg = st["spmv_seconds"] / launches
     bytes_avg = st["spmv_bytes"] / launches
@@ -386,7 +404,7 @@ def learned_workload(args):
                      "traffic_source": os.path.relpath(TRAFFIC_PROFILE, ROOT),
                      "bytes_per_launch": bytes_avg,
                      "avg_launch_us": 1e6 * spmv_avg, "launches_timed": st["spmv_timed"],
-                     "sampled_every_n_steps": args.profile_every,
+                     "sampled_every_n_steps": args.profile_every, "measured_in": SPMV_RUN,
                      "cache_resident": bool(6 * st["nnz"] < 256e6)},
     }
     for s in ctxs.values():
@@ -488,7 +506,6 @@ def nversion_workload(args):
     for h in (0.5, 0.2, 0.1):
         spec = inputs.nversion(h, 60000)
         s = sim.from_spec(spec)
-        s.set_profiling(args.profile_every)
         torch.cuda.synchronize()
         t0 = time.perf_counter()
         t, steps, _ = nv.run_to_activation(s, spec)
@@ -502,7 +519,7 @@ def nversion_workload(args):
         if h == 0.1:
             n, steps01, el01 = spec.mesh.n_nodes, steps, el
             rate = n * steps / el
-            st = s.stats()
+            st = spmv_run(s, 100, args.profile_every)
     launches = max(1, st["spmv_timed"])
     spmv_avg = st["spmv_seconds"] / launches
     bytes_avg = st["spmv_bytes"] / launches
@@ -520,7 +537,7 @@ def nversion_workload(args):
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": None, "bytes_per_launch": bytes_avg,
                      "avg_launch_us": 1e6 * spmv_avg, "launches_timed": st["spmv_timed"],
-                     "sampled_every_n_steps": args.profile_every,
+                     "sampled_every_n_steps": args.profile_every, "measured_in": SPMV_RUN,
                      "cache_resident": bool(10 * st["nnz"] < 256e6)},
     }
     print(json.dumps(out), flush=True)
@@ -572,14 +589,13 @@ def batched_workload(args):
         s.run(args.warmup)
         s.prepare(b.dt)           # back to rest (also resets the layout choice)
     install()
-    s.set_profiling(args.profile_every)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     _, status = s.run(args.steps)
     torch.cuda.synchronize()
     elapsed = time.perf_counter() - t0
-    st = s.stats()
     its = s.instance_iterations(args.steps)
+    st = spmv_run(s, min(args.steps, 100), args.profile_every)
     print(f"[bench] {args.steps} steps in {elapsed:.3f} s, mean CG iterations per instance "
           f"{its.mean():.2f} (max {its.max()}), status {status}", flush=True)
     launches = st["spmv_timed"]
@@ -616,7 +632,8 @@ def batched_workload(args):
                      "bytes_per_launch": bytes_avg,
                      "avg_launch_us": 1e6 * spmv_avg if launches else None,
                      "launches_timed": st["spmv_timed"],
-                     "sampled_every_n_steps": args.profile_every, "cache_resident": False},
+                     "sampled_every_n_steps": args.profile_every, "measured_in": SPMV_RUN,
+                     "cache_resident": False},
     }
     if not args.no_cpu:
         from oracle import orc
@@ -651,7 +668,8 @@ def main():
                              "batched_surface"])
     ap.add_argument("--cpu-steps", type=int, default=40)
     ap.add_argument("--no-cpu", action="store_true")
-    ap.add_argument("--profile-every", type=int, default=10)
+    ap.add_argument("--profile-every", type=int, default=10,
+                    help="SpMV launches timed in every n-th step of the run after the timed one")
     ap.add_argument("--instances", type=int, default=64, help="batched workload")
     ap.add_argument("--total-nodes", type=int, default=12_000_000, help="batched workload")
     ap.add_argument("--no-graph", action="store_true", help="batched workload")
@@ -719,22 +737,19 @@ def single_workload(args):
     if args.warmup:
         s.run(args.warmup)
         s.prepare(spec.dt)          # back to rest; timing starts from t = 0
-    # HIP events on the SpMV launches of every 10th step of the timed region
-    # (events on every launch would slow the step loop by ~15%)
-    s.set_profiling(args.profile_every)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     _, status = s.run(args.steps)
     torch.cuda.synchronize()
     elapsed = time.perf_counter() - t0
-    st = s.stats()
     iters = s.iterations(args.steps)
+    st = spmv_run(s, min(args.steps, 100), args.profile_every)
     print(f"[bench] {args.steps} steps in {elapsed:.3f} s, mean CG iterations "
           f"{iters.mean():.2f}, status {status}", flush=True)
 
     value = n * args.steps / elapsed
     nnz = st["nnz"]
-    # dominant kernel: the PCG launch carrying q = A p.  Its algorithmic bytes
+    # the PCG launch carrying q = A p.  Its algorithmic bytes
     # (summed by the library over the launches that did the product): per
     # structural nonzero the value and column (12 B FP64, 8 B FP32), per row p
     # read once and q written once (16 B FP64, 8 B FP32)
@@ -768,7 +783,7 @@ def single_workload(args):
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": None, "bytes_per_launch": bytes_avg,
                      "avg_launch_us": 1e6 * spmv_avg, "launches_timed": st["spmv_timed"],
-                     "sampled_every_n_steps": args.profile_every,
+                     "sampled_every_n_steps": args.profile_every, "measured_in": SPMV_RUN,
                      "launches_with_product": st["spmv_work"],
                      "cache_resident": bool((12 if prec == "fp64" else 8) * nnz < 256e6)},
     }
