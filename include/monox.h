@@ -308,11 +308,14 @@ MDX_API mdx_status mdx_set_profiling(mdx_ctx *ctx, int32_t every_n);
  *                        and a solve takes an iteration or two, 0 is the
  *                        faster choice for four threads and more.
  *   MDX_TUNE_ONCHIP_GIVE_UP  for tests of that fallback: e * 512 + w * 256 + g
- *                        has workgroup g of such a launch stop looking at its
- *                        e-th exchange of sums (e >= 1; 0, the default: none);
- *                        with w = 1 not before the launch's outcome is known
- *                        or ONCHIP_POLLS looks have passed.  Results are valid
- *                        with any value.
+ *                        has workgroup g of such a launch stop looking at one
+ *                        exchange of sums, e = 1 + 8 k + c: the first (c = 0)
+ *                        or second (1) of iteration k, or (2, 3, 4) those of a
+ *                        residual replacement after k iterations; 0, the
+ *                        default: none.  With w = 1 it stops when the launch's
+ *                        outcome is known or ONCHIP_POLLS looks have passed.
+ *                        In a batch it looks once at every exchange instead.
+ *                        Results are valid with any value.
  * MAX_GROUPS, SPMV_MAX_GROUPS and ITER_SCHEME take effect at the next
  * mdx_prepare / mdx_run;
  * the batched keys need a prepared batched context and act at once. */

@@ -100,7 +100,7 @@ void enqueue_onchip(mdx_ctx *c, hipStream_t st, const BatchPtrs &q)
     a.zb = c->dev<float>(c->L.oc_z);
     a.words = c->dev<unsigned long long>(c->L.words);
     a.polls = c->onchip_polls;
-    a.give_up = c->onchip_give_up;
+    a.once = c->onchip_give_up.exchange ? c->onchip_give_up.group : -1;
     a.lanes = c->fmt <= 1 ? c->lpr : 1;   // sliced ELL or CSR; 4-entry loads add in column order
     a.turn = c->dev<int32_t>(c->L.oc_turn);
     a.sc = q.bsc;

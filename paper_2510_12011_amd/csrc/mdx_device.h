@@ -281,9 +281,8 @@ __device__ __forceinline__ bool passes(const StopTest &t, double zn)
     return zn < t.atol || zn < t.rtol * t.ref || zn <= t.floor_;
 }
 
-// One wavefront: the scalars (whole 4-byte words) into host-visible memory,
-// a system-scope fence, then the sequence number the host waits for.
-__device__ __forceinline__ void publish_scalars(const Scalars *sc, Published *pub, int32_t seq)
+// One wavefront: the scalars (whole 4-byte words) into host-visible memory.
+__device__ __forceinline__ void copy_scalars(const Scalars *sc, Published *pub)
 {
     static_assert(sizeof(Scalars) % 4 == 0, "whole words");
     constexpr int words = (int)(sizeof(Scalars) / 4);
@@ -292,8 +291,13 @@ __device__ __forceinline__ void publish_scalars(const Scalars *sc, Published *pu
     int32_t *dst = reinterpret_cast<int32_t *>(&pub->s);
     for (int w = lane; w < words; w += 64)
         dst[w] = __hip_atomic_load(src + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// and, behind a system-scope fence, the sequence number the host waits for
+__device__ __forceinline__ void publish_scalars(const Scalars *sc, Published *pub, int32_t seq)
+{
+    copy_scalars(sc, pub);
     __threadfence_system();
-    if (lane == 0) pub->seq = seq;
+    if ((threadIdx.x & 63) == 0) pub->seq = seq;
 }
 
 // A producer kernel's workgroup g stores its NV sums at partial[k * groups + g].

@@ -231,9 +231,9 @@ struct OnchipMap {
     float *val32, *dinv32;    // [pass][quad][thread][4], [position]
     float *r_away, *d_away;   // [position]: FP32 r and correction of the largest blocks
 };
-// For tests: workgroup `group` stops looking at its `exchange`-th exchange (1:
-// the first; 0: none); with `wait` only once the launch's outcome is known, or
-// its polls are used up.
+// For tests: workgroup `group` stops looking at exchange `exchange` (1 + 8 k + c:
+// c of iteration k, as exchange_of() counts; 0: none); with `wait` only once the
+// launch's outcome is known, or its polls are used up.
 struct OnchipGiveUp {
     int exchange, group, wait;
 };
@@ -387,7 +387,7 @@ struct OnchipBatch {
     float *zb;                       // by block position
     unsigned long long *words;       // kOnchipWords
     int polls;
-    OnchipGiveUp give_up;
+    int once;                        // for tests: a workgroup that looks once at each exchange (-1: none)
     int lanes;                       // of a row in the streaming layout (1, 2, 4, 8, 16)
     int32_t *turn;                   // [instance] turn of its next exchange
     BScalars *sc;

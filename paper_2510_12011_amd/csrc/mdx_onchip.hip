@@ -106,17 +106,23 @@ __device__ __forceinline__ void st_agent(T *p, T v)
 // this wavefront's stores have reached the agent's point of coherence
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// The launch's outcome if it has one, else this one: word holds 2 * launch +
-// (1: gave up) from then on.
+// One try to enter the launch's outcome, 2 * launch + (1: gave up), over an
+// earlier launch's: what it found, `was` if the entry now stands.
+__device__ __forceinline__ uint32_t try_settle(uint32_t *word, uint32_t was, uint32_t outcome)
+{
+    __hip_atomic_compare_exchange_strong(word, &was, outcome, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+    return was;
+}
+// The launch's outcome if it has one, else this one.
 __device__ __forceinline__ bool settle(uint32_t *word, unsigned launch, bool gave_up)
 {
-    uint32_t now = (launch - 1) << 1;   // the last launch's, as a rule: one round trip
-    do {
+    uint32_t now = ld_agent(word);
+    while (now >> 1 != launch)   // at most one other entry gets in between
         if (__hip_atomic_compare_exchange_strong(word, &now, launch << 1 | (gave_up ? 1u : 0u),
                                                  __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT))
             return gave_up;
-    } while (now >> 1 != launch);   // at most one other entry gets in between
     return now & 1;
 }
 
@@ -130,38 +136,45 @@ struct ExchangeLds {
 struct Team {
     u64 *words;
     int polls, g, g0, G;
-    int left;   // 2 x exchanges until this workgroup stops looking + OnchipGiveUp::wait (below 2: none)
 };
 // a workgroup's part in a launch with one outcome
 struct SolveTeam : Team {
-    uint32_t *verdict;
-    unsigned launch;
+    const OnchipSolve &a;
+    // exchange at which this workgroup takes its looks for used up (-1: none)
+    int stops_at;
+    __device__ __forceinline__ SolveTeam(const OnchipSolve &a, int g, int G)
+        : Team{a.words, a.polls, g, 0, G}, a(a),
+          stops_at(a.give_up.group == g ? a.give_up.exchange - 1 : -1)
+    {
+    }
+    __device__ __forceinline__ bool stops(int at) const { return at == stops_at; }
     // no more looking: true if the launch gives up
     __device__ __forceinline__ bool gives_up() const
     {
-        const int r = (threadIdx.x & 63) == 0 && settle(verdict, launch, true);
+        uint32_t *const word = &a.sc->onchip_verdict;
+        if (stops_at >= 0 && a.give_up.wait)
+            for (int n = 0; n < polls && ld_agent(word) >> 1 != a.launch;) ++n;
+        const int r = (threadIdx.x & 63) == 0 && settle(word, a.launch, true);
         return __builtin_amdgcn_readfirstlane(r) != 0;
     }
-    __device__ __forceinline__ bool settled() const { return ld_agent(verdict) >> 1 == launch; }
 };
 // the batched form: a kernel behind it looks at every instance's outcome
 struct BatchTeam : Team {
+    __device__ __forceinline__ bool stops(int) const { return false; }
     __device__ __forceinline__ bool gives_up() const { return true; }
-    __device__ __forceinline__ bool settled() const { return true; }
 };
-__device__ __forceinline__ Team team_of(u64 *words, int polls, const OnchipGiveUp &t, int g, int g0, int G)
-{
-    return {words, polls, g, g0, G, t.group == g ? 2 * t.exchange + t.wait : 0};
-}
+// exchanges of iteration `it` (kind 0 p.q, 1 r.z; 2, 3, 4 of a replacement after
+// it), as OnchipGiveUp counts them from 1 on
+__device__ __forceinline__ int exchange_of(int it, int kind) { return 8 * it + kind; }
 
 // Sum v over all threads of the team; false when the wait gave up.
-// turn: 0, 1, 2, 0, ... in successive exchanges.  during() runs once the
-// workgroup's sums are on their way: loads issued there are hidden by the wait
-// (issued before it they would hold up the sums: the store count that orders
-// them counts loads too).
+// turn: 0, 1, 2, 0, ... in successive exchanges; at: which one this is.
+// during() runs once the workgroup's sums are on their way: loads issued there
+// are hidden by the wait (issued before it they would hold up the sums: the store
+// count that orders them counts loads too).
 template <int NV, class T, class F>
-__device__ __forceinline__ bool exchange(double (&v)[NV], ExchangeLds &l, T &team,
-                                         int &turn, F &&during)
+__device__ __forceinline__ bool exchange(double (&v)[NV], ExchangeLds &l, const T &team,
+                                         int &turn, int at, F &&during)
 {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     constexpr size_t TURN = NXCD * 2 * kOnchipGroups;   // slots of a turn: [XCD][value][workgroup]
@@ -191,45 +204,40 @@ __device__ __forceinline__ bool exchange(double (&v)[NV], ExchangeLds &l, T &tea
         }
     }
     during();
-    bool stop = false;
-    if (team.left > 1) {
-        team.left -= 2;
-        stop = team.left < 2;
-    }
     if (w == 0) {
         buf += blockIdx.x % NXCD * (2 * kOnchipGroups) + team.g0;
         constexpr int C = kOnchipGroups / SLICE;
         double acc[NV];
-        int n = 0;
-        if (stop) {
-            if (team.left)
-                while (!team.settled() && n < team.polls) ++n;
-            n = team.polls;
+        bool all = false;
+        // (the outer loop's second pass: the sums that lack are on their way)
+        for (bool look = !team.stops(at);; look = true) {
+            int n = 0;
+            if (look)
+                do {
+                    u64 s[C][NV];
+#pragma unroll
+                    for (int c = 0; c < C; ++c)
+                        if (c * SLICE < G) {
+                            const int slot = c * SLICE + lane;
+#pragma unroll
+                            for (int k = 0; k < NV; ++k)
+                                s[c][k] = slot < G ? ld_agent(buf + k * kOnchipGroups + slot) : 0ull;
+                        }
+                    all = true;
+#pragma unroll
+                    for (int k = 0; k < NV; ++k) acc[k] = 0.0;
+#pragma unroll
+                    for (int c = 0; c < C; ++c)
+                        if (c * SLICE < G)
+#pragma unroll
+                            for (int k = 0; k < NV; ++k) {
+                                all = all && s[c][k] != kEmpty;
+                                acc[k] += __longlong_as_double((long long)s[c][k]);
+                            }
+                    all = __all(all);
+                } while (!all && ++n < team.polls);
+            if (all || team.gives_up()) break;
         }
-        bool all;
-        do {
-            u64 s[C][NV];
-#pragma unroll
-            for (int c = 0; c < C; ++c)
-                if (c * SLICE < G) {
-                    const int slot = c * SLICE + lane;
-#pragma unroll
-                    for (int k = 0; k < NV; ++k)
-                        s[c][k] = slot < G ? ld_agent(buf + k * kOnchipGroups + slot) : 0ull;
-                }
-            all = true;
-#pragma unroll
-            for (int k = 0; k < NV; ++k) acc[k] = 0.0;
-#pragma unroll
-            for (int c = 0; c < C; ++c)
-                if (c * SLICE < G)
-#pragma unroll
-                    for (int k = 0; k < NV; ++k) {
-                        all = all && s[c][k] != kEmpty;
-                        acc[k] += __longlong_as_double((long long)s[c][k]);
-                    }
-            all = __all(all) && !(stop && n == team.polls);
-        } while (!all && (++n < team.polls || !team.gives_up()));
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
             const double t = wave_total63(acc[k]);
@@ -325,13 +333,21 @@ struct Outcome {
     double rho, znorm;
     int it, done, nonfinite, aborted;
 };
-__device__ void report(const OnchipSolve &a, const Start &s, const Outcome &o, int turn)
+// The first workgroup enters "finished", over the last launch's outcome as a
+// rule: before the stores of x and of the scalars and the copy, which hide the
+// way there and back.  (Without an exchange nobody has given up.)
+__device__ __forceinline__ uint32_t enter_finished(const OnchipSolve &a, const Outcome &o)
+{
+    uint32_t found = (a.launch - 1) << 1;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && !o.aborted && o.it > 0)
+        found = try_settle(&a.sc->onchip_verdict, found, a.launch << 1);
+    return found;
+}
+__device__ void report(const OnchipSolve &a, const Start &s, const Outcome &o, int turn, uint32_t found)
 {
     if (blockIdx.x != 0 || threadIdx.x >= SLICE) return;
     Scalars *sc = a.sc;
     if (threadIdx.x == 0) {
-        // (without an exchange nobody can have given up)
-        const int gave_up = o.aborted || (o.it > 0 && settle(&sc->onchip_verdict, a.launch, false));
         st_agent(&sc->rho[o.it & 1], o.rho);
         st_agent(&sc->ref, s.ref);
         st_agent(&sc->floor_, s.floor_);
@@ -343,11 +359,21 @@ __device__ void report(const OnchipSolve &a, const Start &s, const Outcome &o, i
         st_agent(&sc->beta, 0.0);
         st_agent(&sc->it_next, o.it);
         st_agent(&sc->onchip_turn, turn);
-        st_agent(&sc->onchip_gave_up, gave_up);
-        st_agent(&sc->done, gave_up ? 0 : o.done);
+        st_agent(&sc->onchip_gave_up, o.aborted);
+        st_agent(&sc->done, o.aborted ? 0 : o.done);
     }
     stores_done();
-    publish_scalars(sc, a.pub, a.seq);
+    copy_scalars(sc, a.pub);
+    // looked at now: the host and kernels behind this one look after it
+    if (found != (a.launch - 1) << 1 && settle(&sc->onchip_verdict, a.launch, false)) {
+        stores_done();   // the copy, by other lanes
+        st_agent(&sc->onchip_gave_up, 1);
+        st_agent(&sc->done, 0);
+        a.pub->s.onchip_gave_up = 1;
+        a.pub->s.done = 0;
+    }
+    __threadfence_system();
+    if (threadIdx.x == 0) a.pub->seq = a.seq;
 }
 
 // This thread's rows: pass i holds row i * OB + thread of the block, if the
@@ -628,7 +654,7 @@ __global__ __launch_bounds__(OB, waves_per_simd(W, R)) void k_onchip(OnchipSolve
     __shared__ double win[own + kOnchipHalo];
     __shared__ double ldv[R][OB];
     const int G = gridDim.x, g = logical_group(G);
-    SolveTeam team = {team_of(a.words, a.polls, a.give_up, g, 0, G), &a.sc->onchip_verdict, a.launch};
+    const SolveTeam team(a, g, G);
     int t = threadIdx.x;
     unsigned at0 = (unsigned)g * own + t;   // block position of pass i: at0 + i * OB
     double *zb = static_cast<double *>(a.zb);
@@ -655,7 +681,7 @@ __global__ __launch_bounds__(OB, waves_per_simd(W, R)) void k_onchip(OnchipSolve
     Outcome o{st.rho, st.z0, 0, 1, st.finite ? 0 : 2, 0};
     int turn = a.sc->onchip_turn;   // the first workgroup writes it after every exchange
     if (st.done) {
-        report(a, st, o, turn);
+        report(a, st, o, turn, (a.launch - 1) << 1);
         return;
     }
     __syncthreads();
@@ -675,7 +701,7 @@ __global__ __launch_bounds__(OB, waves_per_simd(W, R)) void k_onchip(OnchipSolve
             p[i] = win[i * OB + t] + beta * p[i];
             pq[0] += p[i] * q[i];
         }
-        if (!exchange<1>(pq, xl, team, turn, nothing)) {
+        if (!exchange<1>(pq, xl, team, turn, exchange_of(it, 0), nothing)) {
             o.aborted = 1;
             break;
         }
@@ -692,7 +718,7 @@ __global__ __launch_bounds__(OB, waves_per_simd(W, R)) void k_onchip(OnchipSolve
             v[1] += z * z;
         }
         Halo halo;
-        if (!exchange<2>(v, xl, team, turn, [&] { halo.fetch<double>(a.map.halo_at + h0, nh); })) {
+        if (!exchange<2>(v, xl, team, turn, exchange_of(it, 1), [&] { halo.fetch<double>(a.map.halo_at + h0, nh); })) {
             o.aborted = 1;
             break;
         }
@@ -715,13 +741,14 @@ __global__ __launch_bounds__(OB, waves_per_simd(W, R)) void k_onchip(OnchipSolve
     }
     o.it = it;
     o.rho = rho;
+    const uint32_t found = enter_finished(a, o);
     if (!o.aborted)
 #pragma unroll
         for (int i = 0; i < R; ++i) {
             const int row = a.map.row[at0 + i * OB];
             if (row >= 0) a.x[row] = x[i];
         }
-    report(a, st, o, turn);
+    report(a, st, o, turn, found);
 }
 
 // ---- FP32 iteration with FP64 residual replacement ---------------------------
@@ -738,7 +765,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
     __shared__ float win[own + kOnchipHalo];
     __shared__ float ldv[AWAY ? 1 : R][OB];
     const int G = gridDim.x, g = logical_group(G);
-    SolveTeam team = {team_of(a.words, a.polls, a.give_up, g, 0, G), &a.sc->onchip_verdict, a.launch};
+    const SolveTeam team(a, g, G);
     int t = threadIdx.x;
     unsigned at0 = (unsigned)g * own + t;
     float *zb = static_cast<float *>(a.zb);
@@ -771,7 +798,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
     Outcome o{st.rho, st.z0, 0, 1, st.finite ? 0 : 2, 0};
     int turn = a.sc->onchip_turn;   // the first workgroup writes it after every exchange
     if (st.done) {
-        report(a, st, o, turn);
+        report(a, st, o, turn, (a.launch - 1) << 1);
         return;
     }
     __syncthreads();
@@ -801,7 +828,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
                 p[i] = win[i * OB + t] + bf * p[i];
                 pq[0] += (double)p[i] * (double)q[i];
             }
-            if (!exchange<1>(pq, xl, team, turn, nothing)) {
+            if (!exchange<1>(pq, xl, team, turn, exchange_of(it, 0), nothing)) {
                 o.aborted = 1;
                 out = true;
                 break;
@@ -829,7 +856,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
                 v[0] += (double)r[i] * (double)z;
                 v[1] += (double)z * (double)z;
             }
-            if (!exchange<2>(v, xl, team, turn, [&] { halo.fetch<float>(a.map.halo_at + h0, nh); })) {
+            if (!exchange<2>(v, xl, team, turn, exchange_of(it, 1), [&] { halo.fetch<float>(a.map.halo_at + h0, nh); })) {
                 o.aborted = 1;
                 out = true;
                 break;
@@ -862,7 +889,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
         // them where the values are gone, else a row ahead of its product
         Ahead<R> row;
         double none[1] = {0.0};
-        const bool there = exchange<1>(none, xl, team, turn, [&] {
+        const bool there = exchange<1>(none, xl, team, turn, exchange_of(it, 2), [&] {
             row.places(a.map.row + at0);
             if constexpr (AWAY)
 #pragma unroll
@@ -905,7 +932,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
                 d[i] = 0.0f;
             }
         }
-        if (!exchange<2>(v, xl, team, turn, nothing)) {
+        if (!exchange<2>(v, xl, team, turn, exchange_of(it, 3), nothing)) {
             o.aborted = 1;
             break;
         }
@@ -932,7 +959,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
             win[i * OB + t] = z;
             st_agent(zb + at0 + i * OB, z);
         }
-        if (!exchange<1>(none, xl, team, turn, nothing)) {
+        if (!exchange<1>(none, xl, team, turn, exchange_of(it, 4), nothing)) {
             o.aborted = 1;
             break;
         }
@@ -940,7 +967,8 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
     }
     o.it = it;
     o.rho = rho;
-    report(a, st, o, turn);
+    const uint32_t found = enter_finished(a, o);
+    report(a, st, o, turn, found);
 }
 
 // ---- batched: independent systems, FP32 iteration, FP64 replacement ----------
@@ -976,7 +1004,7 @@ __global__ __launch_bounds__(OB) void k_onchip_batch(OnchipBatch a)
     __shared__ float ldv[R][OB];
     const int g = logical_group(gridDim.x);
     const int4 gr = a.grp[g];
-    BatchTeam team = {team_of(a.words, a.polls, a.give_up, g, gr.y, gr.z)};
+    const BatchTeam team = {{a.words, g == a.once ? 1 : a.polls, g, gr.y, gr.z}};
     int t = threadIdx.x;
     unsigned at0 = (unsigned)g * own + t;
     // the instance's partials, summed by each of its workgroups in one order
@@ -1064,7 +1092,7 @@ __global__ __launch_bounds__(OB) void k_onchip_batch(OnchipBatch a)
             formed(q[i]);
             pq[0] += (double)win[i * OB + t] * (double)q[i];
         }
-        gave_up = !exchange<1>(pq, xl, team, turn, nothing);
+        gave_up = !exchange<1>(pq, xl, team, turn, 0, nothing);
         if (gave_up) break;
         const float alpha = (float)(rho / pq[0]);
         double v[2] = {0.0, 0.0};
@@ -1078,7 +1106,7 @@ __global__ __launch_bounds__(OB) void k_onchip_batch(OnchipBatch a)
             v[1] += (double)z * (double)z;
         }
         Halo halo;
-        gave_up = !exchange<2>(v, xl, team, turn, [&] { halo.fetch<float>(a.map.halo_at + h0, nh); });
+        gave_up = !exchange<2>(v, xl, team, turn, 0, [&] { halo.fetch<float>(a.map.halo_at + h0, nh); });
         if (gave_up) break;
         ++it;
         znorm = sqrt(v[1]);
@@ -1107,7 +1135,7 @@ __global__ __launch_bounds__(OB) void k_onchip_batch(OnchipBatch a)
         }
         Ahead<R> row;
         double none[1] = {0.0};
-        gave_up = !exchange<1>(none, xl, team, turn, [&] {
+        gave_up = !exchange<1>(none, xl, team, turn, 0, [&] {
             row.places(a.map.row + at0);
             row.read(a.r, a.x, a.dinv, 0);
         });
@@ -1133,7 +1161,7 @@ __global__ __launch_bounds__(OB) void k_onchip_batch(OnchipBatch a)
             d[i] = 0.0f;
             v[0] += (double)ri * (double)(ldv[i][t] * ri);
         }
-        gave_up = !exchange<2>(v, xl, team, turn, nothing);
+        gave_up = !exchange<2>(v, xl, team, turn, 0, nothing);
         if (gave_up) break;
         znorm = sqrt(v[1]);
         nonfinite = !isfinite(znorm) || !isfinite(v[0]);
@@ -1152,7 +1180,7 @@ __global__ __launch_bounds__(OB) void k_onchip_batch(OnchipBatch a)
             win[i * OB + t] = pi;
             st_agent(a.zb + at0 + i * OB, pi);
         }
-        gave_up = !exchange<1>(none, xl, team, turn, nothing);
+        gave_up = !exchange<1>(none, xl, team, turn, 0, nothing);
         if (gave_up) break;
         halo.fill(a.zb, win + own, nh);
     }

@@ -2,8 +2,9 @@
 
 Whichever exchange it is, and whether the first workgroup has finished by then
 or not, the run's results are the streaming kernels': a step is either solved
-by the launch or, as a whole, again.  A solve of k iterations has 2 k exchanges
-in FP64 and 2 k + 2 with the FP32 iteration (one residual replacement).
+by the launch or, as a whole, again.  The last exchange of a solve of k
+iterations is the second of iteration k - 1 in FP64 (1 + 8 (k - 1) + 1) and the
+second of the residual replacement after it with the FP32 iteration (1 + 8 k + 3).
 
 Bars as in test_gpu_onchip.py, of V and of the states it drives (1e-11 FP64,
 1e-8 FP32 iteration, of the norm).  Times are ends of steps: one step apart where
@@ -59,23 +60,25 @@ def test_one_workgroup_stops_looking(precision, where, group, wait):
     steps = 1 if where == "last_of_run" else 30
     ref = _reference(precision, steps)
     assert np.isfinite(ref[0]["lat"]).any() and ref[1][0] > 2
-    last = 2 * int(ref[1][0]) + (0 if precision == "fp64" else 2)
-    exchange = {"first": 1, "middle": last - 3}.get(where, last)
+    k = int(ref[1][0])
+    last = 1 + 8 * (k - 1) + 1 if precision == "fp64" else 1 + 8 * k + 3
+    exchange = {"first": 1, "middle": 1 + 8 * (k - 2)}.get(where, last)
     print("[case]", precision, where, group, wait, "exchange", exchange, flush=True)
     got = _run(precision, steps, 3000, (exchange, group, wait))
     _same(got, ref, BAR[precision], 0.01)
 
 
-@pytest.mark.parametrize("exchange,group", [(1, 0), (2, 5), (4, 5), (6, 5)])
-def test_one_workgroup_of_a_batch_stops_looking(exchange, group):
+@pytest.mark.parametrize("group", [0, 2, 5])
+def test_one_workgroup_of_a_batch_stops_looking(group):
+    """It looks once at each exchange: the first at which another is later than it."""
     from paper_2510_12011_amd import sim
     out = []
-    for tuning in (dict(onchip_polls=3000, onchip_give_up=(exchange, group, 0)), dict(onchip_polls=0)):
+    for tuning in (dict(onchip_polls=3000, onchip_give_up=(1, group, 0)), dict(onchip_polls=0)):
         one = [inputs.small_box(nx=n, ny=9, nz=8, lx=0.15 * n, ly=1.4, lz=1.2, seed=n) for n in (12, 20)]
         spec = inputs.BatchSpec(name="boxes", chi=one[0].chi, cm=one[0].cm, theta=0.5, ionic="ms", dt=0.02,
                                 n_steps=40,
                                 instances=[inputs.Instance(o.mesh, 0.17, 0.019, o.stimuli) for o in one])
-        print("[case] batch", exchange, group, tuning, flush=True)
+        print("[case] batch", group, tuning, flush=True)
         s = sim.batch_from_spec(spec)
         s.set_tuning(**tuning)
         _, st = s.run(40)
