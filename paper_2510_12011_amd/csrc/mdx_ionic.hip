@@ -756,13 +756,13 @@ __device__ __forceinline__ void put_gather(const GatherOut &g, int64_t i, double
 // ---------------------------------------------------------------------------
 // The ten Tusscher-Panfilov and Courtemanche-Ramirez-Nattel updates were bound
 // by instruction issue: ~4,000 vector instructions a wavefront, half of them
-// the library's exponentials, logarithms and divisions.  With the functions of cell:: and shared
-// exponentials it is ~1,700, and the state traffic (18 or 20 rows read and
-// written) bounds the large sizes: at 1,255,450 cells 180 -> 117 us and
-// 178 -> 123 us (392 and 432 MB: 82 and 90 us at the copy rate), at 300,007
-// 58 -> 41 and 55 -> 42 us.  Gates are streamed, loaded three ahead of their
-// use: 108 and 117 registers, four wavefronts per SIMD with no spills (with
-// the CRN states held in registers it was 179 and two wavefronts, 134 us).
+// the library's exponentials, logarithms and divisions.  With the functions of
+// cell:: and shared exponentials it is ~1,700, and the state traffic (18 or 20
+// rows read and written) bounds the large sizes: at 1,255,450 cells 180 -> 117
+// us and 178 -> 123 us (392 and 432 MB: 82 and 90 us at the copy rate), at
+// 300,007 58 -> 41 and 55 -> 42 us.  Gates are streamed, loaded three ahead of
+// their use: 106 and 118 registers, four wavefronts per SIMD with no spills
+// (with the CRN states held in registers it was 179 and two wavefronts, 134 us).
 template <int KIND, bool GATHER>
 __global__ __launch_bounds__(256) void k_ionic_step(IonicParams P, int64_t n, int64_t ld, double dt,
                                                     double cm, const double *__restrict__ V,

@@ -5,23 +5,25 @@
 // streaming kernels (mdx_solver.hip, mdx_mixed.hip) spend an iteration on
 // re-reading it and on four to five launches of 2-5 us each.  Here the rows
 // are cut into one compact block per CU (recursive coordinate bisection,
-// onchip_partition in mdx_layout.hip); a 512-thread workgroup loads its block's
+// build_onchip in mdx_layout.hip); a 512-thread workgroup loads its block's
 // values into registers and their 16-bit local columns into LDS once per solve
 // and keeps r, p, q, x (or the FP32 form's correction) in registers until the
 // end.  z of the block and of its halo (the neighbouring blocks' rows that its
 // columns name) lies in LDS, so a row's gathers are LDS reads; per iteration
-// only the halo and one or two FP64 sums per exchange cross workgroups.
+// only the halo and one or two FP64 sums per exchange cross workgroups.  15
+// entries of 8 to 10 rows a thread do not fit: see AWAY below.
 //
-// What bounds it: the two exchanges.  Of an iteration of the 442,401-node FP64
-// slab (17.2 a step; 256 workgroups of 4 rows a thread) the products take
-// 1.1 us, the update 0.7, the halo 0.9 and each exchange 3 (1.3 with 20
-// workgroups); an exchange alone measured 1.8 us at 256 workgroups, 3.0 with
-// one copy of the slots, 2.1-2.3 over two levels.  Time steps, streaming
-// kernels -> this: 9,261-node cube 283 -> 83 us, 58,176-node slab 406 -> 143,
-// 442,401-node slab 696 -> 292 (solve 169), FP32 iteration on 871,221 nodes
-// 464 -> 331 (solve 110 since its replacement reads ahead), on the
-// 1,255,450-node shell with the network 727 -> 684 and, with the values read
-// again instead of spilled, 650 (solve 295).
+// What bounds it: the two exchanges.  An iteration's parts by the clock, us,
+// (products, exchange, update, exchange, halo): 9,261-node FP64 cube, 19
+// workgroups of a row a thread, 0.3 + 1.3 + 0.1 + 1.7 + 0.5; 442,401-node slab,
+// 256 of 4 rows, 1.0 + 2.9 + 0.2 + 3.2 + 0.7; FP32, 871,221 nodes, 7 rows, 2.0 +
+// 3.4 + 0.4 + 3.6 + 0.6; 1,255,450-node shell, 10 rows, 5.1 + 7.0 + 3.0 + 5.2 +
+// 3.4.  Wavefronts wait 64-81% of their cycles.  An exchange alone measured 1.3
+// us at 16 workgroups, 1.8 at 256, there 3.0 with one copy of the slots and 2.1-2.3
+// over two levels.  Time steps, streaming kernels -> this (solve): cube 283 -> 82
+// us (65-67), 58,176-node slab 406 -> 133 (108-111), 442,401-node slab 696 ->
+// 258 (171-178), FP32 iteration on 871,221 nodes 464 -> 263 (106-115), learned
+// 1,255,450-node shell 727 -> 569 (300-315).
 // Gathering z through the caches instead of LDS took 4.3 us of the FP64 slab's
 // iteration and 14 of the shell's.
 //
@@ -40,15 +42,16 @@
 // Slots are kept once per XCD (fewer pollers per line) and in three turns: on
 // leaving exchange e a workgroup empties its slots of exchange e - 1 (every
 // workgroup has left that one: it has written e), and they are empty before it
-// writes e + 1, so before any workgroup looks for e + 2 in them.  What crosses workgroups is stored and loaded with agent scope
-// (write-through past the XCD's L2, read past it) and complete (vmcnt) before
-// the slot is written, so no cache is flushed or invalidated.
+// writes e + 1, so before any workgroup looks for e + 2 in them.  What crosses
+// workgroups is stored and loaded with agent scope (write-through past the XCD's
+// L2, read past it) and complete (vmcnt) before the slot is written, so no cache
+// is flushed or invalidated.
 //
-// The wait needs every workgroup resident: at most one per CU is launched, and
-// launches run together only as far as the CUs reach (OnchipCus).  Polls are bounded:
-// where other work keeps a workgroup off the chip for long, the launch gives
-// up and changes nothing but scratch and x; the host then forms the step's
-// right-hand side again and solves it with the streaming kernels.
+// The wait needs every workgroup resident: a launch has at most one per CU, and
+// launches are in flight together only as far as the CUs reach (OnchipCus).
+// Polls are bounded: where other work keeps a workgroup off the chip for long,
+// the launch gives up and changes nothing but scratch and x; the host then forms
+// the step's right-hand side again and solves it with the streaming kernels.
 //
 // A launch has one outcome: a workgroup whose polls are used up enters "gave
 // up", the first workgroup "finished" where it has seen the last exchange, and
@@ -753,9 +756,12 @@ __global__ __launch_bounds__(OB, waves_per_simd(W, R)) void k_onchip(OnchipSolve
 
 // ---- FP32 iteration with FP64 residual replacement ---------------------------
 // LQ: quads of columns in LDS (fewer than all where R rows' would not fit).
-// AWAY: r and the correction, which the product does not need, are kept in
-// memory by block position (they stay in the L2) and come back for the
-// update: with them the largest blocks do not fit.
+// AWAY: r, the correction and D^-1, which the product does not need, are kept in
+// memory by block position and come back for the update: with them the largest
+// blocks do not fit.  Nor do they quite without: 10 rows of 15 entries spill 672
+// bytes a lane (8 rows 408), and by counters a solve of the 1,255,450-node shell
+// moves 717 MB in and 355 MB out beyond the L2s where its matrix and vectors are
+// some 180 MB.
 template <int W, int R, int LQ, bool AWAY>
 __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
 {
@@ -986,7 +992,7 @@ __global__ __launch_bounds__(OB) void k_onchip32(OnchipSolve a)
 //
 // Solve of a step, streaming kernels -> this (and the whole step, with the
 // ionic update's fused passes): 12 unstructured shells of 232,472 nodes in
-// all, 4.0 iterations, 130 -> 47 us (187 -> 96); 8 surfaces of 1,310,736, 1.8
+// all, 4.0 iterations, 130 -> 49 us (187 -> 96); 8 surfaces of 1,310,736, 1.8
 // iterations, 165 -> 69 (280 -> 171).
 // Bound by one read of the values and columns (23 and 45 MB), the replacement's
 // read of the FP64 values and some 3 us per exchange.
